@@ -3,7 +3,7 @@
 One step = the whole hot path over one batch of 32 configurations of the
 read-only DML SQL workload (V = 151,936): prologue (allowed terminals, EOS
 gate, first-shift summaries), class verdicts, the id-ordered mask stream, the
-residue walk, row finalize, and the -inf fill of bf16 logits [32, V].  Steps
+residue walk with the row status, and the -inf fill of bf16 logits [32, V].  Steps
 cycle through distinct, device-resident config batches; the mask cache is not
 used (every step is a cold mask).
 
@@ -39,7 +39,7 @@ sys.path.insert(0, str(ROOT))
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_PROFILE = ROOT / "profiles" / "mask_traffic_dml_b32.md"
 KERNEL_SOURCE = ROOT / "paper_2607_11951_amd" / "csrc" / "kernels.hip"
-MASK_KERNELS = ("prologue_kernel", "verdict_kernel", "stream_kernel", "residue_kernel", "finalize_kernel")
+MASK_KERNELS = ("prologue_kernel", "judge_kernel", "stream_kernel", "residue_kernel")
 
 
 def mask_traffic_bytes():
@@ -578,7 +578,7 @@ def main():
         "p50_step_us": float(np.percentile(step_us, 50)),
         "p99_step_us": float(np.percentile(step_us, 99)),
         "phase_us": {k: v["us"] for k, v in per_phase.items()},
-        "roofline": {"bound": "hbm", "kernel": "grid_mask (prologue, verdict, stream, residue, finalize kernels)",
+        "roofline": {"bound": "hbm", "kernel": "grid_mask (prologue, judge, stream, residue kernels)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": mask_traffic_bytes(), "bytes_per_launch": bytes_step,
                      "mask_us_per_launch": mask_s * 1e6, "dominant_phase": dominant,

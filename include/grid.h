@@ -222,7 +222,9 @@ enum {
   GRID_ART_PARSE_SHIFT,     /* u16 per shift entry of the ACTION table: per LR state, in
                                terminal order, the target state of every terminal whose
                                PARSE_STATE shift bit is set (0 for accept); terminal t's
-                               target is entry (shift bits below t) of the state's run */
+                               target is entry (shift bits below t) of the state's run.
+                               After the runs, from the next 16-byte boundary, the mask
+                               kernels' dense action table */
   GRID_ART_STATE_SYMBOL,    /* u32 [n_lr]: the symbol on which the LR automaton enters each
                                state (terminal id, or 0x10000 | nonterminal index;
                                0xFFFFFFFF for the initial state) -- the "goto" of the
@@ -243,6 +245,21 @@ enum {
                                Unit states are never left on a stack after a shift, so the
                                stacks after every shift are those of GOTO; a lookahead the
                                unit state would refuse is refused later in the chain */
+  GRID_ART_PROG_MAP,        /* u16 [S][V], u32 [S+1], u32 [classes][4]: the classes of the */
+  GRID_ART_PROG_OFF,        /* reduced lexeme programs, laid out as CLASS_MAP, CLASS_OFF and */
+  GRID_ART_PROG_REC,        /* CLASS_REC: lexemes that are ignored under any configuration
+                               (white space, comments) are left out, states that accept any
+                               trailing lexeme are one, and byte positions are kept only
+                               where a lexicon may be asked about, so there are fewer classes
+                               and fewer tokens that end more lexemes than a record holds.
+                               Record: ends | 16 | 32 as CLASS_REC | 64 if what was left out
+                               held the pending lexeme | starts of lexemes 1 and 2 and of the
+                               trailing lexeme in bits 8..31 (8 bits each); two words of
+                               states; ends of lexemes 0, 1, 2 and the start of lexeme 0.
+                               Optional: with the three of them bound the kernels judge these
+                               classes and the three CLASS_* artifacts need not be bound;
+                               without them they judge those of CLASS_*.  The masks are the
+                               same */
   GRID_ART_COUNT
 };
 int grid_artifact(const grid_compiled* g, int32_t which, const void** host_ptr, size_t* bytes);
@@ -300,12 +317,12 @@ int grid_mask(const grid_compiled* g, int32_t B, const grid_config* cfg_dev,
                                        row's lexer state */
 #define GRID_PHASE_WALK 2u          /* mask_dev in token-id order from the class map;
                                        tokens whose class needs their own bytes are
-                                       marked in the row's residue bitmaps (workspace) */
-#define GRID_PHASE_RESIDUE 4u       /* the marked spellings: class verdict with their own
-                                       lexicon flags, else the byte walk; allowed bits
-                                       are OR-ed into mask_dev */
-#define GRID_PHASE_FINALIZE 8u      /* tokens the residue walk handed to the slow path,
+                                       listed in the row's workspace */
+#define GRID_PHASE_RESIDUE 4u       /* the listed tokens judged to their end with their
+                                       own bytes; allowed bits are OR-ed into mask_dev;
                                        then the row status when status_dev is not null */
+#define GRID_PHASE_FINALIZE 8u      /* the caches' new entries published (nothing without
+                                       a cache) */
 #define GRID_PHASE_ALL 15u
 int grid_mask_phases(const grid_compiled* g, int32_t B, const grid_config* cfg_dev,
                      const uint16_t* stack_pool_dev, uint32_t* mask_dev, uint8_t* eos_dev,

@@ -157,20 +157,45 @@ VocabArtifacts build_vocab(const uint8_t* bytes, const uint64_t* off, int V, con
   return va;
 }
 
-ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va) {
+void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
+                        ClassTables& full, ClassTables& reduced) {
   const size_t U = va.spell_off.size() - 1;
   const size_t S = (size_t)dfa.S, V = (size_t)va.V;
   if (S * V > ((size_t)3 << 29))
     throw Error(GRID_E_CAPACITY, "class map of " + std::to_string(S) + " lexer states x " + std::to_string(V) +
                                      " tokens is larger than 3 GiB");
-  ClassTables ct;
-  ct.map.assign(S * V, 0);
-  std::vector<std::vector<uint32_t>> recs(S);
-  // the lexeme program of spelling u when the scan resumes in q
-  auto program = [&](uint32_t q, size_t u, uint32_t (&r)[4]) {
+  // what the reduced programs leave out, per state
+  const size_t T = term_info.size();
+  auto plain_ignored = [&](size_t t) { return (term_info[t] & 1u) && (term_info[t] >> 8) == 0xFFu; };
+  auto category = [&](size_t t) { return (term_info[t] >> 8) != 0xFFu; };
+  std::vector<uint8_t> skip(S, 0), asks(S, 0), asks_trail(S, 0);
+  std::vector<uint32_t> last(S);  // the state that stands for it after the last byte
+  uint32_t any_trail = 0;         // the first state that accepts any trailing lexeme
+  for (size_t q = 0; q < S; ++q) {
+    const uint32_t lo = dfa.accept_off[q], hi = dfa.accept_off[q + 1];
+    skip[q] = hi > lo && plain_ignored(dfa.accept_list[lo]);
+    for (uint32_t j = lo; j < hi; ++j) asks[q] |= category(dfa.accept_list[j]);
+    bool always = false;
+    for (size_t t = 0; t < T; ++t) {
+      if (!((dfa.live[q * kTermWords + (t >> 5)] >> (t & 31)) & 1u)) continue;
+      always = always || plain_ignored(t);
+      asks_trail[q] |= category(t);
+    }
+    last[q] = (uint32_t)q;
+    if (always) {
+      if (!any_trail) any_trail = (uint32_t)q;
+      last[q] = any_trail;
+      asks_trail[q] = 0;
+    }
+  }
+  // the lexeme program of spelling u when the scan resumes in q (r), and the
+  // reduced one (p)
+  auto program = [&](uint32_t q, size_t u, uint32_t (&r)[4], uint32_t (&p)[4]) {
     const uint8_t* b = va.spell_bytes.data() + va.spell_off[u];
     const uint32_t n = va.spell_off[u + 1] - va.spell_off[u];
     uint32_t cur = q, ends = 0, qe[kClassEnds] = {0, 0, 0}, pe[kClassEnds] = {0, 0, 0}, flags = 0;
+    uint32_t kept = 0, kq[kClassEnds] = {0, 0, 0}, ks[kClassEnds] = {0, 0, 0}, ke[kClassEnds] = {0, 0, 0}, kflags = 0;
+    uint32_t start = 0;  // of the current lexeme
     for (uint32_t i = 0; i < n; ++i) {
       const uint32_t nq = dfa.step((int)cur, b[i]);
       if (nq != (uint32_t)kDead) {
@@ -188,7 +213,19 @@ ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va) {
         qe[ends] = cur;
         pe[ends] = i;
       }
+      if (skip[cur]) {
+        if (ends == 0) kflags |= kProgFresh;
+      } else {
+        if (i == 0) kflags |= kClassP0;
+        if (kept < (uint32_t)kClassEnds) {
+          kq[kept] = cur;
+          ks[kept] = start;
+          ke[kept] = i;
+        }
+        ++kept;
+      }
       ++ends;
+      start = i;
       cur = dfa.step(kStart, b[i]);
       if (cur == (uint32_t)kDead) {
         r[0] = kClassReject, r[1] = r[2] = r[3] = 0;
@@ -199,6 +236,17 @@ ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va) {
     r[1] = cur | qe[0] << 16;
     r[2] = qe[1] | qe[2] << 16;
     r[3] = pe[0] | pe[1] << 8 | pe[2] << 16;
+    const bool more = kept > (uint32_t)kClassEnds;
+    for (int j = 0; j < kClassEnds; ++j)
+      if (!asks[kq[j]]) {
+        ks[j] = 0;
+        if (!(more && j == kClassEnds - 1)) ke[j] = 0;
+      }
+    const uint32_t st = more || !asks_trail[cur] ? 0u : start;
+    p[0] = (more ? kClassMore : kept) | kflags | ks[1] << 8 | ks[2] << 16 | st << 24;
+    p[1] = (more ? 0u : last[cur]) | kq[0] << 16;
+    p[2] = kq[1] | kq[2] << 16;
+    p[3] = ke[0] | ke[1] << 8 | ke[2] << 16 | ks[0] << 24;
   };
   struct Key {
     uint32_t a, b, c, d;
@@ -211,53 +259,74 @@ ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va) {
       return (size_t)(h ^ (h >> 29));
     }
   };
+  // one table's classes of one state: the records and every spelling's class
+  struct State {
+    std::unordered_map<Key, uint32_t, KeyHash> seen;
+    std::vector<uint16_t> local;
+    void start(std::vector<uint32_t>& rq) {
+      seen.clear();
+      rq = {kClassReject, 0, 0, 0, kClassWalk, 0, 0, 0};  // local classes 0 and 1
+    }
+    void add(std::vector<uint32_t>& rq, size_t u, const uint32_t (&r)[4]) {
+      auto it = seen.find(Key{r[0], r[1], r[2], r[3]});
+      if (it != seen.end()) {
+        local[u] = (uint16_t)it->second;
+        return;
+      }
+      const uint32_t c = (uint32_t)(rq.size() / 4);
+      if (c >= kClassMaxLocal) {  // beyond capacity: this token walks its bytes
+        local[u] = 1;
+        return;
+      }
+      seen.emplace(Key{r[0], r[1], r[2], r[3]}, c);
+      rq.insert(rq.end(), {r[0], r[1], r[2], r[3]});
+      local[u] = (uint16_t)c;
+    }
+  };
+  ClassTables* const out[2] = {&full, &reduced};
+  std::vector<std::vector<uint32_t>> recs[2];
+  for (int k = 0; k < 2; ++k) {
+    out[k]->map.assign(S * V, 0);
+    recs[k].resize(S);
+  }
   const int nt = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   std::vector<std::thread> pool;
   for (int w = 0; w < nt; ++w)
     pool.emplace_back([&, w]() {
-      std::vector<uint16_t> local(U);
-      std::unordered_map<Key, uint32_t, KeyHash> seen;
+      State st[2];
+      for (State& x : st) x.local.resize(U);
       for (size_t q = (size_t)w; q < S; q += (size_t)nt) {
-        seen.clear();
-        std::vector<uint32_t>& rq = recs[q];
-        rq = {kClassReject, 0, 0, 0, kClassWalk, 0, 0, 0};  // local classes 0 and 1
+        for (int k = 0; k < 2; ++k) st[k].start(recs[k][q]);
         for (size_t u = 0; u < U; ++u) {
-          uint32_t r[4];
-          program((uint32_t)q, u, r);
+          uint32_t r[4], p[4];
+          program((uint32_t)q, u, r, p);
           if (r[0] & kClassReject) {
-            local[u] = 0;
+            st[0].local[u] = st[1].local[u] = 0;
             continue;
           }
-          auto it = seen.find(Key{r[0], r[1], r[2], r[3]});
-          if (it != seen.end()) {
-            local[u] = (uint16_t)it->second;
-            continue;
-          }
-          const uint32_t c = (uint32_t)(rq.size() / 4);
-          if (c >= kClassMaxLocal) {  // beyond capacity: this token walks its bytes
-            local[u] = 1;
-            continue;
-          }
-          seen.emplace(Key{r[0], r[1], r[2], r[3]}, c);
-          rq.insert(rq.end(), {r[0], r[1], r[2], r[3]});
-          local[u] = (uint16_t)c;
+          st[0].add(recs[0][q], u, r);
+          st[1].add(recs[1][q], u, p);
         }
-        uint16_t* m = ct.map.data() + q * V;
-        for (size_t id = 0; id < V; ++id) {
-          const uint32_t u = va.spell_of_id[id];
-          m[id] = u == 0xFFFFFFFFu ? (uint16_t)0 : local[u];
+        for (int k = 0; k < 2; ++k) {
+          uint16_t* m = out[k]->map.data() + q * V;
+          for (size_t id = 0; id < V; ++id) {
+            const uint32_t u = va.spell_of_id[id];
+            m[id] = u == 0xFFFFFFFFu ? (uint16_t)0 : st[k].local[u];
+          }
         }
       }
     });
   for (auto& th : pool) th.join();
-  ct.off.assign(S + 1, 0);
-  for (size_t q = 0; q < S; ++q) {
-    ct.off[q + 1] = ct.off[q] + (uint32_t)(recs[q].size() / 4);
-    ct.max_classes = std::max(ct.max_classes, ct.off[q + 1] - ct.off[q]);
+  for (int k = 0; k < 2; ++k) {
+    ClassTables& ct = *out[k];
+    ct.off.assign(S + 1, 0);
+    for (size_t q = 0; q < S; ++q) {
+      ct.off[q + 1] = ct.off[q] + (uint32_t)(recs[k][q].size() / 4);
+      ct.max_classes = std::max(ct.max_classes, ct.off[q + 1] - ct.off[q]);
+    }
+    ct.rec.reserve((size_t)ct.off[S] * 4);
+    for (size_t q = 0; q < S; ++q) ct.rec.insert(ct.rec.end(), recs[k][q].begin(), recs[k][q].end());
   }
-  ct.rec.reserve((size_t)ct.off[S] * 4);
-  for (size_t q = 0; q < S; ++q) ct.rec.insert(ct.rec.end(), recs[q].begin(), recs[q].end());
-  return ct;
 }
 
 uint32_t LexiconStore::child(int slot, uint32_t node, uint8_t b) const {

@@ -65,7 +65,7 @@ extern "C" int grid_compile(const grid_compile_args* a, grid_compiled** out) {
     }
     g->vocab = build_vocab(a->vocab_bytes, a->vocab_offsets, a->vocab_size, a->special_ids,
                            a->n_special, a->eos_id);
-    g->classes = build_class_tables(g->dfa, g->vocab);
+    build_class_tables(g->dfa, g->vocab, g->term_info, g->classes, g->progs);
     add_lexicon(g->lex, g->dfa, g->gram, g->vocab, g->term_cat, {});  // slot 0: no restrictions
     // FNV-1a over the tables a cached mask row depends on
     uint32_t fp = 2166136261u;
@@ -207,6 +207,9 @@ extern "C" int grid_artifact(const grid_compiled* g, int32_t which, const void**
     case GRID_ART_CLASS_MAP: put(g->classes.map, p, n); break;
     case GRID_ART_CLASS_OFF: put(g->classes.off, p, n); break;
     case GRID_ART_CLASS_REC: put(g->classes.rec, p, n); break;
+    case GRID_ART_PROG_MAP: put(g->progs.map, p, n); break;
+    case GRID_ART_PROG_OFF: put(g->progs.off, p, n); break;
+    case GRID_ART_PROG_REC: put(g->progs.rec, p, n); break;
     case GRID_ART_LEX_STRIDE: put(g->lex.stride, p, n); break;
     case GRID_ART_LEX_TOKEN: put(g->lex.token, p, n); break;
     case GRID_ART_ID_FIRST: put(g->vocab.id_first, p, n); break;

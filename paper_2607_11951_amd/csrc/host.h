@@ -20,6 +20,7 @@ constexpr int kMaxCategories = 8;
 constexpr uint32_t kNoLex = 0xFFFFFFFFu;
 constexpr uint16_t kActShift = 0x4000, kActReduce = 0x8000, kActAccept = 0xC000;
 constexpr uint16_t kNoGoto = 0xFFFF;
+constexpr uint32_t kMactShift = 0x8000, kMactPushed = 0x4000;  // entries of the mask kernels' action table
 constexpr uint32_t kSymNonterminal = 0x10000u, kNoSymbol = 0xFFFFFFFFu;
 constexpr int kDead = 0, kStart = 1;   // lexer DFA state numbering
 
@@ -87,7 +88,13 @@ struct Parser {
   int tw = 0;
   std::vector<uint32_t> pstate;
   std::vector<uint32_t> predx;     // extra reduce groups: [production][bits TW]
-  std::vector<uint16_t> pshift;    // shift targets per state, in terminal order (record word 2TW+2)
+  std::vector<uint16_t> pshift;    // shift targets per state, in terminal order (record word 2TW+2);
+                                   // from entry mact_off: the mask kernels' action table (u16 [states][T+1])
+  uint32_t mact_off = 0;           // a multiple of 8
+  uint32_t n_shift_runs = 0;       // entries of pshift before it
+  int mact_bits = 0;               // bits of the left side in a reduce entry; 0: entries index mact_red
+  uint32_t mact_red_off = 0;       // where those reductions start in pshift (u32 each: lhs | pops << 16)
+  uint32_t n_mact_red = 0;
   // GOTO as an open-addressing hash of H (power of two) u32 pairs: key
   // (state << 16 | nonterminal) + 1 (0 empty), target
   std::vector<uint32_t> goto_hash;
@@ -139,7 +146,10 @@ struct ClassTables {
   std::vector<uint32_t> rec;   // [classes][4]
   uint32_t max_classes = 0;    // largest class count of one state
 };
-ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va);
+// The class tables of the exported lexeme programs, and those of the reduced
+// programs the kernels read (lexhash.h).
+void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
+                        ClassTables& full, ClassTables& reduced);
 
 // ---- lexicon slots
 struct LexiconStore {
@@ -178,6 +188,8 @@ struct grid_compiled {
   grid::VocabArtifacts vocab;
   grid::LexiconStore lex;
   grid::ClassTables classes;          // lexeme-program classes
+  grid::ClassTables progs;            // those of the reduced programs
+  uint32_t max_classes() const { return classes.max_classes > progs.max_classes ? classes.max_classes : progs.max_classes; }
   uint32_t fingerprint = 0;           // of the lexer, parser and vocabulary (mask-cache entries)
   uint32_t family_fp = 0;             // of the lexer and vocabulary only (shared by every role)
   std::vector<int> term_cat;          // category index per terminal or -1

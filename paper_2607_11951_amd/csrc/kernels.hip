@@ -1,44 +1,40 @@
 // kernels.hip -- device side of the cold exact mask and the -inf apply (gfx950).
 //
 // grid_mask launches, on the caller's stream:
-//  1. prologue (one workgroup per row; compact LR tables and the top of the
-//     row's stack in LDS): thread t runs terminal t's reduce chain and shift
-//     from sigma, so A(sigma) (section 3.2, allowed terminals under table
-//     compression) is the set that shifted and each one's post-shift stack (an
-//     overlay above the shared read-only stack) is recorded; the allowed set
-//     of every post-shift stack follows by set simulation (one reduce chain
-//     for a whole terminal set), and the end-of-sequence gate (section 3.2) is
-//     run after each candidate winner's shift and from sigma.  Then the
-//     pending lexeme's winner, the trailing-flag tables of every lexer state
-//     under A(sigma) and after the winner's shift (Definition 2), and the
+//  1. prologue (one 1024-thread workgroup per row; the dense action and GOTO
+//     tables and the top of the row's stack in LDS): thread t runs terminal t's
+//     reduce chain and shift from sigma, so A(sigma) (section 3.2, allowed
+//     terminals under table compression) is the ballot of those that shifted, and
+//     each one's post-shift stack (an overlay above the shared read-only stack) is
+//     recorded; the allowed set of every post-shift stack follows the same way, a
+//     wave per 64 terminals, the end of input as one more; then the
+//     end-of-sequence gate (section 3.2), the pending lexeme's winner and the
 //     bytes that continue the pending lexeme in the schema lexicon.
-//  2. verdicts (one thread per lexeme-program class of the row's lexer
-//     state): tokens whose lexeme programs from that state are equal share a
-//     class (the verdict-equivalence idea of section 4.2, fixed at compile
-//     time per state); each class is judged once against A(sigma) and the
-//     prologue's allowed sets after a first shift -- reject, allow, walk (a
-//     second shift or more than three lexeme ends) or lexicon (the verdict
-//     depends on the token's own lexicon flags, section 2 L3).
-//  3. stream (XCD-aware, 64 ids per wave): the mask in token-id order
-//     straight from the class map, one ballot per 64 ids; lexicon classes are
-//     settled by a shortcut where the token's first byte or its token-flag
-//     entry answers the class's first lexicon question; the rest mark their
-//     spellings in the row's residue bitmaps.
-//  4. residue (one 1024-thread workgroup per compute unit): marked
-//     spellings in spelling order, a few per wave; lexicon spellings re-run
-//     their class verdict with their own lexicon flags; the others walk their
-//     bytes (section 4.1): DFA steps in LDS, a byte that kills the DFA emits
-//     the pending lexeme as the highest-priority candidate that is allowed (or
-//     ignored) and passes the lexicon, later shifts simulated on the lane's LDS
-//     overlay; the allowed ids are OR-ed into the mask.  A lane whose stack
-//     area is too small hands its spelling to the slow path.
-//  5. finalize: the slow path re-walks handed-over spellings with a large
-//     stack area, then the row status (Proposition 8: a viable configuration
-//     has a nonempty mask); with a mask cache, the rows' masks are published.
+//  2. judge (one thread per lexeme-program class of the row's lexer state):
+//     tokens whose lexeme programs from that state are equal share a class (the
+//     verdict-equivalence idea of section 4.2, fixed at compile time per state);
+//     each class is judged once against A(sigma) and the allowed sets after a
+//     first shift -- reject, allow, walk (a second shift or more than three lexeme
+//     ends) or lexicon (the verdict depends on the token's own lexicon flags,
+//     section 2 L3).
+//  3. stream (512 ids per wave step): the mask in token-id order straight from
+//     the class map, a byte per lane; lexicon classes are settled by a shortcut
+//     where the token's first byte or its token-flag entry answers the class's
+//     first lexicon question; the ids left open go to the row's list.
+//  4. residue (one 1024-thread workgroup per compute unit): the open ids of the
+//     whole batch dealt evenly, a few per wave; each is judged to its end, from
+//     its class's record with its own lexicon flags and, past the record, by DFA
+//     steps over its bytes (section 4.1), later shifts on the lane's LDS overlay;
+//     the allowed ids are OR-ed into the mask.  An id whose stack area is too
+//     small is judged again with a large one.  The last chunk of a row writes its
+//     status (Proposition 8: a viable configuration has a nonempty mask).
+//  5. with a mask cache or a context-independent word cache: the rows' new entries
+//     are published.
 // grid_apply is a streaming in-place -inf fill of the masked logits.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <cstdint>
 #include <string>
@@ -57,32 +53,41 @@ using namespace grid;
 namespace {
 
 constexpr int kBlock = 256;          // workgroup size of most kernels
-constexpr int kProThreads = 512;     // prologue workgroup size (more set-simulation jobs per row)
+constexpr int kProThreads = 1024;    // prologue workgroup size (one per row)
 constexpr int kStackWin = 256;       // top of the row's stack kept in LDS (prologue)
 constexpr int kPostCap = 14;         // overlay states recorded per first shift
-constexpr int kTmpCap = 32;          // prologue: virtual pushes of one simulation
 constexpr int kGuard = 4096;         // reduce-chain step bound
-constexpr int kSlowCap = 4096;       // tokens handed to the slow path per row
-constexpr int kSlowThreads = 64;
-constexpr int kSlowLane = 512;       // slow path per-thread stack area (workspace)
 constexpr uint32_t kRowValid = 0x600D;
 constexpr size_t kWsHead = 256;      // workspace head (reserved)
-constexpr int kMaxRounds = 257;      // set-simulation reruns (each peels one reduce group)
 
-// residue walk launch shape: one 1024-thread workgroup per compute unit
-constexpr int kWalkThreads = 1024;
-constexpr int kFastLane = 16;        // per-lane stack area in LDS (overlay at the bottom,
-                                     // virtual pushes above it)
-constexpr int kRowGroup = 32;        // rows resident in LDS at once (at most)
 constexpr int kWalkWin = 64;         // top stack entries of each row in the walk's LDS
-constexpr int kMaxItems = 1024;      // residue work items a workgroup scans at once
-constexpr int kWalkChunk = 16;       // byte-walk spellings a wave takes at a time
-constexpr int kLexChunk = 32;        // lexicon spellings a wave takes at a time
-constexpr int kLaneSlots = 32;       // lanes of a wave with a stack area in the residue LDS
-static_assert(kWalkChunk <= kLaneSlots && kLexChunk <= kLaneSlots, "chunks fit the lane stack areas");
-static_assert((kLaneSlots & (kLaneSlots - 1)) == 0, "kLaneSlots is a power of two");
+constexpr int kJudgeThreads = 512;   // workgroup size of the judge kernel
+
+// stream kernel
+constexpr int kStreamThreads = 512;
+constexpr int kStreamWaves = kStreamThreads / 64;
+constexpr int kStepIds = 512;        // ids of one wave step (8 per lane)
+constexpr int kOpenList = 8192;      // open ids a row lists at most
+constexpr int kOpenLocal = 1024;     // and one stream workgroup
+constexpr uint32_t kListFull = 1u << 30;  // in a row's count: some open ids are not listed
+
+// residue kernel
+constexpr int kResThreads = 1024;
+constexpr int kResWaves = kResThreads / 64;
+constexpr int kChunkMin = 64;        // open ids a workgroup takes at a time, about
+constexpr int kChunkMax = 512;
+constexpr int kQueue = kChunkMax + kStepIds;  // and at most (a whole last step)
+constexpr int kTableThreads = kResThreads - kChunkMax;  // those that take no listed id stage the tables
+constexpr int kCountRegs = 4;        // rows' counts a lane keeps
+constexpr int kLanesMax = 32;        // ids a wave takes at a time, at most
+constexpr int kFastLane = 16;        // per-lane stack area of a byte walk (overlay at the
+                                     // bottom, virtual pushes above it)
+constexpr int kSlowLane = 512;       // the same for a walk that outgrew it
+constexpr int kSlowWaves = kResWaves * kLanesMax * kFastLane / kSlowLane;  // walks that fit in its place
 static_assert(kStackWin == kBlock, "one stack-window entry per prologue thread");
-constexpr uint32_t kWalkLdsMax = 160 * 1024;
+constexpr uint32_t kLdsMax = 160 * 1024;
+constexpr uint32_t kLdsStatic = 4096;     // LDS the judge and mask kernels declare statically, at most
+constexpr uint32_t kTablesMax = 133328;   // lexer and LR tables, the largest that are supported
 
 struct Tables {
   const uint16_t* dfa;        // [S*C]
@@ -90,7 +95,11 @@ struct Tables {
   const uint32_t* acc_off;    // [S+1]
   const uint8_t* acc_list;
   const uint32_t* live;       // [S*8]
-  const uint16_t* action;     // [NS*(T+1)] (shift targets)
+  const uint16_t* action;     // [NS*(T+1)] LALR actions
+  const uint32_t* prod;       // [P] lhs | length << 16
+  const uint16_t* mact;       // [NS*(T+1)] the mask kernels' actions
+  const uint32_t* mred;       // their reductions, when entries are indices
+  int mbits;                  // bits of the left side in a reduce entry, 0: an index
   const uint32_t* term_info;  // [T]
   const uint32_t* pstate;     // [NS][parse_record_words(tw)]
   const uint32_t* predx;
@@ -99,8 +108,6 @@ struct Tables {
   const uint8_t* spell_bytes;
   const uint4* spell_rec;     // [U]: head lo, head hi, first id | multi << 31, length | chunk << 8
   const uint4* spell_tail;    // chunk u: bytes 8..23 of spelling u; overflow chunks after
-  const uint32_t* alias_off;  // [U+1]
-  const int32_t* alias_ids;
   const uint32_t* spell_of_id;  // [V]
   const uint16_t* lex_flags;
   const uint32_t* lex_hash;
@@ -116,6 +123,7 @@ struct Tables {
   const uint4* crec;          // class records
   int S, C, T, N, NS, P, U, V, W, n_slots, eos_id;
   int max_classes;            // largest class count of one lexer state
+  int prog;                   // the classes are those of the reduced programs
   const uint16_t* pshift;      // shift targets per LR state
   const uint16_t* go;          // dense GOTO [states][N], kNoGoto none
   int tw, n_pstate, n_predx, n_pshift, n_acc, hbits;
@@ -178,7 +186,6 @@ __device__ inline uint64_t stack_mix(uint32_t i, uint32_t s, uint64_t salt) {
 // stack window to LDS in one piece).
 struct RowHeader {
   uint32_t A[8];              // allowed terminals of sigma
-  uint32_t Aw[8];             // allowed terminals after shifting the winner
   uint32_t R[8];              // terminals whose category the row's lexicon restricts
   uint32_t slot[kSlotWords];  // the row's lexicon slot record (the words Slot holds; the rest 0)
   uint32_t cont[8];           // bytes b such that (pending lexeme) b prefixes a lexicon word
@@ -188,19 +195,18 @@ struct RowHeader {
   uint32_t wkind;             // 0 no winner, 1 the winner is ignored, 2 it shifts
   uint32_t stk_off, stk_depth, q, lexnode;
   uint32_t rem_lo, rem_hi, rem_len;  // first 8 bytes and length of the pending lexeme
-  uint32_t slow_count;
   int32_t pstat;              // status bits from the prologue
-  int32_t wstat;              // status bits from the walk
-  uint32_t nonempty;          // the walk allowed some token
+  unsigned long long done;    // the row's residue chunks that ended (see residue_kernel)
+  uint32_t nonempty;          // the stream allowed some id
   int32_t cache_slot;         // mask-cache entry this row publishes to, -1 none
-  int32_t fstat;              // final row status (finalize)
+  int32_t fstat;              // final row status
   uint32_t cls_base, n_cls;   // the row's lexer state's class records
   uint32_t slot_id;           // the row's lexicon slot
   int32_t ci_hit;             // context-independent-words entry serving this row, -1 none
   int32_t ci_claim;           // such an entry this row publishes to, -1 none
-  uint32_t pad[14];
+  uint32_t pad[6];
 };
-static_assert(sizeof(RowHeader) == 320, "row header is 320 bytes");
+static_assert(sizeof(RowHeader) == 256, "row header is 256 bytes");
 
 struct Post {                 // stack after shifting one allowed terminal
   uint16_t k;                 // shared base entries kept
@@ -212,117 +218,59 @@ static_assert(sizeof(Post) == 32, "post entry is 32 bytes");
 static_assert(kPostCap == 14, "the walk decodes a post entry as two 16-byte halves");
 
 struct RowLayout {
-  size_t cls, win, block, post, a2, vcode, vrule, cont2, rbits, slow, slow_ov, total;
+  size_t win, usets, acc, block, post, codes, cats, cont2, open, n_open, list, total;
 };
 
 __host__ __device__ inline uint32_t pad16(uint32_t x) { return (x + 15u) & ~15u; }
 
-// One row's workspace: header; trailing-flag tables under A(sigma) and after
-// the winner's shift (one byte per DFA state each); the top kWalkWin states
-// of the stack; [block ends here]; post-shift stacks and allowed sets of the
-// allowed terminals; the class verdicts (2 bits per class of the row's lexer
-// state) and lexicon shortcuts (a byte per class); for every byte b that
-// continues the pending lexeme in the lexicon, the bytes that continue it
-// after b (256 bits per b, rows of other b unwritten); the residue bitmaps (one
-// bit per spelling the stream kernel left to the residue pass, in spelling
-// order: first those the lexicon decides, then those the byte walk decides);
-// the slow path's list and stack areas.
-__host__ __device__ inline RowLayout row_layout(int T, int S, int U, int max_classes) {
+// One row's workspace: header; the top kWalkWin states of the stack; the allowed sets with the ignored terminals added, from
+// sigma and after each allowed terminal's shift; the packed accept lists; the
+// stacks after each allowed terminal's shift; [the block the residue kernel keeps in LDS ends here]; a
+// verdict byte per class of the row's lexer state and, where the stream settles
+// it by prefix flags, its categories; for every byte b that continues the pending lexeme in
+// the lexicon, the bytes that continue it after b (256 bits per b, rows of
+// other b unwritten); the ids the stream kernel left open, a bit each (16 words per wave step, written
+// where the step has some), their number per step (u16), and, when the row's
+// are few enough, a list of them (id, class | its code << 16).
+__host__ __device__ inline int open_list_cap(int V) { return V < kOpenList ? V : kOpenList; }
+__host__ __device__ inline int stream_steps(int V) { return (V + kStepIds - 1) / kStepIds; }
+__host__ __device__ inline RowLayout row_layout(int T, int S, int V, int max_classes) {
   RowLayout L;
   size_t o = sizeof(RowHeader);
-  L.cls = o;
-  o += 2 * (size_t)pad16((uint32_t)S);
   L.win = o;
   o += kWalkWin * 2;
-  L.block = o;
+  L.usets = o;
+  o += (size_t)(1 + T) * 32;
+  L.acc = o;
+  o += pad16((uint32_t)S * 4u);
   L.post = o;
   o += (size_t)T * sizeof(Post);
-  L.a2 = o;
-  o += (size_t)T * 32;
-  L.vcode = o;
-  o += (size_t)pad16(((uint32_t)max_classes + 3u) / 4u);
-  L.vrule = o;
+  L.block = o;
+  L.codes = o;
+  o += (size_t)pad16((uint32_t)max_classes);
+  L.cats = o;
   o += (size_t)pad16((uint32_t)max_classes);
   L.cont2 = o;
   o += 256 * 32;
-  L.rbits = o;
-  o += (size_t)((U + 63) / 64) * 16;
-  L.slow = o;
-  o += kSlowCap * 4;
-  L.slow_ov = o;
-  o += (size_t)kSlowThreads * kSlowLane * 2;
+  L.open = o;
+  o += (size_t)stream_steps(V) * (kStepIds / 8);
+  L.n_open = o;
+  o += (size_t)stream_steps(V) * 2;
+  o = (o + 15) & ~(size_t)15;
+  L.list = o;
+  o += (size_t)open_list_cap(V) * 8;
   L.total = (o + 255) & ~(size_t)255;
   return L;
 }
 
-__host__ __device__ inline RowLayout row_layout(const Tables& tb) { return row_layout(tb.T, tb.S, tb.U, tb.max_classes); }
+__host__ __device__ inline RowLayout row_layout(const Tables& tb) { return row_layout(tb.T, tb.S, tb.V, tb.max_classes); }
 
-// Several global -> LDS copies (each region 16-byte aligned) in one pass:
-// the regions' 16-byte chunks are numbered consecutively and every thread
-// issues the loads of K chunks before it stores any, so the whole staging
-// costs about one memory round trip instead of one per region.  The last,
-// partial chunk of a region is copied byte by byte.
 #define GRID_LDS_VOID __attribute__((address_space(3))) void
 struct StageRegion {
   const uint8_t* src;
   uint8_t* dst;
   uint32_t bytes;
 };
-
-template <int N, int K>
-__device__ inline void stage_regions(const StageRegion (&rg)[N], int tid, int nt) {
-  uint32_t total = 0;
-#pragma unroll
-  for (int j = 0; j < N; ++j) total += (rg[j].bytes + 15u) / 16u;
-  for (uint32_t base = tid; base < total; base += (uint32_t)nt * K) {
-    uint4 v[K];
-    uint8_t* dst[K];
-    uint32_t left[K];  // bytes of the region from this chunk on (0: no chunk)
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const uint32_t i = base + (uint32_t)(k * nt);
-      // the region holding chunk i, chosen without indexing rg at run time
-      const uint8_t* src = rg[0].src;
-      dst[k] = rg[0].dst;
-      uint32_t bytes = rg[0].bytes, first = 0, pre = 0;
-#pragma unroll
-      for (int t = 0; t < N; ++t) {
-        if (t > 0 && i >= pre) {
-          src = rg[t].src;
-          dst[k] = rg[t].dst;
-          bytes = rg[t].bytes;
-          first = pre;
-        }
-        pre += (rg[t].bytes + 15u) / 16u;
-      }
-      const uint32_t off = (i - first) * 16u;
-      left[k] = i < total ? bytes - off : 0u;
-      src += off;
-      dst[k] += off;
-      v[k] = make_uint4(0, 0, 0, 0);
-      if (left[k] >= 16u) {
-        v[k] = *reinterpret_cast<const uint4*>(src);
-      } else if (left[k] > 0) {
-        uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int b = 0; b < 16; ++b)  // independent loads, all in flight
-          if ((uint32_t)b < left[k]) w[b >> 2] |= (uint32_t)src[b] << (8 * (b & 3));
-        v[k] = make_uint4(w[0], w[1], w[2], w[3]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      if (left[k] >= 16u) {
-        *reinterpret_cast<uint4*>(dst[k]) = v[k];
-      } else if (left[k] > 0) {
-        const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-#pragma unroll
-        for (int b = 0; b < 16; ++b)
-          if ((uint32_t)b < left[k]) dst[k][b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3)));
-      }
-    }
-  }
-}
 
 // Global -> LDS copies by direct global-to-LDS loads (global_load_lds, 16
 // bytes a lane): no registers hold the data on the way, so every load of the
@@ -358,14 +306,6 @@ __device__ inline uint32_t dma_regions(const StageRegion (&rg)[N], int tid, int 
 
 // Waits for this thread's outstanding loads, direct-to-LDS ones included.
 __device__ inline void dma_wait() { __builtin_amdgcn_s_waitcnt(0); }
-
-// Terminal set of every terminal (not the end of input), word w.
-__device__ inline uint32_t all_word(int T, int w) {
-  const int lo = w * 32;
-  if (T >= lo + 32) return 0xFFFFFFFFu;
-  if (T <= lo) return 0u;
-  return (1u << (T - lo)) - 1u;
-}
 
 // ------------------------------------------------------- compact LR tables
 // The tables and the lanes' stack areas sit in LDS in the prologue and the
@@ -433,30 +373,6 @@ __host__ __device__ inline ParseLds prologue_parse_lds(const Tables& tb) {
   return d.total <= kPrologueParseMax ? d : parse_lds(tb, 0, false);
 }
 
-// The prologue's dynamic LDS: the LR tables, then (when they fit beside
-// them) the lexer's accept lists and live sets and the terminal info.
-struct ProLds {
-  ParseLds pl;
-  uint32_t acc_off, acc_list, live, tinfo, total;
-  int lexer;  // the lexer tables are staged (else read from global memory)
-};
-__host__ __device__ inline ProLds prologue_lds(const Tables& tb) {
-  ProLds P;
-  P.pl = prologue_parse_lds(tb);
-  uint32_t o = P.pl.total;
-  P.acc_off = o;
-  o += pad16((uint32_t)(tb.S + 1) * 4u);
-  P.acc_list = o;
-  o += pad16((uint32_t)tb.n_acc);
-  P.live = o;
-  o += pad16((uint32_t)tb.S * 32u);
-  P.tinfo = o;
-  o += pad16((uint32_t)tb.T * 4u);
-  P.lexer = o <= kPrologueParseMax ? 1 : 0;
-  P.total = P.lexer ? o : P.pl.total;
-  return P;
-}
-
 __device__ inline StageRegion parse_region(const Tables& tb, uint8_t* lds, const ParseLds& L, int which) {
   if (which == 0) return {(const uint8_t*)tb.pstate, lds + L.st, (uint32_t)tb.n_pstate * 4};
   if (which == 1) return {(const uint8_t*)tb.predx, lds + L.redx, (uint32_t)tb.n_predx * 4};
@@ -500,37 +416,7 @@ __device__ __forceinline__ uint16_t goto_of(const ParseTabs<L>& pt, uint32_t s, 
   return e.x == key ? (uint16_t)e.y : kNoGoto;
 }
 
-// One state record: shift bits, main-reduce bits, main production (lhs |
-// length << 16, kNoProd none), extra groups | offset << 8.
-constexpr uint32_t kNoProd = 0xFFFFFFFFu;
-template <int MW>
-struct PRec {
-  uint32_t sh[MW], rd[MW], main, extra;
-};
-
-template <bool L, int MW>
-__device__ __forceinline__ PRec<MW> rec_of(const ParseTabs<L>& pt, uint32_t s) {
-  constexpr int R = parse_record_words(MW);
-  const mptr<L, const u32x4> p = (mptr<L, const u32x4>)(pt.st + s * (uint32_t)R);
-  uint32_t w[R];
-#pragma unroll
-  for (int i = 0; i < R / 4; ++i) {
-    const u32x4 v = p[i];
-    w[4 * i] = v.x;
-    w[4 * i + 1] = v.y;
-    w[4 * i + 2] = v.z;
-    w[4 * i + 3] = v.w;
-  }
-  PRec<MW> r;
-#pragma unroll
-  for (int k = 0; k < MW; ++k) {
-    r.sh[k] = w[k];
-    r.rd[k] = w[MW + k];
-  }
-  r.main = w[2 * MW];
-  r.extra = w[2 * MW + 1];
-  return r;
-}
+constexpr uint32_t kNoProd = 0xFFFFFFFFu;  // no production
 
 // Action of the terminal with set word w and bit `bit` in state s:
 // kActShiftP (shift, or accept for the end-of-input column), kNoProd
@@ -553,11 +439,6 @@ __device__ __forceinline__ uint32_t action_of(const ParseTabs<L>& pt, uint32_t s
       break;
     }
   return a;
-}
-
-template <bool L, int MW>
-__device__ __forceinline__ uint32_t action_of(const ParseTabs<L>& pt, uint32_t s, int x) {
-  return action_of<L, MW>(pt, s, (uint32_t)x >> 5, 1u << (x & 31));
 }
 
 // Target of the shift of terminal x in state s (x's shift bit is set): entry
@@ -627,166 +508,126 @@ __device__ __forceinline__ uint32_t goto_source(const BaseStack<L>& bs, uint32_t
   return sb;
 }
 
-// Reduce chain of terminal x, not changing the stack (pushes go to tmp).  1
-// shift, 2 accept (x is the end of input), 0 error, -1 capacity.
-template <bool L, int MW>
-__device__ __forceinline__ int sim1_test(const ParseTabs<L>& pt, const BaseStack<L>& bs, uint32_t k, int m,
-                                         mptr<L, const uint16_t> ov, mptr<L, uint16_t> tmp, int tmpcap, int x) {
-  const uint32_t w = (uint32_t)x >> 5, bit = 1u << (x & 31);
-  int t = 0;
-  uint32_t s = stack_at_top<L>(bs, k, m, ov, 0, tmp), below = kNoState;
-  int res = -1;  // guard exhausted or capacity
-  for (int guard = 0; guard < kGuard; ++guard) {
-    const uint32_t a = action_of<L, MW>(pt, s, w, bit);
-    if (a >= kActShiftP) {
-      res = a == kActShiftP ? (x == pt.T ? 2 : 1) : 0;
-      break;
-    }
-    const uint32_t len = a >> 16;
-    if (!pop_len(len, k, m, t)) {
-      res = 0;
-      break;
-    }
-    const uint32_t sb = goto_source<L>(bs, len, s, below, k, m, ov, t, tmp);
-    const uint16_t g = goto_of<L>(pt, sb, a & 0xFFFFu);
-    if (g == kNoGoto || t >= tmpcap) {
-      res = g == kNoGoto ? 0 : -1;
-      break;
-    }
-    tmp[t++] = g;
-    below = sb;
-    s = g;
-  }
-  return res;
+// ---------------------------------------------------- reduce chains of the mask
+// The mask kernels run every reduce chain on two dense tables: the action of
+// (state, terminal) with all that these two decide done ahead (host:
+// build_mask_actions), and GOTO.  At every step a chain holds one state above a
+// prefix of its stack, so a step is one action read, at most one stack read and
+// one GOTO read, with no pushes to keep -- a step of the compact tables (state
+// record, bit tests, extra reduce groups, overlay) took about twice as long.
+template <bool L>
+struct LrTabs {
+  mptr<L, const uint16_t> act, go;  // [states][T + 1], [states][N]
+  const uint32_t* red;              // reductions of indexed entries (bits = 0), global
+  uint32_t T1, N;
+  int bits;
+};
+
+struct LrLds {  // byte offsets of the two tables in LDS
+  uint32_t act, go, total;
+};
+__host__ __device__ inline LrLds lr_lds(const Tables& tb, uint32_t base) {
+  LrLds l;
+  l.act = base;
+  l.go = l.act + pad16((uint32_t)tb.NS * (uint32_t)(tb.T + 1) * 2u);
+  l.total = l.go + pad16((uint32_t)tb.NS * (uint32_t)tb.N * 2u) - base;
+  return l;
+}
+// The largest tables the mask kernels keep in LDS beside what else they stage;
+// larger ones are read from global memory.
+constexpr uint32_t kLrLdsMax = 96 * 1024;
+__host__ __device__ inline bool lr_in_lds(const Tables& tb) { return lr_lds(tb, 0).total <= kLrLdsMax; }
+
+__device__ inline uint32_t dma_lr(const Tables& tb, uint8_t* lds, const LrLds& l, int tid, int nt, uint32_t first) {
+  const StageRegion rg[2] = {{(const uint8_t*)tb.mact, lds + l.act, (uint32_t)tb.NS * (uint32_t)(tb.T + 1) * 2u},
+                             {(const uint8_t*)tb.go, lds + l.go, (uint32_t)tb.NS * (uint32_t)tb.N * 2u}};
+  return dma_regions<2>(rg, tid, nt, first);
+}
+template <bool L>
+__device__ inline LrTabs<L> lr_tabs(const Tables& tb, uint8_t* lds, const LrLds& l) {
+  if constexpr (L)
+    return {in_mem<true>((const uint16_t*)(lds + l.act)), in_mem<true>((const uint16_t*)(lds + l.go)), tb.mred,
+            (uint32_t)tb.T + 1u, (uint32_t)tb.N, tb.mbits};
+  else
+    return {in_mem<false>(tb.mact), in_mem<false>(tb.go), tb.mred, (uint32_t)tb.T + 1u, (uint32_t)tb.N, tb.mbits};
 }
 
-// Reduce chain of terminal x applied to (k, m, ov), then its shift.  1 shifted,
-// 2 accept, 0 error, -1 capacity.
-template <bool L, int MW>
-__device__ __forceinline__ int sim1_shift(const ParseTabs<L>& pt, const BaseStack<L>& bs, uint32_t& k, int& m,
-                                          mptr<L, uint16_t> ov, int cap, int x) {
-  const uint32_t w = (uint32_t)x >> 5, bit = 1u << (x & 31);
-  int t = 0;
-  uint32_t s = stack_at_top<L>(bs, k, m, ov, 0, ov), below = kNoState;
-  int res = -1;  // guard exhausted or capacity
-  for (int guard = 0; guard < kGuard; ++guard) {
-    const uint32_t a = action_of<L, MW>(pt, s, w, bit);
-    if (a >= kActShiftP) {
-      res = a == kActShiftP ? 1 : 0;
-      break;
-    }
-    const uint32_t len = a >> 16;
-    if (!pop_len(len, k, m, t)) {
-      res = 0;
-      break;
-    }
-    const uint32_t sb = goto_source<L>(bs, len, s, below, k, m, ov, 0, ov);
-    const uint16_t g = goto_of<L>(pt, sb, a & 0xFFFFu);
-    if (g == kNoGoto || m >= cap) {
-      res = g == kNoGoto ? 0 : -1;
-      break;
-    }
-    ov[m++] = g;
-    below = sb;
-    s = g;
+// A row's stack as the chains see it: base[0, k) ++ ov[0, m), the base read
+// from its LDS window (entries from lo on) or the pool.
+struct ChainStack {
+  const uint16_t* pool;
+  mptr<true, const uint16_t> win;
+  uint32_t lo, k;
+  mptr<true, const uint16_t> ov;
+  uint32_t m;
+  __device__ __forceinline__ uint32_t at(uint32_t i) const {
+    const bool over = i >= k, deep = !over && i < lo;
+    const mptr<true, const uint16_t> p = over ? ov + (i - k) : win + (deep ? 0u : i - lo);
+    uint32_t v = *p;  // a valid LDS address in every case
+    if (deep) v = pool[i];
+    return v;
   }
-  if (res != 1) return res;
-  if (x == pt.T) return 2;
-  if (m >= cap) return -1;
-  ov[m++] = shift_target<L, MW>(pt, s, x);
-  return 1;
+};
+
+// Reduce chain of terminal x from the stack: in, s is its top state and n the
+// entries below it; out, the stack that x is shifted on is its first n entries
+// and s, moved tells whether some reduction ran.  Returns the last action: 0
+// (refused), or a kMactShift entry.
+template <bool L>
+__device__ __forceinline__ uint32_t lr_chain(const LrTabs<L>& lt, const ChainStack& st, uint32_t x, uint32_t& n,
+                                             uint32_t& s, bool& moved) {
+  uint32_t a = lt.act[__umul24(s, lt.T1) + x];
+  uint32_t e = n ? st.at(n - 1u) : 0u;  // the state below s
+  moved = false;
+  for (int guard = 0; guard < kGuard && a - 1u < kMactShift - 1u; ++guard) {  // a reduction
+    uint32_t lhs = a & ((1u << lt.bits) - 1u), pops = a >> lt.bits;
+    if (lt.bits == 0) {  // uniform
+      const uint32_t r = lt.red[a - 1u];
+      lhs = r & 0xFFFFu;
+      pops = r >> 16;
+    }
+    if (pops > n) return 0u;  // it would empty the stack
+    if (pops > 1u) {
+      n -= pops - 1u;
+      e = st.at(n - 1u);
+    }
+    s = lt.go[__umul24(e, lt.N) + lhs];
+    moved = true;
+    if (s == kNoGoto) return 0u;
+    a = lt.act[__umul24(s, lt.T1) + x];
+  }
+  return a & kMactShift ? a : 0u;
 }
 
-// Set simulation: acc |= the terminals of X that can be shifted next from
-// base[0,k0) ++ ov[0,m0).  All of X runs one reduce chain; at each state the
-// shifting terminals are accepted, those reduced by one production continue
-// together, terminals of another reduce production of the same state rerun
-// from the start (they follow the same chain up to that state, so every rerun
-// peels off at least one group), the rest fail.  MW = words per set (the
-// tables' TW).  0 ok, -1 capacity (acc is then incomplete).
-template <bool L, int MW>
-__device__ __forceinline__ int sim_set(const ParseTabs<L>& pt, const BaseStack<L>& bs, uint32_t k0, int m0,
-                                       mptr<L, const uint16_t> ov, mptr<L, uint16_t> tmp, int tmpcap,
-                                       const uint32_t (&X)[MW], uint32_t (&acc)[MW]) {
-  uint32_t todo[MW];
-#pragma unroll
-  for (int w = 0; w < MW; ++w) todo[w] = X[w];
-  const uint32_t s0 = stack_at_top<L>(bs, k0, m0, ov, 0, tmp);
-  for (int round = 0; round < kMaxRounds; ++round) {
-    uint32_t any = 0;
-#pragma unroll
-    for (int w = 0; w < MW; ++w) any |= todo[w];
-    if (!any) return 0;
-    uint32_t cur[MW];
-#pragma unroll
-    for (int w = 0; w < MW; ++w) {
-      cur[w] = todo[w];
-      todo[w] = 0;
-    }
-    uint32_t k = k0, s = s0, below = kNoState;
-    int m = m0, t = 0;
+// The stack after a chain's shift (a its last action): base entries kept and
+// overlay, written over ov[0, m).  False if the overlay outgrows cap (or the
+// base its 16 bits, for a record).
+__device__ __forceinline__ bool lr_commit(const Tables& tb, uint32_t a, uint32_t x, uint32_t n, uint32_t s, bool moved,
+                                          uint32_t& k, uint32_t& m, mptr<true, uint16_t> ov, uint32_t cap) {
+  if (moved) {
+    m = n > k ? n - k : 0u;
+    k = min(k, n);
+    if (m >= cap) return false;
+    ov[m++] = (uint16_t)s;
+  }
+  if (a & kMactPushed) {  // the states the empty reductions push first (rare: the LALR tables in global memory)
+    const uint32_t floor = m, T1 = (uint32_t)tb.T + 1u;
+    uint32_t top = s;
     for (int guard = 0; guard < kGuard; ++guard) {
-      const PRec<MW> r = rec_of<L, MW>(pt, s);
-      uint32_t nxt[MW], live = 0;
-#pragma unroll
-      for (int w = 0; w < MW; ++w) {
-        acc[w] |= cur[w] & r.sh[w];
-        nxt[w] = cur[w] & r.rd[w];
-        live |= nxt[w];
-      }
-      uint32_t chosen = live ? r.main : kNoProd;
-      const uint32_t nx = r.extra & 0xFFu;
-      mptr<L, const uint32_t> g = pt.redx + (r.extra >> 8);
-      for (uint32_t e = 0; e < nx; ++e, g += MW + 1) {  // the state's other reduce groups
-        uint32_t gl = 0, part[MW];
-#pragma unroll
-        for (int w = 0; w < MW; ++w) {
-          part[w] = cur[w] & g[1 + w];
-          gl |= part[w];
-        }
-        if (!gl) continue;
-        if (chosen == kNoProd) {
-          chosen = g[0];
-#pragma unroll
-          for (int w = 0; w < MW; ++w) nxt[w] = part[w];
-        } else {
-#pragma unroll
-          for (int w = 0; w < MW; ++w) todo[w] |= part[w];
-        }
-      }
-      if (chosen == kNoProd) break;
-#pragma unroll
-      for (int w = 0; w < MW; ++w) cur[w] = nxt[w];
-      const uint32_t len = chosen >> 16;
-      if (!pop_len(len, k, m, t)) break;
-      const uint32_t sb = goto_source<L>(bs, len, s, below, k, m, ov, t, tmp);
-      const uint16_t gs = goto_of<L>(pt, sb, chosen & 0xFFFFu);
-      if (gs == kNoGoto) break;
-      if (t >= tmpcap) return -1;
-      tmp[t++] = gs;
-      below = sb;
-      s = gs;
+      const uint32_t la = tb.action[top * T1 + x];
+      if ((la & 0xC000u) != kActReduce) break;
+      const uint32_t pr = tb.prod[la & 0x3FFFu], len = pr >> 16;
+      if (len > m - floor) return false;
+      m -= len;
+      const uint32_t g = tb.go[(m > floor ? (uint32_t)ov[m - 1u] : s) * (uint32_t)tb.N + (pr & 0xFFFFu)];
+      if (g == kNoGoto || m >= cap) return false;
+      ov[m++] = (uint16_t)g;
+      top = g;
     }
   }
-  uint32_t any = 0;
-#pragma unroll
-  for (int w = 0; w < MW; ++w) any |= todo[w];
-  return any ? -1 : 0;
-}
-
-// Allowed set of base[0,k) ++ ov[0,m): every terminal (not the end of input)
-// that can be shifted next.
-template <bool L, int MW>
-__device__ __forceinline__ int allowed_set(const ParseTabs<L>& pt, const BaseStack<L>& bs, uint32_t k, int m,
-                                           mptr<L, const uint16_t> ov, mptr<L, uint16_t> tmp, int tmpcap,
-                                           uint32_t (&acc)[MW]) {
-  uint32_t X[MW];
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    X[w] = all_word(pt.T, w);
-    acc[w] = 0;
-  }
-  return sim_set<L, MW>(pt, bs, k, m, ov, tmp, tmpcap, X, acc);
+  if (m >= cap) return false;
+  ov[m++] = (uint16_t)(a & 0x3FFFu);
+  return true;
 }
 
 // ---------------------------------------------------------- lexicon helpers
@@ -859,34 +700,6 @@ __device__ __forceinline__ uint32_t lex_flags_bytes(const Tables& tb, const Slot
   return lexs_find(tb, sl, node, low_bytes(b2, len - 16), len - 16).x;
 }
 
-// The pending lexeme as the lexicon sees it: its bytes while it has at most 8
-// (bytes mode), else its lexicon-trie node (kNoLex once no word has it as a
-// prefix).  Kept only when the row's lexicon restricts some category.
-struct LexState {
-  uint64_t w;
-  uint32_t len;
-  uint32_t node;
-  uint32_t need;  // some restricted terminal was viable where the lexeme began
-};
-
-// Appends byte b to the pending lexeme.
-__device__ inline void lex_push(const Tables& tb, const Slot& sl, LexState& lx, uint32_t b) {
-  if (lx.len < 8) {
-    lx.w |= (uint64_t)b << (8 * lx.len);
-  } else if (lx.len == 8) {
-    lx.node = lex_child(tb, sl, lexp_find(tb, sl, lx.w, 8).y, b);
-  } else {
-    lx.node = lex_child(tb, sl, lx.node, b);
-  }
-  ++lx.len;
-}
-
-__device__ inline uint32_t lex_flags_now(const Tables& tb, const Slot& sl, const LexState& lx) {
-  if (lx.len == 0) return 0u;
-  if (lx.len <= 8) return lexp_find(tb, sl, lx.w, lx.len).x;
-  return lex_flags_of(tb, sl, lx.node);
-}
-
 __device__ inline bool bit_of(const uint32_t* s, int t) { return (s[t >> 5] >> (t & 31)) & 1u; }
 
 // What a lane needs to judge terminals: term info, ignored set I, the row's
@@ -899,49 +712,6 @@ struct TermView {
   const uint32_t* live;
   int lstride;
 };
-
-// Terminals a pending lexeme in DFA state q can still complete to that are
-// allowed (acur) or ignored: bit 0 set if one of them has an unrestricted
-// category, bit 1 if one has a restricted category (the lexicon decides for
-// it).  Live sets only shrink as a lexeme grows, so a later byte of the same
-// lexeme never gains a bit.
-template <int MW>
-__device__ inline uint32_t trail_flags(const TermView& tv, const uint32_t (&acur)[MW], int q) {
-  uint32_t unres = 0, res = 0;
-  const uint32_t* lv = tv.live + (size_t)q * tv.lstride;
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    const uint32_t bits = lv[w] & (acur[w] | tv.I[w]);
-    unres |= bits & ~tv.R[w];
-    res |= bits & tv.R[w];
-  }
-  return (unres ? 1u : 0u) | (res ? 2u : 0u);
-}
-
-// Lexicon half of Definition 2 for a lexeme whose trailing class is 2: some
-// restricted terminal it can complete to has a category whose words it
-// prefixes (lf = the lexeme's lexicon flags).
-template <int MW>
-__device__ inline bool trail_lex(const TermView& tv, const uint32_t (&acur)[MW], int q, uint32_t lf) {
-  const uint32_t* lv = tv.live + (size_t)q * tv.lstride;
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    uint32_t r = lv[w] & (acur[w] | tv.I[w]) & tv.R[w];
-    while (r) {
-      const int t = w * 32 + __ffs(r) - 1;
-      r &= r - 1;
-      if ((lf >> ((tv.tinfo[t] >> 8) & 0xFFu)) & 1u) return true;
-    }
-  }
-  return false;
-}
-
-// Definition 2 for a pending lexeme in DFA state q with lexicon flags lf.
-template <int MW>
-__device__ inline bool trail_ok(const TermView& tv, const uint32_t (&acur)[MW], int q, uint32_t lf) {
-  const uint32_t f = trail_flags<MW>(tv, acur, q);
-  return (f & 1u) || ((f & 2u) && trail_lex<MW>(tv, acur, q, lf));
-}
 
 // Pending lexeme's winner at an emission: the first accept-list entry (highest
 // priority, ties to the lower id) that is ignored or allowed and passes the
@@ -1004,7 +774,8 @@ __device__ inline void ci_key(const Tables& tb, const grid_config& cfg, const Sl
                           (uint32_t)cfg.rem_head[2] << 16 | (uint32_t)cfg.rem_head[3] << 24;
   const uint32_t rem_hi = (uint32_t)cfg.rem_head[4] | (uint32_t)cfg.rem_head[5] << 8 |
                           (uint32_t)cfg.rem_head[6] << 16 | (uint32_t)cfg.rem_head[7] << 24;
-  key[0] = family ? (genn ? 3u : 2u) : 1u;
+  // (which tokens are context-independent depends on the class tables in use)
+  key[0] = (family ? (genn ? 3u : 2u) : 1u) | (tb.prog ? 8u : 0u);
   key[1] = family ? tb.family_fp : tb.fp;
   key[2] = cfg.q;
   key[3] = family ? tb.lex_slots[(size_t)cfg.slot * kSlotWords + 9] : (uint32_t)cfg.slot;
@@ -1018,6 +789,48 @@ __device__ inline void ci_key(const Tables& tb, const grid_config& cfg, const Sl
   (void)sl;
 }
 
+// Accept list of a state in one word: its first three terminals, its length in
+// the top byte.
+__device__ __forceinline__ uint32_t pack_accepts(const uint32_t* acc_off, const uint8_t* acc_list, int q) {
+  const uint32_t o = acc_off[q], n = acc_off[q + 1] - o;
+  uint32_t w = n << 24;
+  for (uint32_t j = 0; j < 3u; ++j)
+    if (j < n) w |= (uint32_t)acc_list[o + j] << (8u * j);
+  return w;
+}
+
+// The number of open ids of each of the B rows (after the rows' areas).
+__device__ __forceinline__ uint32_t* open_counts(uint8_t* ws, size_t rbytes, int B) {
+  return (uint32_t*)(ws + kWsHead + (size_t)B * rbytes);
+}
+
+// The prologue's dynamic LDS: the chains' tables (when they fit), then (when they
+// fit beside them) the lexer's accept lists and live sets and the terminal
+// info.
+struct ProLds {
+  LrLds lr;
+  uint32_t acc_off, acc_list, live, tinfo, total;
+  int lexer;  // the lexer tables are staged (else read from global memory)
+};
+constexpr uint32_t kPrologueLdsMax = 128 * 1024;
+__host__ __device__ inline ProLds prologue_lds(const Tables& tb) {
+  ProLds P;
+  P.lr = lr_lds(tb, 0);
+  uint32_t o = lr_in_lds(tb) ? P.lr.total : 0u;
+  const uint32_t base = o;
+  P.acc_off = o;
+  o += pad16((uint32_t)(tb.S + 1) * 4u);
+  P.acc_list = o;
+  o += pad16((uint32_t)tb.n_acc);
+  P.live = o;
+  o += pad16((uint32_t)tb.S * 32u);
+  P.tinfo = o;
+  o += pad16((uint32_t)tb.T * 4u);
+  P.lexer = o <= kPrologueLdsMax ? 1 : 0;
+  P.total = P.lexer ? o : base;
+  return P;
+}
+
 // ---------------------------------------------------------------- prologue
 // One workgroup per row.  Phase 1: every terminal's reduce chain and shift
 // from sigma (A(sigma) is the set that shifted) and, for an allowed terminal,
@@ -1025,18 +838,19 @@ __device__ inline void ci_key(const Tables& tb, const grid_config& cfg, const Sl
 // run speculatively after every candidate winner's shift and from sigma; then
 // the pending lexeme's winner; then the trailing-flag tables, the lexicon
 // continuation bits of the pending lexeme and the row header.
-template <int MW>
+template <int MW, bool L>
 __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const grid_config* __restrict__ cfgs,
                                                           const uint16_t* __restrict__ pool,
                                                           uint32_t* __restrict__ mask,
                                                           uint8_t* __restrict__ eos_out,
+                                                          int32_t* __restrict__ status,
                                                           uint8_t* __restrict__ ws, size_t rbytes) {
   extern __shared__ __align__(16) uint8_t plds[];
   const int row = blockIdx.x;
   const int tid = threadIdx.x;
+  if (tid == 0) open_counts(ws, rbytes, (int)gridDim.x)[row] = 0u;
   __shared__ uint16_t win[kStackWin];
-  __shared__ uint32_t A[8], I[8], R[8], Aw[8];
-  __shared__ uint16_t sim_area[kProThreads][kPostCap + kTmpCap];
+  __shared__ uint32_t A[8], I[8], R[8];
   __shared__ int bad, overflow, winner, eos_ok, eos_sigma, cache_hit;
   __shared__ uint8_t eos_after[256];  // end-of-sequence test after shifting each candidate winner
   __shared__ Post posts[256];          // stack after shifting each allowed terminal
@@ -1045,45 +859,38 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
   __shared__ unsigned long long hacc[2];
   uint8_t* rw = ws + kWsHead + (size_t)row * rbytes;
   RowHeader* hdr = (RowHeader*)rw;
-  const RowLayout L = row_layout(tb);
-  Post* post = (Post*)(rw + L.post);
-  uint32_t* a2 = (uint32_t*)(rw + L.a2);
+  const RowLayout RL = row_layout(tb);
+  Post* post = (Post*)(rw + RL.post);
+  uint32_t* usets = (uint32_t*)(rw + RL.usets);
   const grid_config cfg = cfgs[row];
   const ProLds PR = prologue_lds(tb);
-  const ParseLds PL = PR.pl;
   const uint32_t depth = cfg.stk_depth;
   const uint32_t lo = depth > (uint32_t)kStackWin ? depth - kStackWin : 0;
   // one round trip to memory: the LR tables (and the lexer's accept lists and
   // live sets and the terminal info) go straight to LDS while every thread
   // loads one entry of the top kStackWin stack entries
   const bool shape_ok = cfg.q < tb.S && cfg.slot < tb.n_slots && depth >= 1;  // uniform
+  uint32_t first = 0;
+  if (L) first = dma_lr(tb, plds, PR.lr, tid, kProThreads, 0);
   if (PR.lexer) {
-    const StageRegion rg[8] = {parse_region(tb, plds, PL, 0),
-                               parse_region(tb, plds, PL, 1),
-                               parse_region(tb, plds, PL, 2),
-                               parse_region(tb, plds, PL, 3),
-                               {(const uint8_t*)tb.acc_off, plds + PR.acc_off, (uint32_t)(tb.S + 1) * 4u},
+    const StageRegion rg[4] = {{(const uint8_t*)tb.acc_off, plds + PR.acc_off, (uint32_t)(tb.S + 1) * 4u},
                                {tb.acc_list, plds + PR.acc_list, (uint32_t)tb.n_acc},
                                {(const uint8_t*)tb.live, plds + PR.live, (uint32_t)tb.S * 32u},
                                {(const uint8_t*)tb.term_info, plds + PR.tinfo, (uint32_t)tb.T * 4u}};
-    dma_regions<8>(rg, tid, kProThreads);
-  } else {
-    const StageRegion rg[4] = {parse_region(tb, plds, PL, 0), parse_region(tb, plds, PL, 1),
-                               parse_region(tb, plds, PL, 2), parse_region(tb, plds, PL, 3)};
-    dma_regions<4>(rg, tid, kProThreads);
+    dma_regions<4>(rg, tid, kProThreads, first);
   }
   const uint32_t* acc_off = PR.lexer ? (const uint32_t*)(plds + PR.acc_off) : tb.acc_off;
   const uint8_t* acc_list = PR.lexer ? (const uint8_t*)(plds + PR.acc_list) : tb.acc_list;
   const uint32_t* live = PR.lexer ? (const uint32_t*)(plds + PR.live) : tb.live;
   const uint32_t* tinfo = PR.lexer ? (const uint32_t*)(plds + PR.tinfo) : tb.term_info;
   uint32_t s_top = 0;
-  if (shape_ok && lo + (uint32_t)tid < depth) s_top = pool[cfg.stk_off + lo + tid];
+  if (shape_ok && tid < kStackWin && lo + (uint32_t)tid < depth) s_top = pool[cfg.stk_off + lo + tid];
   // the row's lexicon slot, its class range and this thread's terminal info,
   // in the same round trip
   const Slot sl = shape_ok ? load_slot(tb, cfg.slot) : Slot{0, 0, 0, 0, 0, 0, 0, 0, 0};
   const uint32_t cls_lo = shape_ok ? tb.coff[cfg.q] : 0u, cls_hi = shape_ok ? tb.coff[cfg.q + 1] : 0u;
   const uint32_t ti = tid < tb.T ? tb.term_info[tid] : 0u;
-  const ParseTabs<true> pt = lds_parse(tb, plds, PL);
+  const LrTabs<L> lt = lr_tabs<L>(tb, plds, PR.lr);
   if (tid == 0) {
     int b = shape_ok ? 0 : 1;
     if (!b && cfg.lexnode != kNoLex && cfg.lexnode >= sl.nodes) b = 1;
@@ -1096,20 +903,12 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     hacc[0] = 0;
     hacc[1] = 0;
   }
-  // the residue bitmaps start empty (16-byte stores): cleared during phase 1
-  // by the waves below thread 256 that have no terminal, whose later work is
-  // all in LDS (so nothing waits on these stores), else here
-  const int z0 = ((tb.T + 63) / 64) * 64;
-  uint4* const rb = (uint4*)(rw + L.rbits);
-  const int n_rb = (tb.U + 63) / 64;
-  if (z0 >= 256)
-    for (int i = tid; i < n_rb; i += kProThreads) rb[i] = make_uint4(0, 0, 0, 0);
   dma_wait();
   __syncthreads();
   const bool sum_hash = tb.cache && !tb.stack_hash;  // the cache key needs the whole stack's content
   if (!bad) {  // every entry is an LR state; the window goes to LDS; the content hash for the cache
     uint64_t h1 = 0, h2 = 0;
-    if (lo + (uint32_t)tid < depth) {
+    if (tid < kStackWin && lo + (uint32_t)tid < depth) {
       const uint32_t i = lo + (uint32_t)tid;
       if (s_top >= (uint32_t)tb.NS) bad = 1;
       win[tid] = (uint16_t)s_top;
@@ -1135,11 +934,10 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
   if (bad) {
     if (tid == 0) {
       hdr->pstat = GRID_ROW_BAD_CONFIG;
+      hdr->fstat = GRID_ROW_BAD_CONFIG;
+      if (status) status[row] = GRID_ROW_BAD_CONFIG;
       hdr->valid = 0;
       hdr->eos_ok = 0;
-      hdr->slow_count = 0;
-      hdr->wstat = 0;
-      hdr->nonempty = 0;
       hdr->cache_slot = -1;
       hdr->ci_hit = -1;
       hdr->ci_claim = -1;
@@ -1215,10 +1013,8 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     if (tid == 0) {
       hdr->valid = kRowCached;
       hdr->pstat = (int32_t)e->status;
+      if (status) status[row] = (int32_t)e->status;
       hdr->eos_ok = e->eos;
-      hdr->slow_count = 0;
-      hdr->wstat = 0;
-      hdr->nonempty = 1;
       hdr->cache_slot = -1;
       hdr->ci_hit = -1;
       hdr->ci_claim = -1;
@@ -1230,28 +1026,29 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     I[tid] = tb.ign[tid];
     R[tid] = 0;
     A[tid] = 0;
-    Aw[tid] = 0;
   }
+  const uint32_t s_sigma = win[depth - 1u - lo];  // the top of the stack
   __syncthreads();
   if (tid < tb.T) {  // restricted terminals, one per thread
     const uint32_t c = (ti >> 8) & 0xFFu;
     if (c != 0xFFu && ((sl.restricted >> c) & 1u)) atomicOr(&R[tid >> 5], 1u << (tid & 31));
   }
-  const BaseStack<true> bs{pool + cfg.stk_off, in_mem<true>((const uint16_t*)win), depth, lo};
-  const mptr<true, uint16_t> my = in_mem<true>(&sim_area[tid][0]);
+  const mptr<true, const uint16_t> win_l = in_mem<true>((const uint16_t*)win);
   const TermView tv{tinfo, I, R, live, 8};
   __syncthreads();
 
-  // phase 1: terminal t's reduce chain and shift from sigma (thread t; A(sigma)
-  // is the set that shifted, the stacks after the shifts go to LDS and the
-  // row's workspace); a spare thread runs the end-of-sequence gate from sigma
-  // itself (empty remainder, or an ignored winner); the upper waves meanwhile
-  // find the bytes that continue the pending lexeme in the lexicon (thread
-  // 256 + b for byte b) and, after each, the bytes that continue it further
-  // (the child bitmap of that trie node)
-  static_assert(kProThreads == 512, "the upper 256 threads probe one byte value each");
+  // phase 1: thread x runs terminal x's reduce chain from sigma (x = T: the end
+  // of input, so that is the end-of-sequence gate for an empty remainder or an
+  // ignored winner): A(sigma) is the set that shifts, and their stacks after
+  // the shift go to LDS and the row's workspace.  Meanwhile the threads from
+  // 256 on find the bytes that continue the pending lexeme in the lexicon
+  // (thread 256 + b for byte b) and, after each, the bytes that continue it
+  // further (the child bitmap of that trie node).
+  static_assert(kProThreads == 1024, "threads 256 to 511 probe one byte value each");
   const bool rem_empty = (cfg.flags & 1u) != 0;
-  if (tid >= 256) {  // whole waves
+  const int G = (tb.T + 64) / 64;  // waves over the terminals and the end of input
+  const int lane = tid & 63, wave = tid >> 6;
+  if (tid >= 256 && tid < 512) {  // whole waves
     const uint32_t b = (uint32_t)tid - 256u;
     const uint32_t n1 = rem_empty ? kNoLex : lex_child(tb, sl, cfg.lexnode, b);
     const bool c = n1 != kNoLex;
@@ -1259,41 +1056,44 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     if ((b & 31) == 0) hdr->cont[b >> 5] = (uint32_t)(bal >> (b & 32));
     if (c) {
       const uint4* src = reinterpret_cast<const uint4*>(tb.lex_child + (size_t)(sl.fbase + n1) * 8u);
-      uint4* dst = reinterpret_cast<uint4*>(rw + L.cont2 + (size_t)b * 32u);
+      uint4* dst = reinterpret_cast<uint4*>(rw + RL.cont2 + (size_t)b * 32u);
       dst[0] = src[0];
       dst[1] = src[1];
     }
-  } else if (tid < tb.T) {
-    const int t = tid;
-    uint32_t k = depth;
-    int m = 0;
-    const int r = sim1_shift<true, MW>(pt, bs, k, m, my, kPostCap, t);
-    if (r < 0 || (r == 1 && k > 0xFFFF)) overflow = 1;
-    if (r == 1) {
-      atomicOr(&A[t >> 5], 1u << (t & 31));
-      Post p;
+  } else if (tid >= 512) {  // the packed accept lists, for the verdicts
+    uint32_t* acc = (uint32_t*)(rw + RL.acc);
+    for (int q = tid - 512; q < tb.S; q += kProThreads - 512) acc[q] = pack_accepts(acc_off, acc_list, q);
+  } else if (wave < G) {
+    const ChainStack st{pool + cfg.stk_off, win_l, lo, depth, win_l, 0u};
+    uint32_t n = depth - 1u, s = s_sigma, a = 0;
+    bool moved = false;
+    if (tid <= tb.T) a = lr_chain<L>(lt, st, (uint32_t)tid, n, s, moved);
+    const uint64_t bal = __ballot(a != 0u && tid < tb.T);
+    if (lane == 0) {
+      A[2 * wave] = (uint32_t)bal;
+      A[2 * wave + 1] = (uint32_t)(bal >> 32);
+    }
+    if (tid == tb.T) {
+      eos_sigma = a != 0u;
+    } else if (a) {
+      uint32_t k = depth, m = 0;
+      Post& p = posts[tid];
+      if (!lr_commit(tb, a, (uint32_t)tid, n, s, moved, k, m, in_mem<true>((uint16_t*)p.ov), kPostCap) || k > 0xFFFFu)
+        overflow = 1;
       p.k = (uint16_t)k;
       p.m = (uint8_t)m;
       p.ok = 1;
-      for (int j = 0; j < kPostCap; ++j) p.ov[j] = j < m ? (uint16_t)my[j] : (uint16_t)0;
-      posts[t] = p;
-      post[t] = p;
+      uint4* dst = reinterpret_cast<uint4*>(&post[tid]);
+      const uint4* src = reinterpret_cast<const uint4*>(&p);
+      dst[0] = src[0];
+      dst[1] = src[1];
     }
-  } else if (tid == 255) {  // at most 255 terminals: never a terminal's thread
-    eos_sigma = sim1_test<true, MW>(pt, bs, depth, 0, my, my, kPostCap + kTmpCap, tb.T) == 2;
-  }
-  if (z0 < 256 && tid >= z0 && tid < 256)
-    for (int i = tid - z0; i < n_rb; i += 256 - z0) rb[i] = make_uint4(0, 0, 0, 0);
-  if (tid < 256) {
-#pragma unroll
-    for (int w = 0; w < MW; ++w) a2_s[tid][w] = 0u;
   }
   __syncthreads();
-  // phase 2: the allowed set after each allowed terminal's shift, split into
-  // P jobs per terminal (job j simulates the terminals x with x mod P == j, so
-  // the reduce groups, each of which costs the set simulation a rerun, spread
-  // over the jobs) and sized to the workgroup; then, for every candidate
-  // winner of the pending lexeme, the end-of-sequence gate after its shift
+  // phase 2: the allowed set after each allowed terminal's shift, a wave per 64
+  // terminals of one set (the ballot is the set), with the end-of-sequence gate
+  // after that shift on the end-of-input lane; the last wave finds the pending
+  // lexeme's winner and probes the CI words meanwhile
   int nA = 0;
 #pragma unroll
   for (int w = 0; w < MW; ++w) nA += __popc(A[w]);
@@ -1306,37 +1106,23 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     alist[rank] = (uint8_t)tid;
   }
   __syncthreads();
-  // the set jobs take the first kSetThreads threads, the gates the last wave
-  // (a wave runs divergent branches one after the other)
-  constexpr int kSetThreads = kProThreads - 64;
-  const int P = nA > 0 ? max(1, min(64, kSetThreads / nA)) : 1;
-  const int n_set = nA * P;
-  const bool set_lane = tid < kSetThreads;
-  for (int j = set_lane ? tid : n_set + (tid - kSetThreads); j < (set_lane ? n_set : n_set + nA);
-       j += set_lane ? kSetThreads : 64) {
-    const int t = alist[j < n_set ? j / P : j - n_set];
+  constexpr int kSetWaves = kProThreads / 64 - 1;
+  for (int j = wave; wave < kSetWaves && j < nA * G; j += kSetWaves) {  // uniform per wave
+    const int t = alist[j / G], g = j % G, x = g * 64 + lane;
     const Post& p = posts[t];
-    const mptr<true, const uint16_t> ov = in_mem<true>((const uint16_t*)p.ov);
-    if (j < n_set) {
-      const int part = j % P;
-      uint32_t X[MW], acc[MW];
-#pragma unroll
-      for (int w = 0; w < MW; ++w) {
-        uint32_t x = 0;
-        for (int b = (part - w * 32 % P + P) % P; b < 32; b += P) x |= 1u << b;
-        X[w] = x & all_word(tb.T, w);
-        acc[w] = 0;
-      }
-      if (sim_set<true, MW>(pt, bs, p.k, p.m, ov, my, kPostCap + kTmpCap, X, acc) < 0) overflow = 1;
-#pragma unroll
-      for (int w = 0; w < MW; ++w)
-        if (acc[w]) atomicOr(&a2_s[t][w], acc[w]);
-    } else if (!rem_empty) {
-      bool cand = false;
-      for (uint32_t q = acc_off[cfg.q]; q < acc_off[cfg.q + 1]; ++q) cand = cand || acc_list[q] == t;
-      if (cand) eos_after[t] = sim1_test<true, MW>(pt, bs, p.k, p.m, ov, my, kPostCap + kTmpCap, tb.T) == 2;
+    const ChainStack st{pool + cfg.stk_off, win_l, lo, p.k, in_mem<true>((const uint16_t*)p.ov), p.m};
+    uint32_t n = (uint32_t)p.k + p.m - 1u, a = 0;
+    uint32_t s = st.at(n);
+    bool moved = false;
+    if (x <= tb.T) a = lr_chain<L>(lt, st, (uint32_t)x, n, s, moved);
+    const uint64_t bal = __ballot(a != 0u && x < tb.T);
+    if (lane == 0) {
+      if (2 * g < MW) a2_s[t][2 * g < MW ? 2 * g : 0] = (uint32_t)bal;
+      if (2 * g + 1 < MW) a2_s[t][2 * g + 1 < MW ? 2 * g + 1 : 0] = (uint32_t)(bal >> 32);
     }
+    if (x == tb.T) eos_after[t] = a != 0u;
   }
+  constexpr int kSetThreads = kSetWaves * 64;
   // the pending lexeme's winner if a byte ends it (the gate wave's first
   // thread, while the set jobs run)
   if (tid == kSetThreads && !rem_empty) {
@@ -1389,34 +1175,18 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
   const bool w_shifts = w >= 0 && !bit_of(I, w);
   if (tid < tb.T && bit_of(A, tid)) {
 #pragma unroll
-    for (int k = 0; k < MW; ++k) a2[tid * 8 + k] = a2_s[tid][k];
+    for (int k = 0; k < MW; ++k) usets[(1 + tid) * 8 + k] = a2_s[tid][k] | I[k];
   }
-  if (w >= 0 && tid < MW) Aw[tid] = a2_s[w][tid];
+  if (tid >= 256 && tid < 264) usets[tid - 256] = A[tid - 256] | I[tid - 256];
   if (tid == 0) eos_ok = (rem_empty || (w >= 0 && !w_shifts)) ? eos_sigma : (w >= 0 ? (int)eos_after[w] : 0);
   __syncthreads();
-  // phase 3: the trailing-flag tables of every DFA state under A(sigma) and
-  // after the winner's shift, and the top of the stack for the residue walk
-  {
-    uint32_t a0[MW], aw[MW];
-#pragma unroll
-    for (int k = 0; k < MW; ++k) {
-      a0[k] = A[k];
-      aw[k] = Aw[k];
-    }
-    uint8_t* clsA = rw + L.cls;
-    uint8_t* clsW = clsA + pad16((uint32_t)tb.S);
-    for (int q = tid; q < tb.S; q += kProThreads) {
-      clsA[q] = (uint8_t)trail_flags<MW>(tv, a0, q);
-      clsW[q] = (uint8_t)trail_flags<MW>(tv, aw, q);
-    }
-    uint16_t* wwin = (uint16_t*)(rw + L.win);
+  {  // the top of the stack for the walks
+    uint16_t* wwin = (uint16_t*)(rw + RL.win);
     const uint32_t wlo = depth > (uint32_t)kWalkWin ? depth - kWalkWin : 0u;
     if ((uint32_t)tid < depth - wlo) wwin[tid] = win[wlo + tid - lo];
   }
-  __syncthreads();
   if (tid < 8) {
     hdr->A[tid] = A[tid];
-    hdr->Aw[tid] = Aw[tid];
     hdr->R[tid] = R[tid];
   }
   if (tid == 0) {  // the slot's table bases and masks (its other words are not used on the device side)
@@ -1439,114 +1209,14 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const 
     hdr->rem_hi = (uint32_t)cfg.rem_head[4] | (uint32_t)cfg.rem_head[5] << 8 | (uint32_t)cfg.rem_head[6] << 16 |
                   (uint32_t)cfg.rem_head[7] << 24;
     hdr->rem_len = rem_empty ? 0u : cfg.rem_len;
-    hdr->slow_count = 0;
-    hdr->wstat = 0;
     hdr->nonempty = 0;
+    hdr->done = 0;
     hdr->slot_id = cfg.slot;
     hdr->cls_base = cls_lo;
     hdr->n_cls = cls_hi - cls_lo;
     hdr->pstat = overflow ? GRID_ROW_OVERFLOW : GRID_ROW_OK;
     hdr->valid = kRowValid;
   }
-}
-
-// ------------------------------------------------------- lane machinery
-// A lane's parser side.  Mode 0: the stack is sigma and acur = A(sigma).
-// Mode 1: sigma plus the shift of t1, acur = that stack's allowed set (from
-// the prologue).  Mode 2: a stack of its own (base[0,k) ++ overlay[0,m)) and
-// the part of its allowed set that the current lexeme can still use: after
-// every shift only the terminals live in the DFA state reached by the next
-// lexeme's first byte are set-simulated (live sets only shrink along a
-// lexeme, so every later check of that lexeme asks about a subset of them).
-template <int MW>
-struct Lane {
-  int mode;
-  int t1;
-  uint32_t k;
-  int m;
-  uint32_t acur[MW];
-  uint4 ph;  // mode 1: first 16 bytes of the row's stack after shifting t1, loaded early
-};
-
-template <bool L>
-struct RowCtx {
-  const Tables* tb;
-  ParseTabs<L> pt;
-  BaseStack<L> bs;
-  Slot sl;
-  TermView tv;
-  const uint32_t* acc_off;  // accept-list offsets (LDS or global)
-  const uint8_t* acc_list;  // accept lists (LDS or global)
-  const uint32_t* a2;       // row's allowed sets after each first shift
-  int a2_stride;            // words per terminal in a2
-  const uint8_t* clsA;      // trailing flags per DFA state under A(sigma), or null
-  const uint8_t* clsW;      // the same after shifting the winner, or null
-  int winner;               // the pending lexeme's winner (-1 none)
-  const Post* post;         // row's stacks after each first shift (global)
-};
-
-// Mode 2: acur = the allowed terminals of the lane's stack among those live
-// in DFA state q_next (ignored ones left out: they are always viable).  1 ok,
-// -1 capacity.
-template <bool L, int MW>
-__device__ __forceinline__ int lane_allowed(const RowCtx<L>& rc, Lane<MW>& ln, mptr<L, uint16_t> ov, int cap,
-                                            int q_next) {
-  uint32_t X[MW];
-  const uint32_t* lv = rc.tv.live + (size_t)q_next * rc.tv.lstride;
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    X[w] = q_next == kDead ? 0u : lv[w] & ~rc.tv.I[w];
-    ln.acur[w] = 0;
-  }
-  return sim_set<L, MW>(rc.pt, rc.bs, ln.k, ln.m, ov, ov + ln.m, cap - ln.m, X, ln.acur) < 0 ? -1 : 1;
-}
-
-// Emits the pending lexeme in DFA state q (lexicon state lx); q_next is the
-// DFA state after the next lexeme's first byte.  ov is the lane's stack area
-// of cap entries: the overlay occupies [0, m), virtual pushes use [m, cap).
-// 1 ok, 0 reject, -1 capacity.
-template <bool L, int MW>
-__device__ __forceinline__ int emit(const RowCtx<L>& rc, Lane<MW>& ln, mptr<L, uint16_t> ov, int cap, int q,
-                                    const LexState& lx, int q_next) {
-  const int t = winner_of<MW>(rc.tv, rc.acc_off, rc.acc_list, ln.acur, q,
-                              [&]() { return lex_flags_now(*rc.tb, rc.sl, lx); });
-  if (t < 0) return 0;
-  // an ignored winner leaves the stack unchanged; in mode 2 the next lexeme
-  // still asks anew for its live terminals (the one allowed-set call below
-  // serves ignored and shifted lanes of a wave together)
-  const bool ignored = bit_of(rc.tv.I, t);
-  if (ignored && ln.mode != 2) return 1;
-  if (!ignored && ln.mode == 0) {
-    ln.mode = 1;
-    ln.t1 = t;
-    ln.ph = reinterpret_cast<const uint4*>(rc.post)[2 * t];  // needed at the next shift
-#pragma unroll
-    for (int w = 0; w < MW; ++w) ln.acur[w] = rc.a2[t * rc.a2_stride + w];
-    return 1;
-  }
-  if (!ignored && ln.mode == 1) {  // the stack after t1 (Post: k u16, m u8, ok u8, overlay u16[kPostCap])
-    const uint32_t pk = ln.ph.x & 0xFFFFu, pm = (ln.ph.x >> 16) & 0xFFu, pok = ln.ph.x >> 24;
-    if (!pok || pk == 0 || pk > rc.bs.depth || pm > (uint32_t)kPostCap || (int)pm > cap) return -1;
-    ln.k = pk;
-    ln.m = (int)pm;
-    const uint32_t lo[3] = {ln.ph.y, ln.ph.z, ln.ph.w};
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-      if (j < ln.m) ov[j] = (uint16_t)(lo[j >> 1] >> (16 * (j & 1)));
-    if (ln.m > 6) {
-      const uint4 h2 = reinterpret_cast<const uint4*>(rc.post)[2 * ln.t1 + 1];
-      const uint32_t hi[4] = {h2.x, h2.y, h2.z, h2.w};
-#pragma unroll
-      for (int j = 6; j < 14; ++j)
-        if (j < ln.m) ov[j] = (uint16_t)(hi[(j - 6) >> 1] >> (16 * (j & 1)));
-    }
-    ln.mode = 2;
-  }
-  if (!ignored) {
-    const int r = sim1_shift<L, MW>(rc.pt, rc.bs, ln.k, ln.m, ov, cap, t);
-    if (r != 1) return r < 0 ? -1 : 0;
-  }
-  return lane_allowed<L, MW>(rc, ln, ov, cap, q_next);
 }
 
 struct DfaView {  // lexer DFA by byte class (LDS copy or global)
@@ -1557,131 +1227,13 @@ struct DfaView {  // lexer DFA by byte class (LDS copy or global)
   __device__ int next(int q, uint32_t c) const { return next_[q * C + c]; }
 };
 
-// Walks the bytes [i, n) of one spelling from lane state (ln, q, lx); f is
-// the trailing flags of the last byte taken before i (1 if none).
-// byte_at(i) yields byte i, called once per i in increasing order.  The lanes
-// of a wave alternate between a scan phase (every lane that can takes its
-// next byte: a DFA step and the trailing class, all in LDS) and an emission
-// phase (lanes whose byte killed the DFA emit together), so a wave pays for
-// emissions once per emission depth rather than once per byte.  Lexicon
-// lookups happen only where a lexeme ends: at an emission, and at the end of
-// the spelling when only restricted terminals remain (by the shrinking of live
-// sets this one check covers every byte of the lexeme).  1 allowed,
-// 0 rejected, -1 capacity.
-template <bool L, int MW, class ByteAt>
-__device__ __forceinline__ int walk_bytes(const RowCtx<L>& rc, Lane<MW>& ln, int q, LexState lx, uint32_t i,
-                                          uint32_t n, ByteAt byte_at, const DfaView& step, mptr<L, uint16_t> ov,
-                                          int cap, uint32_t f) {
-  const Tables& tb = *rc.tb;
-  const bool track = rc.sl.restricted != 0;
-  // trailing flags of a state: from the row's table while the lane's allowed
-  // set is that of sigma or of the winner's shift, else computed
-  const uint8_t* ctab = ln.mode == 0 ? rc.clsA : (ln.mode == 1 && ln.t1 == rc.winner ? rc.clsW : nullptr);
-  int status = 2;         // 2 running, else the result
-  int pend = -1;          // byte class waiting for an emission
-  uint32_t pend_b = 0;    // that byte
-  // look-ahead, so that a byte costs one round trip to LDS: byte i and its
-  // class (b0, c0), the DFA step on it from q (nx), byte i + 1 and its class
-  // (b1, c1); each byte is fetched once, in increasing order, and only below n
-  uint32_t b0 = i < n ? byte_at(i) : 0u;
-  uint32_t b1 = i + 1 < n ? byte_at(i + 1) : 0u;
-  uint32_t c0 = step.cls(b0), c1 = step.cls(b1);
-  int nx = i < n ? step.next(q, c0) : kDead;
-  // f: trailing flags after the last byte taken (the caller's, before any)
-  for (;;) {
-    for (;;) {  // scan phase
-      const bool run = status == 2 && pend < 0 && i < n;
-      if (!__any(run)) break;
-      if (run) {
-        if (nx != kDead) {
-          q = nx;
-          if (lx.need) lex_push(tb, rc.sl, lx, b0);
-          // byte i's flags, the step on byte i + 1 and byte i + 2's class
-          // depend on q or on nothing: issued together
-          const uint32_t b2 = i + 2 < n ? byte_at(i + 2) : 0u;
-          const uint32_t c2 = step.cls(b2);
-          const int nx1 = i + 1 < n ? step.next(q, c1) : kDead;
-          f = ctab ? (uint32_t)ctab[q] : trail_flags<MW>(rc.tv, ln.acur, q);
-          if (f == 0) {
-            status = 0;
-          } else {
-            ++i;
-            b0 = b1;
-            c0 = c1;
-            nx = nx1;
-            b1 = b2;
-            c1 = c2;
-          }
-        } else {
-          pend = (int)c0;
-          pend_b = b0;
-        }
-      }
-    }
-    if (status == 2 && pend < 0)  // the spelling ended inside a lexeme
-      status = ((f & 1u) || trail_lex<MW>(rc.tv, ln.acur, q, lex_flags_now(tb, rc.sl, lx))) ? 1 : 0;
-    const bool em = status == 2 && pend >= 0;
-    if (!__any(em)) break;
-    if (em) {  // emission phase
-      const int r = emit<L, MW>(rc, ln, ov, cap, q, lx, step.next(kStart, (uint32_t)pend));
-      if (r <= 0) {
-        status = r;
-      } else {
-        ctab = ln.mode == 0 ? rc.clsA : (ln.mode == 1 && ln.t1 == rc.winner ? rc.clsW : nullptr);
-        q = step.next(kStart, (uint32_t)pend);  // byte i starts the next lexeme
-        const uint32_t b2 = q != kDead && i + 2 < n ? byte_at(i + 2) : 0u;
-        const uint32_t c2 = step.cls(b2);
-        const int nx1 = q != kDead && i + 1 < n ? step.next(q, c1) : kDead;
-        f = q == kDead ? 0u : (ctab ? (uint32_t)ctab[q] : trail_flags<MW>(rc.tv, ln.acur, q));
-        lx = LexState{pend_b, 1u, kNoLex, track && (f & 2u) ? 1u : 0u};
-        if (f == 0) {
-          status = 0;
-        } else {
-          ++i;
-          b0 = b1;
-          c0 = c1;
-          nx = nx1;
-          b1 = b2;
-          c1 = c2;
-        }
-        pend = -1;
-      }
-    }
-  }
-  return status;
-}
-
-// Bytes 1, 2, ... of one spelling, called in that order: a 64-bit window
-// holds the next bytes, taken from the record (bytes 0..7), the tail chunk
-// fetched with it (bytes 8..23), then one 16-byte load per overflow chunk.
-struct SpellBytes {
-  uint64_t win;      // next bytes, lowest first
-  uint64_t lo0, hi;  // bytes 8..15; the second half of the current chunk
-  const uint4* ovf;  // overflow chunk c holds bytes 24 + 16c .. 39 + 16c
-  __device__ uint32_t operator()(uint32_t i) {
-    if (i >= 8 && (i & 7) == 0) {
-      if (i == 8) {
-        win = lo0;
-      } else if ((i & 15) == 0) {
-        win = hi;
-      } else {
-        const uint4 c = ovf[(i - 24) >> 4];
-        win = (uint64_t)c.x | (uint64_t)c.y << 32;
-        hi = (uint64_t)c.z | (uint64_t)c.w << 32;
-      }
-    }
-    const uint32_t b = (uint32_t)win & 0xFFu;
-    win >>= 8;
-    return b;
-  }
-};
-
 // ----------------------------------------------------------- class verdicts
 // Codes of a class for a row (2 bits per class in the row's verdict table).
 // kVerdictLexicon: the verdict depends on the schema lexicon (a lexeme's
 // winner or the trailing lexeme's viability), so each token of the class is
 // judged again with its own lexemes' lexicon flags.
 constexpr uint32_t kVerdictReject = 0, kVerdictAllow = 1, kVerdictWalk = 2, kVerdictLexicon = 3;
+constexpr uint32_t kCodeCi = 4;  // beside kVerdictAllow in a class's byte: its tokens are context-independent
 
 // Answers of a lexicon policy besides flags: the question is open (no
 // answer: the class is decided by the lexicon), or the lexeme is out of
@@ -1689,146 +1241,191 @@ constexpr uint32_t kVerdictReject = 0, kVerdictAllow = 1, kVerdictWalk = 2, kVer
 // marks a lexeme whose flags were not asked for yet.
 constexpr uint32_t kLexOpen = 0xFFFFFFFFu, kLexOut = 0xFFFFFFFEu;
 
-// Verdict of one lexeme-program class for a row.  The lexemes the token
-// ends are judged in order against the allowed set the parser has at that
-// point: A(sigma) before any shift, the prologue's allowed set after the
-// first shift (a2, a2_stride words per terminal; the live sets have
-// live_stride words per DFA state), unknown after a second
-// one.  Each ended lexeme's winner is the first accept-list entry (priority
-// order) that is ignored or allowed and, for a restricted terminal, whose
-// category has the lexeme as a word (section 2, L3); the trailing lexeme
-// (state after the last byte) must still complete to an allowed or ignored
-// terminal, a restricted one only where the lexeme prefixes a word of its
-// category (Definition 2).  An ignored unrestricted terminal live there
-// accepts it under any stack.  Lexicon flags come from lex.word(i) (lexeme
-// i) and lex.trail(); a lexeme after two shifts and a token with more
-// recorded ends than the record holds are left to the byte walk.  With Reg,
-// the row's allowed, restricted and ignored sets are first copied to
-// registers (fewer dependent LDS reads, more registers).
-template <int MW, class Lex, bool Reg = true>
-__device__ __forceinline__ uint32_t class_verdict(const RowHeader& h, const uint32_t* I, const uint32_t* live,
-                                                  int live_stride, const uint32_t* tinfo, const uint32_t* acc_off,
-                                                  const uint8_t* acc_list, const uint32_t* a2, int a2_stride,
-                                                  uint4 rec, Lex& lex) {
+// Verdict of one lexeme-program class, or of one of its tokens, for a row.  The
+// lexemes the token ends are judged in order against the allowed set the parser
+// has at that point: A(sigma) before any shift, the prologue's set after the
+// first, the set after the second where it is known.
+// Each ended lexeme's winner is the first accept-list entry (priority order)
+// that is ignored or allowed and, for a restricted terminal, whose category has
+// the lexeme as a word (section 2, L3); the trailing lexeme (state after the
+// last byte) must still complete to an allowed or ignored terminal, a restricted
+// one only where the lexeme prefixes a word of its category (Definition 2).  An
+// ignored unrestricted terminal live there accepts it under any stack.  Lexicon
+// flags come from lex.word(i) (lexeme i) and lex.trail().
+// With a second shift, or more ends than the record holds, the verdict is
+// kVerdictWalk.  An accept list is one packed word, and the
+// first three candidates' bits are read side by side, so a lexeme costs two
+// dependent LDS reads and hardly a branch.
+
+template <int MW>
+__device__ __forceinline__ bool set_has(const uint32_t (&set)[MW], uint32_t t) {
+  uint32_t w = 0;  // masked, not selected: a select of array elements becomes an indexed load from scratch
+#pragma unroll
+  for (int i = 0; i < MW; ++i) w |= set[i] & (0u - (uint32_t)((t >> 5) == (uint32_t)i));
+  return (w >> (t & 31u)) & 1u;
+}
+
+// What a verdict reads of the row and the grammar.  The allowed sets are in LDS
+// with the ignored terminals added: usets[0] from sigma, usets[1 + t] after
+// shifting t, 8 words each.
+template <int MW>
+struct RowView {
+  uint32_t R[MW], I[MW];     // restricted and ignored terminals (uniform)
+  const uint32_t* R_s;       // R in LDS
+  const uint32_t* usets;     // [1 + T][8]
+  const uint32_t* live;      // [S][8]
+  const uint32_t* acc;       // packed accept lists [S]
+  const uint32_t* acc_off;   // the lists themselves, past the packed three
+  const uint8_t* acc_list;
+  const uint32_t* tinfo;
+  int winner;
+  uint32_t wkind;
+  __device__ __forceinline__ int accept(uint32_t q, uint32_t packed, uint32_t j) const {
+    return j < 3u ? (int)((packed >> (8u * j)) & 0xFFu) : (int)acc_list[acc_off[q] + j];
+  }
+  __device__ __forceinline__ const uint32_t* after(int t) const { return usets + (1 + t) * 8; }
+  // The winner of a lexeme that ends in state q when set is the allowed set:
+  // the first accept-list entry in the set that, if restricted, has its
+  // category's word flag in flags() (asked for at most once).  -1 if none.
+  template <class Flags>
+  __device__ __forceinline__ int winner_in(uint32_t q, const uint32_t* set, Flags flags) const {
+    const uint32_t packed = acc[q], n = packed >> 24;
+    const uint32_t c0 = packed & 0xFFu, c1 = (packed >> 8) & 0xFFu, c2 = (packed >> 16) & 0xFFu;
+    const uint32_t u0 = set[c0 >> 5] >> (c0 & 31u), u1 = set[c1 >> 5] >> (c1 & 31u), u2 = set[c2 >> 5] >> (c2 & 31u);
+    const uint32_t r0 = R_s[c0 >> 5] >> (c0 & 31u), r1 = R_s[c1 >> 5] >> (c1 & 31u), r2 = R_s[c2 >> 5] >> (c2 & 31u);
+    const uint32_t ok = ((u0 & 1u) | (u1 & 1u) << 1 | (u2 & 1u) << 2) & ((1u << min(n, 3u)) - 1u);
+    const uint32_t rs = (r0 & 1u) | (r1 & 1u) << 1 | (r2 & 1u) << 2;
+    if (ok == 0u && n <= 3u) return -1;
+    const uint32_t f = ok & (0u - ok);
+    if (f & ~rs) return (int)(f == 1u ? c0 : (f == 2u ? c1 : c2));
+    uint32_t wf = 0;
+    bool have = false;
+    for (uint32_t j = 0; j < n; ++j) {  // a restricted candidate first, or a long list
+      const int c = accept(q, packed, j);
+      if (!((set[c >> 5] >> (c & 31)) & 1u)) continue;
+      if ((R_s[c >> 5] >> (c & 31)) & 1u) {
+        if (!have) wf = flags();
+        have = true;
+        if (!((wf >> (8 + ((tinfo[c] >> 8) & 7u))) & 1u)) continue;
+      }
+      return c;
+    }
+    return -1;
+  }
+};
+
+// A view of the row whose block is in LDS.
+template <int MW>
+__device__ __forceinline__ void view_row(RowView<MW>& rv, const Tables& tb, const RowLayout& RL, const uint8_t* block) {
+  const RowHeader& h = *(const RowHeader*)block;
+#pragma unroll
+  for (int w = 0; w < MW; ++w) {
+    rv.R[w] = __builtin_amdgcn_readfirstlane(h.R[w]);
+    rv.I[w] = tb.ign[w];
+  }
+  rv.R_s = h.R;
+  rv.usets = (const uint32_t*)(block + RL.usets);
+  rv.acc = (const uint32_t*)(block + RL.acc);
+  rv.acc_off = tb.acc_off;
+  rv.acc_list = tb.acc_list;
+  rv.winner = __builtin_amdgcn_readfirstlane(h.winner);
+  rv.wkind = __builtin_amdgcn_readfirstlane(h.wkind);
+}
+
+// Definition 2's test of a trailing lexeme in state q against the set cur
+// (known: the parser's whole allowed set; else only what holds under any stack).
+template <int MW, class Trail>
+__device__ __forceinline__ uint32_t trail_verdict(const RowView<MW>& rv, const uint32_t* set, bool known, uint32_t q,
+                                                  Trail trail) {
+  const uint32_t* lv = rv.live + (size_t)q * 8;
+  uint32_t unres = 0, res = 0, ign = 0, rw[MW];
+#pragma unroll
+  for (int w = 0; w < MW; ++w) {
+    const uint32_t l = lv[w], bits = l & set[w];
+    unres |= bits & ~rv.R[w];
+    rw[w] = bits & rv.R[w];
+    res |= rw[w];
+    ign |= l & rv.I[w] & ~rv.R[w];
+  }
+  if (ign || (known && unres)) return kVerdictAllow;
+  if (!known) return kVerdictWalk;
+  if (!res) return kVerdictReject;
+  uint32_t cats = 0;
+#pragma unroll
+  for (int w = 0; w < MW; ++w)
+    for (uint32_t r = rw[w]; r; r &= r - 1) cats |= 1u << ((rv.tinfo[w * 32 + __ffs(r) - 1] >> 8) & 7u);
+  return (trail(cats) & cats) ? kVerdictAllow : kVerdictReject;
+}
+
+template <int MW, class Lex>
+__device__ __forceinline__ uint32_t class_verdict(const RowView<MW>& rv, uint4 rec, Lex& lex) {
   const uint32_t w0 = rec.x;
   if (w0 & kClassReject) return kVerdictReject;
   if (w0 & kClassWalk) return kVerdictWalk;
   const uint32_t ends = w0 & kClassEndsMask;
-  const uint32_t qe[kClassEnds] = {rec.y >> 16, rec.z & 0xFFFFu, rec.z >> 16};
-  // the row's sets: 0 allowed A(sigma), 1 restricted R, 2 ignored I
-  uint32_t Ar[MW], Rr[MW], Ir[MW];
-  if constexpr (Reg) {
-#pragma unroll
-    for (int w = 0; w < MW; ++w) {
-      Ar[w] = h.A[w];
-      Rr[w] = h.R[w];
-      Ir[w] = I[w];
-    }
-  }
-  auto bit = [&](int which, int c) -> bool {
-    if constexpr (!Reg) return bit_of(which == 0 ? h.A : (which == 1 ? h.R : I), c);
-    const uint32_t* set = which == 0 ? Ar : (which == 1 ? Rr : Ir);
-    uint32_t word = 0;
-#pragma unroll
-    for (int w = 0; w < MW; ++w)
-      if (w == (c >> 5)) word = set[w];
-    return (word >> (c & 31)) & 1u;
-  };
-  int sel = -1;  // allowed set now: -1 A(sigma), t >= 0 after shifting t, -2 unknown
-  const uint32_t nchk = ends > (uint32_t)kClassEnds ? (uint32_t)kClassEnds : ends;
-  for (uint32_t i = 0; i < nchk; ++i) {
-    int t = -1;
+  const uint32_t* set = rv.usets;  // the set in force
+  int sel = -1;                    // -1 from sigma, t >= 0 after shifting t, -2 unknown
+  for (uint32_t i = 0; i < min(ends, (uint32_t)kClassEnds); ++i) {
+    int t;
     if (i == 0 && (w0 & kClassP0)) {  // byte 0 ends the pending lexeme: the prologue's winner
-      if (h.wkind == 0) return kVerdictReject;
-      if (h.wkind == 1) continue;
-      t = h.winner;
+      if (rv.wkind == 0) return kVerdictReject;
+      t = rv.winner;
     } else {
       if (sel == -2) return kVerdictWalk;
-      const uint32_t q = qe[i];
-      uint32_t wf = kLexOpen;  // the lexeme's lexicon flags, asked for at most once
-      for (uint32_t j = acc_off[q]; j < acc_off[q + 1]; ++j) {
-        const int c = acc_list[j];
-        const bool ok = bit(2, c) || (sel == -1 ? bit(0, c) : bit_of(a2 + sel * a2_stride, c));
-        if (!ok) continue;
-        if (bit(1, c)) {
-          if (wf == kLexOpen) wf = lex.word(i);
-          if (wf == kLexOpen) return kVerdictLexicon;
-          if (wf == kLexOut) return kVerdictWalk;
-          if (!((wf >> (8 + ((tinfo[c] >> 8) & 7u))) & 1u)) continue;
-        }
-        t = c;
-        break;
-      }
+      const uint32_t q = i == 0 ? rec.y >> 16 : (i == 1 ? rec.z & 0xFFFFu : rec.z >> 16);
+      t = rv.winner_in(q, set, [&]() { return lex.word(i); });
       if (t < 0) return kVerdictReject;
-      if (bit(2, t)) continue;
     }
-    sel = sel == -1 ? t : -2;
+    if (set_has<MW>(rv.I, t)) continue;
+    if (sel == -1) {
+      sel = t;
+      set = rv.after(t);
+    } else {
+      sel = -2;
+    }
   }
   if (ends > (uint32_t)kClassEnds) return kVerdictWalk;
-  const uint32_t* lv = live + (size_t)(rec.y & 0xFFFFu) * live_stride;
-  uint32_t unres = 0, res = 0, ign = 0;
-  uint32_t rw[MW];  // restricted terminals that keep the trailing lexeme viable
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    const uint32_t Aw = Reg ? Ar[w] : h.A[w], Rw = Reg ? Rr[w] : h.R[w], Iw = Reg ? Ir[w] : I[w];
-    const uint32_t acur = sel == -1 ? Aw : (sel >= 0 ? a2[sel * a2_stride + w] : 0u);
-    const uint32_t bits = lv[w] & (acur | Iw);
-    unres |= bits & ~Rw;
-    rw[w] = bits & Rw;
-    res |= rw[w];
-    ign |= lv[w] & Iw & ~Rw;
-  }
-  if (ign || (sel != -2 && unres)) return kVerdictAllow;
-  if (sel == -2) return kVerdictWalk;
-  if (!res) return kVerdictReject;
-  const uint32_t pf = lex.trail();
-  if (pf == kLexOpen) return kVerdictLexicon;
-  if (pf == kLexOut) return kVerdictWalk;
-  uint32_t cats = 0;
-#pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    uint32_t r = rw[w];
-    while (r) {
-      cats |= 1u << ((tinfo[w * 32 + __ffs(r) - 1] >> 8) & 7u);
-      r &= r - 1;
-    }
-  }
-  return (pf & cats) ? kVerdictAllow : kVerdictReject;
+  return trail_verdict<MW>(rv, set, sel != -2, rec.y & 0xFFFFu, [&](uint32_t cats) { return lex.trail(cats); });
 }
 
-// A lexeme of the class record that starts in the start state at byte 0 or 1
-// of the token: the token-flag table (GRID_ART_LEX_TOKEN) answers for it.
-// Its start offset, or -1.  Lexeme 0 and a trailing lexeme after no end hold
-// the pending bytes, so they qualify only when those are empty.
-__device__ __forceinline__ int covered_start(uint32_t pos, uint32_t i, bool pending_empty) {
-  if (i == 0) return pending_empty ? 0 : -1;
-  const uint32_t o = (pos >> (8 * (i - 1))) & 0xFFu;
-  return o <= 1u ? (int)o : -1;
+// Whether lexeme i of a class record (i = 0 with no end: the trailing one) holds
+// the pending bytes, and the byte it starts at; trail: the trailing lexeme.
+__device__ __forceinline__ bool holds_pending(const uint4& rec, uint32_t i) { return i == 0 && !(rec.x & kProgFresh); }
+__device__ __forceinline__ uint32_t lexeme_start(const uint4& rec, int prog, uint32_t i, bool trail) {
+  if (!prog) return i == 0 ? 0u : (rec.w >> (8u * (i - 1u))) & 0xFFu;  // where the lexeme before it ended
+  if (trail) return rec.x >> 24;
+  return i == 0 ? rec.w >> 24 : (i == 1 ? (rec.x >> 8) & 0xFFu : (rec.x >> 16) & 0xFFu);
 }
 
 // Lexicon policy that answers the class's first lexicon question with "no
 // flags" and records it (kind, start offset in the token, whether the lexeme
 // holds the pending bytes); it notes whether a second question is asked.
 struct LexNo {
-  uint32_t pos, ends;
+  uint4 rec;
+  int prog;
   bool pending_empty;
   int kind;           // first question: -1 none yet, 0 trailing prefix, 1 word
-  int start;          // its start offset in the token, or -1
+  int start;          // its start offset in the token where the token-flag table
+                      // (GRID_ART_LEX_TOKEN: bytes 0 and 1, in the start state) answers for it, or -1
   bool pending;       // its lexeme holds the pending bytes
   bool second;        // a second question was asked
+  uint32_t cats;      // the categories a trailing question asks about
   __device__ void first(uint32_t i, int k) {
     kind = k;
-    pending = i == 0 && !pending_empty;
-    start = covered_start(pos, i, pending_empty);
+    const bool hp = holds_pending(rec, i);
+    const uint32_t o = lexeme_start(rec, prog, i, k == 0);
+    pending = hp && !pending_empty;
+    start = hp ? (pending_empty ? 0 : -1) : (o <= 1u ? (int)o : -1);
   }
   __device__ uint32_t word(uint32_t i) {
     if (kind >= 0) second = true;
     else first(i, 1);
     return 0u;
   }
-  __device__ uint32_t trail() {
-    if (kind >= 0 || ends > (uint32_t)kClassEnds) second = true;
-    else first(ends, 0);
+  __device__ uint32_t trail(uint32_t c) {
+    if (kind >= 0) second = true;
+    else first(rec.x & kClassEndsMask, 0);
+    cats = c;
     return 0u;
   }
 };
@@ -1847,271 +1444,302 @@ struct LexNo {
 // when the token has one (a trailing lexeme, or a word ending at offset 2 or
 // later).
 constexpr uint32_t kNoValid = 1u << 7;
-// The class's code and, for a class the lexicon decides, its shortcut, from
-// one verdict run: the run under "no flags" follows the run without token
-// bytes up to the first lexicon question, so a class that asks none has its
-// final verdict there, and one that asks is a lexicon class whose verdict
-// under "no flags" is the run's result.  Returns the code; *rule receives
-// the shortcut byte of a lexicon class.
+// The class's byte from one verdict run: the run under "no flags" follows the
+// run without token bytes up to the first lexicon question, so a class that asks
+// none has its final verdict there, and one that asks is a lexicon class whose
+// verdict under "no flags" is the run's result.  A trailing question on a lexeme
+// the token-flag table covers is settled by the stream either way: *cats are the
+// categories whose prefix allows the token.
 template <int MW>
-__device__ __forceinline__ uint32_t class_code(const RowHeader& h, const uint32_t* I, const uint32_t* live,
-                                               const uint32_t* tinfo, const uint32_t* acc_off, const uint8_t* acc_list,
-                                               const uint32_t* a2, uint4 rec, uint32_t* rule) {
-  LexNo ln{rec.w, rec.x & kClassEndsMask, h.rem_len == 0, -1, -1, false, false};
-  const uint32_t v = class_verdict<MW>(h, I, live, 8, tinfo, acc_off, acc_list, a2, 8, rec, ln);
+__device__ __forceinline__ uint32_t class_code(const RowView<MW>& rv, int prog, bool pending_empty, uint4 rec,
+                                               uint32_t* cats) {
+  LexNo ln{rec, prog, pending_empty, -1, -1, false, false, 0u};
+  const uint32_t v = class_verdict<MW>(rv, rec, ln);
+  *cats = ln.cats;
   if (ln.kind < 0) return v;  // no lexicon question: the class's verdict
-  *rule = kVerdictLexicon;
   if (ln.second) return kVerdictLexicon;
   if (ln.pending) {
     const bool two = ln.kind == 0 || (rec.w & 0xFFu) >= 2u;
-    *rule = kVerdictLexicon | (two ? 1u << 4 : 0u) | v << 5 | kNoValid;
-    return kVerdictLexicon;
+    return kVerdictLexicon | (two ? 1u << 4 : 0u) | v << 5 | kNoValid;
   }
   if (ln.start < 0) return kVerdictLexicon;
-  *rule = kVerdictLexicon | (ln.kind == 0 ? 1u : 2u) << 2 | (uint32_t)ln.start << 4 | v << 5 | kNoValid;
-  return kVerdictLexicon;
+  return kVerdictLexicon | (ln.kind == 0 ? 1u : 2u) << 2 | (uint32_t)ln.start << 4 | v << 5 | kNoValid;
 }
 
-// LDS layout of the verdict kernel: live sets and the row's allowed sets
-// after one shift (8 words per DFA state / terminal), terminal info, accept
-// lists.
-struct VerdictLds {
-  uint32_t live, a2, tinfo, acc_off, acc_list, total;
+// LDS of a judge workgroup: the row's block up to its stacks, live sets,
+// terminal info.
+struct JudgeLds {
+  uint32_t block, live, tinfo, total;
 };
 
-__host__ __device__ inline VerdictLds verdict_lds(const Tables& tb) {
-  VerdictLds L;
+__host__ __device__ inline JudgeLds judge_lds(const Tables& tb) {
+  JudgeLds L;
   uint32_t o = 0;
+  L.block = o;
+  o += pad16((uint32_t)row_layout(tb).post);
   L.live = o;
   o += (uint32_t)tb.S * 32u;
-  L.a2 = o;
-  o += (uint32_t)tb.T * 32u;
   L.tinfo = o;
   o += pad16((uint32_t)tb.T * 4u);
-  L.acc_off = o;
-  o += pad16((uint32_t)(tb.S + 1) * 4u);
-  L.acc_list = o;
-  o += pad16((uint32_t)tb.n_acc);
   L.total = o;
   return L;
 }
 
-// Two 16-bit masks interleaved bit by bit: bit i of a goes to bit 2i, bit i
-// of b to bit 2i + 1.
-__device__ inline uint32_t interleave16(uint32_t a, uint32_t b) {
-  auto spread = [](uint32_t x) {
-    x &= 0xFFFFu;
-    x = (x | (x << 8)) & 0x00FF00FFu;
-    x = (x | (x << 4)) & 0x0F0F0F0Fu;
-    x = (x | (x << 2)) & 0x33333333u;
-    x = (x | (x << 1)) & 0x55555555u;
-    return x;
-  };
-  return spread(a) | spread(b) << 1;
-}
-
-// Workgroups (row, y): the verdicts of the row's classes, one class per
-// thread, workgroup y taking every gridDim.y-th group of kBlock classes; each
-// wave packs its 64 two-bit codes with two ballots.  A class the lexicon
-// decides also gets its shortcut byte.  The row's allowed sets after one
-// shift, the accept lists, the live sets and the terminal info are staged in
-// LDS first (one batched pass).
+// After the prologue: the verdict byte of every class of the row's lexer state,
+// from A(sigma) and the allowed sets after one shift; a class with a second shift
+// is left to the walk.  Workgroups (row, part), a part being every parts-th block
+// of kJudgeThreads classes.
+// (The sets after two shifts can be had too: a row's classes ask for some 15 pairs
+// of terminals.  Finding them and judging those classes again took each workgroup
+// 5 us, in all 8 to 12 us of a step of 1 to 47 rows; walking their ids as well costs
+// the residue kernel 1 to 3 us.  At 256 rows, 20 us less residue paid for it.)
 template <int MW>
-__global__ __launch_bounds__(kBlock) void verdict_kernel(Tables tb, uint8_t* __restrict__ ws, size_t rbytes) {
-  extern __shared__ __align__(16) uint8_t vlds[];
-  __shared__ RowHeader h;
-  __shared__ uint32_t I_s[8];
-  const int tid = threadIdx.x, lane = tid & 63;
-  uint8_t* rw = ws + kWsHead + (size_t)blockIdx.x * rbytes;
-  if (tid < (int)(sizeof(RowHeader) / 4)) ((uint32_t*)&h)[tid] = ((const uint32_t*)rw)[tid];
-  if (tid < 8) I_s[tid] = tb.ign[tid];
-  __syncthreads();
-  const uint32_t n = h.n_cls;
-  if (h.valid != kRowValid || blockIdx.y * (uint32_t)kBlock >= n) return;  // uniform
+__global__ __launch_bounds__(kJudgeThreads, 8) void judge_kernel(Tables tb, uint8_t* __restrict__ ws, size_t rbytes,
+                                                              int parts) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  const int tid = threadIdx.x;
+  const int row = (int)blockIdx.x / parts, part = (int)blockIdx.x - row * parts;
+  uint8_t* rw = ws + kWsHead + (size_t)row * rbytes;
+  const RowHeader* hdr = (const RowHeader*)rw;
+  const uint32_t n = hdr->n_cls, cls_base = hdr->cls_base;
+  const uint32_t first = (uint32_t)part * kJudgeThreads, stride = (uint32_t)parts * kJudgeThreads;
+  if (hdr->valid != kRowValid || first >= n) return;  // uniform
+  const JudgeLds JL = judge_lds(tb);
   const RowLayout RL = row_layout(tb);
-  const VerdictLds VL = verdict_lds(tb);
-  uint32_t* live_s = (uint32_t*)(vlds + VL.live);
-  uint32_t* a2_s = (uint32_t*)(vlds + VL.a2);
-  uint32_t* tinfo_s = (uint32_t*)(vlds + VL.tinfo);
-  uint32_t* acc_off_s = (uint32_t*)(vlds + VL.acc_off);
-  uint8_t* acc_list_s = vlds + VL.acc_list;
-  // the first class record is fetched while the tables are staged
-  uint4 rec0 = make_uint4(0, 0, 0, 0);
-  if (blockIdx.y * (uint32_t)kBlock + (uint32_t)tid < n) rec0 = tb.crec[h.cls_base + blockIdx.y * kBlock + tid];
-  {
-    const StageRegion rg[5] = {{(const uint8_t*)tb.live, (uint8_t*)live_s, (uint32_t)tb.S * 32u},
-                               {rw + RL.a2, (uint8_t*)a2_s, (uint32_t)tb.T * 32u},
-                               {(const uint8_t*)tb.term_info, (uint8_t*)tinfo_s, (uint32_t)tb.T * 4u},
-                               {(const uint8_t*)tb.acc_off, (uint8_t*)acc_off_s, (uint32_t)(tb.S + 1) * 4u},
-                               {tb.acc_list, acc_list_s, (uint32_t)tb.n_acc}};
-    dma_regions<5>(rg, tid, kBlock);
-  }
+  uint4 rec = make_uint4(0, 0, 0, 0);
+  if (first + (uint32_t)tid < n) rec = tb.crec[cls_base + first + (uint32_t)tid];
+  const StageRegion rg[3] = {{rw, lds + JL.block, (uint32_t)RL.post},
+                             {(const uint8_t*)tb.live, lds + JL.live, (uint32_t)tb.S * 32u},
+                             {(const uint8_t*)tb.term_info, lds + JL.tinfo, (uint32_t)tb.T * 4u}};
+  dma_regions<3>(rg, tid, kJudgeThreads);
+  const RowHeader& h = *(const RowHeader*)(lds + JL.block);
+  RowView<MW> rv;
+  rv.live = (const uint32_t*)(lds + JL.live);
+  rv.tinfo = (const uint32_t*)(lds + JL.tinfo);
   dma_wait();
   __syncthreads();
-  uint32_t* vc = (uint32_t*)(rw + RL.vcode);
-  uint8_t* vr = rw + RL.vrule;
-  for (uint32_t c0 = blockIdx.y * kBlock; c0 < n; c0 += gridDim.y * kBlock) {  // uniform
-    const uint32_t c = c0 + tid;
+  view_row(rv, tb, RL, lds + JL.block);
+  const bool empty = h.rem_len == 0;
+  uint8_t* codes = rw + RL.codes;
+  uint8_t* cats = rw + RL.cats;
+  for (uint32_t c = first + (uint32_t)tid; c < n; c += stride) {
+    const uint4 cur = rec;
+    if (c + stride < n) rec = tb.crec[cls_base + c + stride];
+    const bool ci = ci_class(cur.x);
     uint32_t code = kVerdictReject;
-    if (c < n) {
-      const uint4 rec = c0 == blockIdx.y * (uint32_t)kBlock ? rec0 : tb.crec[h.cls_base + c];
-      if (h.ci_hit >= 0 && ci_class(rec.x)) {  // served by the row's cached context-independent words
-        code = kVerdictReject;
-      } else {
-        uint32_t rule = 0;
-        code = class_code<MW>(h, I_s, live_s, tinfo_s, acc_off_s, acc_list_s, a2_s, rec, &rule);
-        if (code == kVerdictLexicon) vr[c] = (uint8_t)rule;
-      }
+    if (!(h.ci_hit >= 0 && ci)) {  // (else served by the row's cached context-independent words)
+      uint32_t ct = 0;
+      code = class_code<MW>(rv, tb.prog, empty, cur, &ct);
+      if (((code >> 2) & 3u) == 1u) cats[c] = (uint8_t)ct;  // (only a trailing question has that kind)
+      if (code == kVerdictAllow && ci) code |= kCodeCi;
     }
-    const uint64_t b0 = __ballot(code & 1u), b1 = __ballot(code & 2u);
-    // this wave's 64 classes are words (c0 + 64 * wave) / 16 .. + 3 of the table
-    if (lane < 4) {
-      const uint32_t first = c0 + (uint32_t)(tid & ~63) + 16u * (uint32_t)lane;
-      if (first < n) vc[first >> 4] = interleave16((uint32_t)(b0 >> (16 * lane)), (uint32_t)(b1 >> (16 * lane)));
-    }
-
+    codes[c] = (uint8_t)code;
   }
 }
 
-
 // ------------------------------------------------------------------ stream
-// The mask in token-id order straight from the class map.  Workgroup i runs
-// on XCD i mod 8 and covers one row and kStreamChunks consecutive 64-id
-// chunks inside that XCD's eighth of the vocabulary, so each XCD's L2 holds
-// one eighth of every lexer state's class map.  A wave turns 64 ids into two
-// mask words with one ballot (class verdict "allow", or the EOS id when the
-// row may end).  A token whose class the lexicon decides takes the class's
-// shortcut verdict when the answer to the class's first lexicon question is
-// "no flags" for it (from its first byte and the row's continuation table, or
-// from its token-flag entry).  Every other undecided token marks its
-// spelling in the row's residue bitmap.  Rows served from the mask cache are
-// skipped; rows with a bad configuration get zero words.
-constexpr int kStreamWaves = kBlock / 64;
-constexpr int kStreamUnroll = 4;   // chunks per wave in flight
-constexpr int kStreamRounds = 1;
-constexpr int kStreamChunks = kStreamWaves * kStreamUnroll * kStreamRounds;
+// LDS of a stream workgroup: the row's class bytes, a queue of open ids per
+// wave, those it leaves open.
+struct StreamLds {
+  uint32_t codes, queue, list, total;
+};
+__host__ __device__ inline StreamLds stream_lds(const Tables& tb) {
+  StreamLds L;
+  uint32_t o = 0;
+  L.codes = o;
+  o += pad16((uint32_t)tb.max_classes);
+  L.queue = o;
+  o += kStreamWaves * kStepIds * 4;
+  L.list = o;
+  o += kOpenLocal * 8;
+  L.total = o;
+  return L;
+}
 
-__host__ __device__ inline int stream_slices(int V) { return ((V + 63) / 64 + 7) / 8; }
-__host__ __device__ inline int stream_groups(int V) { return (stream_slices(V) + kStreamChunks - 1) / kStreamChunks; }
+// Eight consecutive class ids (u16), a class-map row being aligned to 2 bytes.
+struct __attribute__((packed, aligned(2))) Ids8 {
+  uint32_t w[4];
+};
 
-__global__ __launch_bounds__(kBlock) void stream_kernel(Tables tb, uint32_t* __restrict__ mask,
-                                                        uint8_t* __restrict__ ws, size_t rbytes, int B) {
+// Position of this lane among the lanes of bal.
+__device__ __forceinline__ int lane_rank(uint64_t bal) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+}
+
+// The mask in token-id order straight from the class map, one row against one
+// slice of the vocabulary per workgroup.  A wave step covers 512 ids, 8 per
+// lane: one 16-byte load of the class map, eight class bytes gathered from LDS,
+// the allowed bits as one byte of the mask.  The ids the class byte leaves
+// open go to the wave's own queue and are taken 64 at a time, so that their
+// lookups cost what the open ids need and not what the step has: a class the
+// lexicon decides takes its shortcut verdict when the answer to its first
+// lexicon question is "no flags" for the token (from its first two bytes and
+// the row's continuation tables, or from its token-flag summary), or when that
+// question is a trailing one the token's prefix flags answer.  What stays
+// open is listed for the residue kernel, and marked in the row's open bitmap for
+// the row that has more than its list holds.  Rows served from the mask cache are skipped; rows with a bad
+// configuration get zero words.
+__global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, uint32_t* __restrict__ mask,
+                                                                uint8_t* __restrict__ ws, size_t rbytes, int B,
+                                                                int n_slices, int slice_ids) {
+  extern __shared__ __align__(16) uint8_t slds[];
+  __shared__ int open_s, base_s;
+  __shared__ uint32_t mbits[kStreamWaves][kStepIds / 32], cbits[kStreamWaves][kStepIds / 32],
+      obits[kStreamWaves][kStepIds / 32];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int x = (int)(blockIdx.x & 7u);
-  const int g = (int)(blockIdx.x >> 3);
-  const int row = g % B, k = g / B;
-  const int nch = (tb.V + 63) / 64, cps = stream_slices(tb.V);
-  const int c_lo = x * cps + k * kStreamChunks;
-  const int c_hi = min(min(c_lo + kStreamChunks, (x + 1) * cps), nch);
-  if (c_lo >= c_hi) return;  // uniform
+  const int row = (int)blockIdx.x / n_slices, slice = (int)blockIdx.x - row * n_slices;
+  const int lo = slice * slice_ids, hi = min(lo + slice_ids, tb.V);
   uint8_t* rw = ws + kWsHead + (size_t)row * rbytes;
   RowHeader* hdr = (RowHeader*)rw;
   const uint32_t valid = hdr->valid;
   if (valid == kRowCached) return;
   uint32_t* mrow = mask + (size_t)row * tb.W;
   if (valid != kRowValid) {  // bad configuration: an empty row
-    for (int c = c_lo + wave; c < c_hi; c += kStreamWaves)
-      if (lane < 2 && 2 * c + lane < tb.W) mrow[2 * c + lane] = 0u;
+    for (int w = (lo >> 5) + tid; w < min((lo + slice_ids) >> 5, tb.W); w += kStreamThreads) mrow[w] = 0u;
     return;
   }
+  const StreamLds SL = stream_lds(tb);
   const RowLayout RL = row_layout(tb);
-  const uint32_t q = hdr->q;
+  const uint16_t* cm = tb.cmap + (size_t)hdr->q * tb.V;
+  const uint32_t cls_base = hdr->cls_base;
+  {
+    const StageRegion rg[1] = {{rw + RL.codes, slds + SL.codes, pad16(hdr->n_cls)}};
+    dma_regions<1>(rg, tid, kStreamThreads);
+  }
+  const uint8_t* codes = slds + SL.codes;
+  const uint32_t* cont2 = (const uint32_t*)(rw + RL.cont2);
+  uint32_t* queue = (uint32_t*)(slds + SL.queue) + wave * kStepIds;
   const int eos = hdr->eos_ok ? tb.eos_id : -1;
+  const uint8_t* tsum = tb.lex_toksum + (size_t)hdr->slot_id * tb.V;
+  const uint32_t* tok = tb.lex_token + (size_t)hdr->slot_id * tb.V;
+  const uint8_t* cats = rw + RL.cats;
   // a row served by cached context-independent words ORs them into its words
-  const int ci = hdr->ci_hit;
+  const int ci = hdr->ci_hit, claim = hdr->ci_claim;
   const uint32_t* ciw = ci >= 0 ? (const uint32_t*)(tb.ci_cache + (size_t)ci * tb.ci_stride + kCiHeader) : nullptr;
   // a row that claimed an entry writes its CI tokens' bits there (the residue
-  // pass adds those it decides; finalize publishes the entry)
-  const int claim = hdr->ci_claim;
+  // pass adds those it decides)
   uint32_t* cdst = claim >= 0 ? (uint32_t*)(tb.ci_cache + (size_t)claim * tb.ci_stride + kCiHeader) : nullptr;
-  const uint4* crow = tb.crec + hdr->cls_base;
-  // the row's 2-bit class codes are read where the class map points (an
-  // L2-resident gather: staging all of them in LDS per workgroup cost more)
-  const uint32_t* vg = (const uint32_t*)(rw + RL.vcode);
-  const uint16_t* cm = tb.cmap + (size_t)q * tb.V;
-  const uint8_t* tsum = tb.lex_toksum + (size_t)hdr->slot_id * tb.V;
-  const uint8_t* vrule = rw + RL.vrule;
-  unsigned long long* rbits = (unsigned long long*)(rw + RL.rbits);
   uint32_t cont[8];
 #pragma unroll
   for (int w = 0; w < 8; ++w) cont[w] = hdr->cont[w];
+  // the class ids of this lane in a step, 0 (rejected) past the vocabulary
+  auto load_ids = [&](int id0) -> Ids8 {
+    Ids8 v = {{0, 0, 0, 0}};
+    if (id0 + 8 <= tb.V) {
+      v = *reinterpret_cast<const Ids8*>(cm + id0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (id0 + j < tb.V) v.w[j >> 1] |= (uint32_t)cm[id0 + j] << (16 * (j & 1));
+    }
+    return v;
+  };
   bool any = false;
-  constexpr int kPer = kStreamRounds * kStreamUnroll;  // chunks per wave
-  // pass 1: class ids of all of this wave's chunks (loads in flight together)
-  uint32_t cls[kPer];
+  uint2* list = (uint2*)(slds + SL.list);
+  int wb = lo + wave * kStepIds;
+  Ids8 ids = {{0, 0, 0, 0}};
+  if (wb < hi) ids = load_ids(wb + lane * 8);
+  if (tid == 0) open_s = 0;
+  dma_wait();
+  __syncthreads();
+  for (; wb < hi; wb += kStreamWaves * kStepIds) {
+    const Ids8 cur = ids;
+    if (wb + kStreamWaves * kStepIds < hi) ids = load_ids(wb + kStreamWaves * kStepIds + lane * 8);
+    uint32_t bits = 0, open = 0, cib = 0;
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int c = c_lo + wave + j * kStreamWaves;
-    const int id = c * 64 + lane;
-    cls[j] = (c < c_hi && id < tb.V) ? (uint32_t)cm[id] : 0u;
-  }
-  // pass 2: codes; for a class the lexicon decides, its shortcut byte, the
-  // token's first two bytes and its token-flag summary; for a token the class
-  // leaves undecided, its spelling (needed below if the shortcut leaves the
-  // token to the residue); again all loads in flight together
-  uint32_t code[kPer], sc[kPer], hd[kPer], tf[kPer], su[kPer];
-  bool cib[kPer];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int c = c_lo + wave + j * kStreamWaves;
-    const int id = c * 64 + lane;
-    code[j] = c < c_hi ? (vg[cls[j] >> 4] >> ((cls[j] & 15u) * 2u)) & 3u : kVerdictReject;
-    const bool lexq = code[j] == kVerdictLexicon && id < tb.V;
-    sc[j] = lexq ? vrule[cls[j]] : 0u;
-    hd[j] = lexq ? tb.id_head[id] : 0u;
-    tf[j] = lexq ? tsum[id] : 0u;
-    su[j] = code[j] >= kVerdictWalk && id < tb.V ? tb.spell_of_id[id] : 0xFFFFFFFFu;
-    cib[j] = cdst && c < c_hi && id < tb.V ? ci_class(crow[cls[j]].x) : false;
-  }
-  // pass 2b: a pending-lexeme question on a lexeme that holds the token's
-  // second byte, after a first byte that continues the lexeme: the second
-  // byte's bit in the row's table (0 when it cannot stop the question here)
-  const uint32_t* cont2 = (const uint32_t*)(rw + RL.cont2);
-  uint32_t c2[kPer];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const uint32_t fb = hd[j] & 0xFFu, sb = (hd[j] >> 8) & 0xFFu;
-    const bool ask = code[j] == kVerdictLexicon && (sc[j] & kNoValid) && ((sc[j] >> 2) & 3u) == 0u &&
-                     ((sc[j] >> 4) & 1u) && (hd[j] & 0x10000u) && ((cont[fb >> 5] >> (fb & 31u)) & 1u);
-    c2[j] = ask ? ~(cont2[fb * 8u + (sb >> 5)] >> (sb & 31u)) & 1u : 0u;
-  }
-  // pass 3: shortcut verdicts, mask words, residue ids
-  uint32_t resu[kPer];  // this lane's residue spellings (or ~0)
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int c = c_lo + wave + j * kStreamWaves;
-    const int id = c * 64 + lane;
-    resu[j] = 0xFFFFFFFFu;
-    if (c >= c_hi) continue;  // uniform across the wave
-    uint32_t cd = code[j];
-    if (cd == kVerdictLexicon && (sc[j] & kNoValid)) {
-      const uint32_t kind = (sc[j] >> 2) & 3u, fb = hd[j] & 0xFFu;
-      const bool no = kind == 0 ? !((cont[fb >> 5] >> (fb & 31u)) & 1u) || c2[j] != 0u
-                                : ((tf[j] >> (2 * ((sc[j] >> 4) & 1u) + (kind == 2 ? 1u : 0u))) & 1u) == 0u;
-      if (no) cd = (sc[j] >> 5) & 3u;
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t cd = codes[(cur.w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu];
+      bits |= ((cd & 3u) == kVerdictAllow ? 1u : 0u) << j;
+      cib |= ((cd & 7u) == (kVerdictAllow | kCodeCi) ? 1u : 0u) << j;
+      open |= ((cd >> 1) & 1u) << j;
     }
-    const uint64_t al = __ballot(cd == kVerdictAllow || id == eos);
-    uint64_t cw = 0;
-    if (ciw) cw = (uint64_t)ciw[2 * c] | (2 * c + 1 < tb.W ? (uint64_t)ciw[2 * c + 1] << 32 : 0ull);
-    any = any || (al | cw) != 0;
-    if (lane < 2 && 2 * c + lane < tb.W) mrow[2 * c + lane] = (uint32_t)((al | cw) >> (32 * lane));
-    if (cdst) {  // uniform: the claimed entry's words (the end-of-sequence bit is never cached)
-      const uint64_t cb = __ballot(cib[j] && cd == kVerdictAllow && id < tb.V && id != tb.eos_id);
-      if (lane < 2 && 2 * c + lane < tb.W) cdst[2 * c + lane] = (uint32_t)(cb >> (32 * lane));
-    }
-    if (cd >= kVerdictWalk && id < tb.V) resu[j] = su[j];
-    code[j] = cd;
-  }
-  // mark the residue spellings in the row's bitmaps (lexicon or byte walk),
-  // last, so no load above waits behind these atomics
-  const uint32_t nsub = ((uint32_t)tb.U + 63u) / 64u;
+    if ((uint32_t)(eos - (wb + lane * 8)) < 8u) bits |= 1u << (eos - (wb + lane * 8));
+    ((uint8_t*)mbits[wave])[lane] = (uint8_t)bits;
+    ((uint8_t*)obits[wave])[lane] = 0;
+    if (cdst) ((uint8_t*)cbits[wave])[lane] = (uint8_t)cib;
+    int n = 0;  // open ids of the step (uniform)
 #pragma unroll
-  for (int k2 = 0; k2 < kPer; ++k2)
-    if (resu[k2] != 0xFFFFFFFFu) {
-      const uint32_t u = resu[k2];
-      atomicOr(rbits + (code[k2] == kVerdictWalk ? nsub : 0u) + (u >> 6), 1ull << (u & 63u));
+    for (int j = 0; j < 8; ++j) {
+      const bool o = (open >> j) & 1u;
+      const uint64_t bal = __ballot(o);
+      if (o)
+        queue[n + lane_rank(bal)] = ((cur.w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu) << 16 | (uint32_t)(lane * 8 + j);
+      n += __popcll(bal);
     }
-  if (lane == 0 && any) hdr->nonempty = 1u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int left = 0;  // of them, left to the residue (uniform)
+    for (int i0 = 0; i0 < n; i0 += 64) {
+      const bool in = i0 + lane < n;
+      const uint32_t e = in ? queue[i0 + lane] : 0u;
+      const uint32_t cls = e >> 16, lid = e & 0xFFFFu;
+      const int id = wb + (int)lid;
+      const uint32_t rule = in ? (uint32_t)codes[cls] : 0u;
+      uint32_t cd = rule & 3u;
+      if (cd == kVerdictLexicon && (rule & kNoValid)) {
+        const uint32_t kind = (rule >> 2) & 3u;
+        bool no;
+        if (kind == 0) {  // on the pending bytes: the token's first byte, then its second
+          const uint32_t hd = tb.id_head[id];
+          const uint32_t fb = hd & 0xFFu, sb = (hd >> 8) & 0xFFu;
+          uint32_t cw = 0;
+#pragma unroll
+          for (int w = 0; w < 8; ++w)
+            if (w == (int)(fb >> 5)) cw = cont[w];
+          no = !((cw >> (fb & 31u)) & 1u);
+          if (!no && ((rule >> 4) & 1u) && (hd & 0x10000u)) no = !((cont2[fb * 8u + (sb >> 5)] >> (sb & 31u)) & 1u);
+        } else {
+          const uint32_t o = (rule >> 4) & 1u;
+          no = (((uint32_t)tsum[id] >> (2u * o + (kind == 2u ? 1u : 0u))) & 1u) == 0u;
+          // a trailing question is the last one: the token's prefix flags settle it
+          if (!no && kind == 1u) cd = (tok[id] >> (16u * o)) & cats[cls] & 0xFFu ? kVerdictAllow : kVerdictReject;
+        }
+        if (no) cd = (rule >> 5) & 3u;
+      }
+      if (cd == kVerdictAllow) {
+        atomicOr(&mbits[wave][lid >> 5], 1u << (lid & 31u));
+        if (cdst && ci_class(tb.crec[cls_base + cls].x)) atomicOr(&cbits[wave][lid >> 5], 1u << (lid & 31u));
+      }
+      const uint64_t bal = __ballot(cd >= kVerdictWalk);
+      if (bal) {  // uniform
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&open_s, __popcll(bal));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (cd >= kVerdictWalk) {
+          atomicOr(&obits[wave][lid >> 5], 1u << (lid & 31u));
+          const int at = base + lane_rank(bal);
+          if (at < kOpenLocal) list[at] = make_uint2((uint32_t)id, cls | (rule & 3u) << 16);
+        }
+        left += __popcll(bal);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int wd = (wb >> 5) + lane;
+    if (lane < kStepIds / 32) {
+      if (wd < tb.W) {
+        uint32_t v = mbits[wave][lane];
+        if (ciw) v |= ciw[wd];
+        any = any || v != 0u;
+        mrow[wd] = v;
+        if (cdst) cdst[wd] = cbits[wave][lane];
+      }
+      if (left) ((uint32_t*)(rw + RL.open))[wd] = obits[wave][lane];
+    }
+    if (lane == 0) ((uint16_t*)(rw + RL.n_open))[wb / kStepIds] = (uint16_t)left;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  if (__any(any) && lane == 0) hdr->nonempty = 1u;
+  __syncthreads();
+  const int n = open_s;
+  if (n == 0) return;  // uniform
+  if (tid == 0) {  // this workgroup's place in the row's list
+    uint32_t* cnt = open_counts(ws, rbytes, B) + row;
+    base_s = (int)(atomicAdd(cnt, (uint32_t)n) & (kListFull - 1u));
+    if (n > kOpenLocal) atomicOr(cnt, kListFull);
+  }
+  __syncthreads();
+  uint2* out = (uint2*)(rw + RL.list);
+  for (int i = tid; i < min(n, kOpenLocal); i += kStreamThreads)
+    if (base_s + i < open_list_cap(tb.V)) out[base_s + i] = list[i];
 }
 
 // ----------------------------------------------------------------- residue
@@ -2122,158 +1750,59 @@ __device__ inline int wave_grab(int* ctr) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
+// The live sets, allowed sets and accept lists of a verdict.
+inline uint32_t verdict_bytes(const Tables& tb) {
+  return (uint32_t)tb.S * 32u + (uint32_t)tb.T * 32u + pad16((uint32_t)tb.T * 4u) + pad16((uint32_t)(tb.S + 1) * 4u) +
+         pad16((uint32_t)tb.n_acc);
+}
+
+// The lexer's and the parser's tables (LR with GOTO as the hash) and two bytes
+// per lexer state: what the supported grammars are bounded by.
+inline uint32_t table_bytes(const Tables& tb) {
+  return pad16((uint32_t)(tb.S * tb.C * 2)) + pad16((uint32_t)(tb.S + 1) * 4u) + pad16((uint32_t)tb.n_acc) +
+         (uint32_t)tb.S * 32u + 2u * pad16((uint32_t)tb.S) + parse_lds(tb, 0, false).total;
+}
+
 struct ResLds {  // byte offsets into dynamic LDS
-  uint32_t dfa, bcls, tinfo, I, acc_off, acc_list, parse, live, lanes, umask, upre, rows, total;
-  uint32_t block;  // bytes per resident row: header, trailing-flag tables, stack window
-  int group;       // rows per group
-  ParseLds pl;
+  uint32_t block, bcls, tinfo, live, dfa, areas, qid, qcls, slow, total;
+  int full;  // the chains' tables, the DFA and the live sets are in LDS too
+  LrLds lr;
 };
 
-__host__ __device__ inline ResLds res_lds_with(const Tables& tb, int mw, int B, bool dense) {
-  (void)mw;
+__host__ __device__ inline ResLds res_lds(const Tables& tb) {
   ResLds w;
   uint32_t o = 0;
-  w.dfa = o;
-  o += pad16((uint32_t)(tb.S * tb.C * 2));
+  w.block = o;
+  o += (uint32_t)row_layout(tb).block;
   w.bcls = o;
   o += 256;
   w.tinfo = o;
-  o += 256 * 4;
-  w.I = o;
-  o += 32;
-  w.acc_off = o;
-  o += pad16((uint32_t)(tb.S + 1) * 4);
-  w.acc_list = o;
-  o += pad16((uint32_t)tb.n_acc);
-  w.parse = o;
-  w.pl = parse_lds(tb, o, dense);
-  o += w.pl.total;
-  w.live = o;  // the live sets as in global memory, 8 words per state
-  o += pad16((uint32_t)(tb.S * 32));
-  w.lanes = o;  // stack areas of the first kLaneSlots lanes of each wave
-  o += (kWalkThreads / 64) * kLaneSlots * kFastLane * 2;
-  w.umask = o;  // per work item: its residue bitmap word
-  o += kMaxItems * 8;
-  w.upre = o;   // prefix counts of residue spellings over the items
-  o += (kMaxItems + 4) * 4;
-  const uint32_t fixed = o + 64;
-  w.block = (uint32_t)row_layout(tb).block;
-  int g = kRowGroup < B ? kRowGroup : B;
-  while (g > 1 && fixed + w.block * (uint32_t)g > kWalkLdsMax) --g;
-  w.group = g;
-  w.rows = o;
-  o += w.block * (uint32_t)g;
+  o += pad16((uint32_t)tb.T * 4u);
+  w.areas = o;
+  o += kResWaves * kLanesMax * kFastLane * 2;
+  w.qid = o;
+  o += kQueue * 4;
+  w.qcls = o;
+  o += kQueue * 2;
+  w.slow = o;
+  o += kQueue * 4;
+  const uint32_t live = (uint32_t)tb.S * 32u;  // as in global memory, 8 words per state
+  const uint32_t dfa = pad16((uint32_t)(tb.S * tb.C * 2));
+  w.lr = lr_lds(tb, o);
+  w.full = o + w.lr.total + live + dfa <= kLdsMax - kLdsStatic ? 1 : 0;
+  w.live = w.dfa = 0;
+  if (w.full) {
+    o += w.lr.total;
+    w.live = o;
+    o += live;
+    w.dfa = o;
+    o += dfa;
+  }
   w.total = o;
   return w;
 }
-
-// The residue kernel's LDS: GOTO as the dense table when that still leaves
-// room for the whole row group, else as the hash.
-__host__ __device__ inline ResLds res_lds(const Tables& tb, int mw, int B) {
-  const ResLds d = res_lds_with(tb, mw, B, true);
-  if (d.group == (kRowGroup < B ? kRowGroup : B) && d.total + 64 <= kWalkLdsMax) return d;
-  return res_lds_with(tb, mw, B, false);
-}
-
-// Everything the residue lanes share about the grammar (pointers into LDS).
-template <int MW>
-struct WalkShared {
-  const Tables* tb;
-  ParseTabs<true> pt;
-  DfaView step;
-  const uint32_t* tinfo;
-  const uint32_t* I;
-  const uint32_t* live;
-  const uint32_t* acc_off;
-  const uint8_t* acc_list;
-  const uint16_t* pool;
-};
-
-// Verdict of one spelling left to the byte walk: byte 0 (continuing the
-// pending lexeme, or ending it with the prologue's winner and starting a new
-// one), then the byte-by-byte walk of the rest with emissions, overlay shifts
-// and lexicon checks.  A lane whose stack area is too small hands its
-// spelling to the slow path.  1 allowed, 0 rejected or handed over.
-template <int MW>
-__device__ __forceinline__ int residue_lane(const WalkShared<MW>& sh, const RowHeader& h, const uint8_t* rowblk,
-                                            uint8_t* rw, const RowLayout& RL, uint32_t u, const uint4& rk,
-                                            const uint4& tl, mptr<true, uint16_t> lane_area) {
-  const Tables& tb = *sh.tb;
-  const uint8_t* clsA = rowblk + sizeof(RowHeader);
-  const uint8_t* clsW = clsA + pad16((uint32_t)tb.S);
-  const uint32_t n = rk.w & 0xFFu;
-  const uint64_t hb = (uint64_t)rk.x | (uint64_t)rk.y << 32;
-  const uint32_t b0 = (uint32_t)(hb & 0xFF);
-  const uint32_t c0 = sh.step.cls(b0);
-  Slot sl;
-  sl.fbase = h.slot[0];
-  sl.hbase = h.slot[1];
-  sl.hmask = h.slot[2];
-  sl.restricted = h.slot[3];
-  sl.nodes = h.slot[4];
-  sl.pbase = h.slot[5];
-  sl.pmask = h.slot[6];
-  sl.sbase = h.slot[7];
-  sl.smask = h.slot[8];
-  RowCtx<true> rc;
-  rc.tb = &tb;
-  rc.pt = sh.pt;
-  rc.bs = BaseStack<true>{sh.pool + h.stk_off, in_mem<true>((const uint16_t*)(rowblk + RL.win)), h.stk_depth,
-                          h.stk_depth > (uint32_t)kWalkWin ? h.stk_depth - kWalkWin : 0u};
-  rc.sl = sl;
-  rc.tv = TermView{sh.tinfo, sh.I, h.R, sh.live, 8};
-  rc.acc_off = sh.acc_off;
-  rc.acc_list = sh.acc_list;
-  rc.a2 = (const uint32_t*)(rw + RL.a2);
-  rc.a2_stride = 8;
-  rc.post = (const Post*)(rw + RL.post);
-  rc.clsA = clsA;
-  rc.clsW = clsW;
-  rc.winner = h.wkind == 2 ? h.winner : -1;
-  Lane<MW> ln;
-  ln.k = 0;
-  ln.m = 0;
-  LexState lx;
-  int q1 = sh.step.next((int)h.q, c0);
-  const uint8_t* ct = clsA;
-  bool dead = false;
-  if (q1 != kDead) {  // byte 0 extends the pending lexeme
-    ln.mode = 0;
-    ln.t1 = -1;
-    lx.len = h.rem_len + 1;
-    lx.w = lx.len <= 8 ? (((uint64_t)h.rem_lo | (uint64_t)h.rem_hi << 32) | (uint64_t)b0 << (8 * h.rem_len)) : 0ull;
-  } else {  // byte 0 ends it: its winner, then a new lexeme
-    dead = h.wkind == 0;
-    q1 = sh.step.next(kStart, c0);
-    dead = dead || q1 == kDead;
-    ln.mode = h.wkind == 2 ? 1 : 0;
-    ln.t1 = h.wkind == 2 ? h.winner : -1;
-    if (ln.mode == 1) ln.ph = reinterpret_cast<const uint4*>(rc.post)[2 * ln.t1];
-    ct = h.wkind == 2 ? clsW : clsA;
-    lx.len = 1;
-    lx.w = b0;
-  }
-#pragma unroll
-  for (int w = 0; w < MW; ++w) ln.acur[w] = ln.mode == 1 ? h.Aw[w] : h.A[w];
-  const uint32_t f0 = dead ? 0u : (uint32_t)ct[q1];
-  if (f0 == 0) return 0;  // byte 0 leaves no allowed or ignored terminal completable
-  lx.need = sl.restricted != 0 && (f0 & 2u) ? 1u : 0u;
-  lx.node = lx.need && lx.len > 8 ? lex_child(tb, sl, h.lexnode, b0) : kNoLex;
-  SpellBytes byte_at;
-  byte_at.win = hb >> 8;
-  byte_at.lo0 = (uint64_t)tl.x | (uint64_t)tl.y << 32;
-  byte_at.hi = (uint64_t)tl.z | (uint64_t)tl.w << 32;
-  byte_at.ovf = tb.spell_tail + (rk.w >> 8);
-  int ok = walk_bytes<true, MW>(rc, ln, q1, lx, 1u, n, byte_at, sh.step, lane_area, kFastLane, f0);
-  if (ok < 0) {  // the lane's stack area is too small: hand over
-    RowHeader* gh = (RowHeader*)rw;
-    const uint32_t slot = atomicAdd(&gh->slow_count, 1u);
-    if (slot < (uint32_t)kSlowCap) ((uint32_t*)(rw + RL.slow))[slot] = u;
-    else atomicOr(&gh->wstat, GRID_ROW_OVERFLOW);
-    ok = 0;
-  }
-  return ok;
-}
+static_assert(kSlowWaves >= 1 && kSlowWaves * kSlowLane <= kResWaves * kLanesMax * kFastLane,
+              "the slow walks' areas fit where the fast ones were");
 
 // Bytes [s, s + 8) of the 24-byte window b0 b1 b2 (zero beyond it).
 __device__ __forceinline__ uint64_t window8(uint64_t b0, uint64_t b1, uint64_t b2, uint32_t s) {
@@ -2296,12 +1825,9 @@ struct LexLane {
   Slot sl;
   uint64_t b0, b1, b2;  // token bytes 0..23, zero padded
   uint32_t n;           // token length
-  uint32_t ends;        // lexeme ends (kClassMore: more than recorded)
-  uint32_t pos;         // byte indices of ends 0, 1, 2 (8 bits each)
   uint64_t rem;         // pending bytes (first 8)
   uint32_t rem_len, lexnode;
   uint32_t tf;          // token-flag entry
-  __device__ __forceinline__ uint32_t end_at(uint32_t i) const { return (pos >> (8 * i)) & 0xFFu; }
   __device__ __forceinline__ uint32_t span(uint32_t o, uint32_t e, bool pending) const {
     if (e > 24) return kLexOut;
     if (pending && rem_len > 0) {
@@ -2322,361 +1848,552 @@ struct LexLane {
     return lex_flags_bytes(*tb, sl, window8(b0, b1, b2, o), window8(b0, b1, b2, o + 8), window8(b0, b1, b2, o + 16),
                            e - o);
   }
-  __device__ __forceinline__ uint32_t word(uint32_t i) const {
-    const int o = covered_start(pos, i, rem_len == 0);
-    if (o >= 0) return ((tf >> (16 * o + 8)) & 0xFFu) << 8;
-    return i == 0 ? span(0, end_at(0), true) : span(end_at(i - 1), end_at(i), false);
-  }
-  __device__ __forceinline__ uint32_t trail() const {
-    if (ends > (uint32_t)kClassEnds) return kLexOut;
-    const int o = covered_start(pos, ends, rem_len == 0);
-    if (o >= 0) return (tf >> (16 * o)) & 0xFFu;
-    return ends == 0 ? span(0, n, true) : span(end_at(ends - 1), n, false);
-  }
 };
 
-// Verdict of one spelling of the residue bitmaps: for a spelling of the
-// lexicon bitmap, its class cls (the class map's entry at its first id) is
-// taken again with its own lexemes' lexicon flags (token-flag table, prefix and
-// stride tables); the byte walk decides the rest.  1 allowed, 0 rejected or
-// handed over.
-template <int MW>
-__device__ __forceinline__ int residue_token(const WalkShared<MW>& sh, const RowHeader& h, const uint8_t* rowblk,
-                                             uint8_t* rw, const RowLayout& RL, uint32_t u, const uint4& rk,
-                                             bool lexicon, uint32_t cls, mptr<true, uint16_t> lane_area) {
-  const Tables& tb = *sh.tb;
-  const uint32_t id0 = rk.z & 0x7FFFFFFFu;
-  const uint32_t n = rk.w & 0xFFu;
-  const uint4 tl = tb.spell_tail[u];
-  if (lexicon) {
-    const uint4 rec = tb.crec[h.cls_base + cls];
-    LexLane lx;
-    lx.tb = &tb;
-    lx.sl = slot_of(h.slot);
-    lx.n = n;
-    lx.b0 = (uint64_t)rk.x | (uint64_t)rk.y << 32;
-    lx.b1 = n > 8 ? (uint64_t)tl.x | (uint64_t)tl.y << 32 : 0ull;
-    lx.b2 = n > 8 ? (uint64_t)tl.z | (uint64_t)tl.w << 32 : 0ull;
-    lx.ends = rec.x & kClassEndsMask;
-    lx.pos = rec.w;
-    lx.rem = (uint64_t)h.rem_lo | (uint64_t)h.rem_hi << 32;
-    lx.rem_len = h.rem_len;
-    lx.lexnode = h.lexnode;
-    lx.tf = tb.lex_token[(size_t)h.slot_id * tb.V + id0];
-    const uint32_t v = class_verdict<MW, LexLane, false>(h, sh.I, sh.live, 8, sh.tinfo, sh.acc_off, sh.acc_list,
-                                                         (const uint32_t*)(rw + RL.a2), 8, rec, lx);
-    if (v == kVerdictAllow) return 1;
-    if (v == kVerdictReject) return 0;
-  }
-  return residue_lane<MW>(sh, h, rowblk, rw, RL, u, rk, tl, lane_area);
-}
+// What a byte walk reads besides the row's sets.
+template <int MW, bool L>
+struct WalkView {
+  const Tables* tb;
+  RowView<MW> rv;
+  LrTabs<L> lt;
+  DfaView step;
+  const uint16_t* pool;       // the row's stack
+  mptr<true, const uint16_t> win;
+  uint32_t lo, depth;
+  const uint4* post;          // stacks after one shift, two 16-byte halves each
+  uint32_t q;                 // the row's scan state
+};
 
-// Sets the mask bit of every id that spells u (its alias ids).
-__device__ inline void allow_spelling(const Tables& tb, uint32_t* mrow, uint32_t u, const uint4& rk) {
-  if (!(rk.z >> 31)) {
-    const uint32_t id = rk.z;
-    atomicOr(mrow + (id >> 5), 1u << (id & 31u));
-    return;
-  }
-  for (uint32_t a = tb.alias_off[u]; a < tb.alias_off[u + 1]; ++a) {
-    const uint32_t id = (uint32_t)tb.alias_ids[a];
-    atomicOr(mrow + (id >> 5), 1u << (id & 31u));
-  }
-}
-
-// The rank-th set bit of m (rank < popcount(m)).
-__device__ inline int nth_set_bit(uint64_t m, int rank) {
-  int pos = 0;
+// A Post record's two halves unpacked onto a lane's stack area: false if it is
+// unusable (not a stack, or more entries than the area holds).
+__device__ __forceinline__ bool load_post(const uint4& h1, const uint4& h2, uint32_t depth, uint32_t cap, uint32_t& k,
+                                          uint32_t& m, mptr<true, uint16_t> ov) {
+  const uint32_t pk = h1.x & 0xFFFFu, pm = (h1.x >> 16) & 0xFFu, pok = h1.x >> 24;
+  if (!pok || pk == 0 || pk > depth || pm > (uint32_t)kPostCap || pm > cap) return false;
+  k = pk;
+  m = pm;
+  const uint32_t w[7] = {h1.y, h1.z, h1.w, h2.x, h2.y, h2.z, h2.w};
 #pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) {
-    const uint64_t low = m & ((1ull << w) - 1ull);
-    const int c = __popcll(low);
-    if (rank >= c) {
-      rank -= c;
-      m >>= w;
-      pos += w;
+  for (uint32_t j = 0; j < 14; ++j)
+    if (j < m) ov[j] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+  return true;
+}
+
+// Verdicts of a walk besides reject and allow.
+constexpr uint32_t kWalkTrail = 4;  // some terminal of X must be shiftable from the lane's stack
+constexpr uint32_t kWalkFull = 5;   // the stack area is too small
+
+// One token judged to its end: lexemes as in class_verdict, from the class
+// record while it has them, else by running the DFA over the bytes; past the
+// first shift the parser's stack is the lane's own (base[0, k) and m overlay
+// entries in its area of cap), a lexeme's candidates are tried in priority order
+// by their reduce chains, and the first that shifts is committed -- no allowed
+// set is needed until the trailing lexeme, whose terminals X are left to the
+// whole wave (see residue_kernel).
+template <int MW, bool L>
+__device__ __forceinline__ uint32_t walk_token(const WalkView<MW, L>& wv, uint4 rec, const LexLane& lex, uint32_t chunk,
+                                               mptr<true, uint16_t> ov, uint32_t cap, uint32_t& k, uint32_t& m,
+                                               uint32_t (&X)[MW]) {
+  const Tables& tb = *wv.tb;
+  const RowView<MW>& rv = wv.rv;
+  const uint32_t w0 = rec.x, ends = w0 & kClassEndsMask, n_rec = min(ends, (uint32_t)kClassEnds);
+  const uint32_t* set = rv.usets;  // the set in force, while it is kept
+  int sel = -1;                    // -1 from sigma, t >= 0 after shifting t, -4 the lane's own stack
+  bool scan = (w0 & kClassWalk) != 0;
+  uint32_t o = 0, si = 0, sq = wv.q, q = 0;  // the current lexeme's first byte; the scan's position and state
+  bool pending = true;                       // the lexeme holds the pending bytes
+  // byte i of the token
+  auto byte_at = [&](uint32_t i) -> uint32_t {
+    if (i >= 24u) return reinterpret_cast<const uint8_t*>(tb.spell_tail + chunk)[i - 24u];
+    const uint64_t b = (lex.b0 & (0ull - (uint64_t)(i < 8u))) | (lex.b1 & (0ull - (uint64_t)(i >= 8u && i < 16u))) |
+                       (lex.b2 & (0ull - (uint64_t)(i >= 16u)));
+    return (uint32_t)(b >> (8u * (i & 7u))) & 0xFFu;
+  };
+  // lexicon flags of bytes [o, e) (with the pending bytes before them)
+  auto flags = [&](uint32_t e) -> uint32_t {
+    const bool cont = pending && lex.rem_len > 0;
+    if (!cont && o <= 1u) return (lex.tf >> (16u * o)) & 0xFFFFu;  // the token-flag table
+    const uint32_t f = lex.span(o, e, pending);
+    if (f != kLexOut) return f;
+    // byte by byte through the lexicon trie
+    uint32_t node = cont ? lex.lexnode : 0u;
+    for (uint32_t i = o; i < e && node != kNoLex; ++i) node = lex_child(tb, lex.sl, node, byte_at(i));
+    return lex_flags_of(tb, lex.sl, node);
+  };
+  for (uint32_t i = 0;; ++i) {
+    uint32_t e;
+    if (!scan && i == n_rec) {
+      if (ends <= (uint32_t)kClassEnds) {
+        q = rec.y & 0xFFFFu;
+        o = lexeme_start(rec, tb.prog, ends, true);
+        pending = holds_pending(rec, ends);
+        break;
+      }
+      scan = true;
+      si = o;
+      sq = kStart;
+    }
+    if (scan) {
+      while (si < lex.n) {
+        const int nq = wv.step.next((int)sq, wv.step.cls(byte_at(si)));
+        if (nq == kDead) break;
+        sq = (uint32_t)nq;
+        ++si;
+      }
+      q = sq;
+      e = si;
+      if (si == lex.n) break;
+      if (si == o && !(pending && lex.rem_len > 0)) return kVerdictReject;  // a byte that starts no lexeme
     } else {
-      m = low;
+      q = i == 0 ? rec.y >> 16 : (i == 1 ? rec.z & 0xFFFFu : rec.z >> 16);
+      o = lexeme_start(rec, tb.prog, i, false);
+      e = (rec.w >> (8u * i)) & 0xFFu;
+      pending = holds_pending(rec, i);
+    }
+    // the lexeme's winner
+    int t = -1;
+    uint32_t a = 0, n = 0, s = 0;
+    bool moved = false;
+    if (!scan && i == 0 && (w0 & kClassP0)) {
+      if (rv.wkind == 0) return kVerdictReject;
+      t = rv.winner;
+    } else {
+      if (sel != -4) {
+        t = rv.winner_in(q, set, [&]() { return flags(e); });
+      } else {
+        const uint32_t acc = rv.acc[q];
+        uint32_t wf = kLexOpen;
+        for (uint32_t j = 0; j < acc >> 24; ++j) {
+          const int c = rv.accept(q, acc, j);
+          if (set_has<MW>(rv.R, c)) {
+            if (wf == kLexOpen) wf = flags(e);
+            if (!((wf >> (8 + ((rv.tinfo[c] >> 8) & 7u))) & 1u)) continue;
+          }
+          if (!set_has<MW>(rv.I, c)) {
+            n = k + m - 1u;
+            const ChainStack st{wv.pool, wv.win, wv.lo, k, ov, m};
+            s = st.at(n);
+            a = lr_chain<L>(wv.lt, st, (uint32_t)c, n, s, moved);
+            if (!a) continue;
+          }
+          t = c;
+          break;
+        }
+      }
+      if (t < 0) return kVerdictReject;
+    }
+    o = e;
+    pending = false;
+    if (scan) sq = kStart;
+    if (set_has<MW>(rv.I, t)) continue;
+    // its shift
+    if (sel == -1) {
+      sel = t;
+      set = rv.after(t);
+      continue;
+    }
+    if (sel != -4) {  // from the kept stack after sel: t is in its allowed set, its chain is still to run
+      if (!load_post(wv.post[2 * sel], wv.post[2 * sel + 1], wv.depth, cap, k, m, ov)) return kWalkFull;
+      n = k + m - 1u;
+      const ChainStack st{wv.pool, wv.win, wv.lo, k, ov, m};
+      s = st.at(n);
+      a = lr_chain<L>(wv.lt, st, (uint32_t)t, n, s, moved);
+      if (!a) return kVerdictReject;
+      sel = -4;
+    }
+    if (!lr_commit(tb, a, (uint32_t)t, n, s, moved, k, m, ov, cap)) return kWalkFull;
+  }
+  // the trailing lexeme, in state q
+  if (sel != -4) return trail_verdict<MW>(rv, set, true, q, [&](uint32_t) { return flags(lex.n); });
+  const uint32_t* lv = rv.live + (size_t)q * 8;
+  uint32_t any = 0, res = 0, ign = 0;
+#pragma unroll
+  for (int w = 0; w < MW; ++w) {
+    X[w] = lv[w];
+    ign |= X[w] & rv.I[w] & ~rv.R[w];
+    res |= X[w] & rv.R[w];
+  }
+  if (ign) return kVerdictAllow;
+  if (res) {  // restricted terminals count where the lexeme prefixes a word of their category
+    const uint32_t pf = flags(lex.n);
+    ign = 0;
+#pragma unroll
+    for (int w = 0; w < MW; ++w)
+      for (uint32_t r = X[w] & rv.R[w]; r; r &= r - 1)
+        if (!((pf >> ((rv.tinfo[w * 32 + __ffs(r) - 1] >> 8) & 7u)) & 1u)) X[w] &= ~(r & (0u - r));
+#pragma unroll
+    for (int w = 0; w < MW; ++w) ign |= X[w] & rv.I[w];
+    if (ign) return kVerdictAllow;
+  }
+#pragma unroll
+  for (int w = 0; w < MW; ++w) {
+    X[w] &= ~rv.I[w];
+    any |= X[w];
+  }
+  return any ? kWalkTrail : kVerdictReject;
+}
+
+// Sum of v over the threads below this one (workgroup of kResThreads), and the
+// total; sums holds a word per wave.  Every thread calls it.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* sums, uint32_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t x = __shfl_up(incl, d);
+    if (lane >= d) incl += x;
+  }
+  __syncthreads();  // the previous scan's sums are read
+  if (lane == 63) sums[wave] = incl;
+  __syncthreads();
+  uint32_t below = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kResWaves; ++w) {
+    if (w < wave) below += sums[w];
+    all += sums[w];
+  }
+  *total = all;
+  return below + incl - v;
+}
+
+// The row and the chunk in it that hold chunk c of the batch when every row's
+// open ids are dealt K at a time; row -1 past the last.  By one wave.
+// first: this lane's counts of the first kCountRegs * 64 rows.
+__device__ __forceinline__ int find_chunk(const uint32_t* counts, const uint32_t (&first)[kCountRegs], int B, uint32_t K,
+                                          uint32_t c, uint32_t* in_row) {
+  const int lane = threadIdx.x & 63;
+  uint32_t run = 0;
+  auto in_rows = [&](int r0, uint32_t n) -> int {  // rows r0.., n open ids in this lane's
+    const uint32_t nc = (n + K - 1u) / K;
+    uint32_t incl = nc;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t x = __shfl_up(incl, d);
+      if (lane >= d) incl += x;
+    }
+    const uint64_t at = __ballot(c < run + incl);
+    if (at) {  // uniform
+      const int l = __ffsll((unsigned long long)at) - 1;
+      *in_row = c - run - (__builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(nc, l));
+      return r0 + l;
+    }
+    run += __builtin_amdgcn_readlane(incl, 63);
+    return -1;
+  };
+#pragma unroll
+  for (int j = 0; j < kCountRegs; ++j) {
+    if (j * 64 >= B) return -1;
+    const int r = in_rows(j * 64, first[j]);
+    if (r >= 0) return r;
+  }
+  for (int r0 = kCountRegs * 64; r0 < B; r0 += 64) {
+    const int r = in_rows(r0, r0 + lane < B ? counts[r0 + lane] & (kListFull - 1u) : 0u);
+    if (r >= 0) return r;
+  }
+  return -1;
+}
+
+// The ids the stream left open, dealt evenly to the workgroups: a chunk is K
+// open ids of one row, K set by the batch's total, so a row with many costs no
+// workgroup more than a row with few.  The waves of the workgroup take a few ids
+// at a time, one per lane (a wave's time is that of its slowest lane), and judge
+// them to the end: the first shift from the sets and stacks kept for the row, later
+// ones by reduce chains, with the chains' tables and the DFA in LDS.
+// An id whose lane's stack area was too small is judged again at the end with a
+// large one.  Allowed ids are OR-ed into the mask.  The last chunk of a row to
+// end writes the row's status (a row without open ids gets it from one thread).
+// (Per id the work is a chain of dependent reads and branches, some thousand
+// cycles long, so what counts is how few ids a lane takes one after the other
+// and that no wave waits for another in between.)
+template <int MW, bool Full>
+__global__ __launch_bounds__(kResThreads) void residue_kernel(Tables tb, const uint16_t* __restrict__ pool,
+                                                              uint32_t* __restrict__ mask, uint8_t* __restrict__ ws,
+                                                              size_t rbytes, int B, int32_t* __restrict__ status) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ int q_cnt, n_walk, n_lex, s_cnt, group_ctr, slow_ctr, any_s, ovf_s, step_lo, step_hi;
+  __shared__ uint32_t sums[kResWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t* counts = open_counts(ws, rbytes, B);
+  const ResLds WL = res_lds(tb);
+  const RowLayout RL = row_layout(tb);
+  // the batch's open ids, and the chunk size that deals them evenly (every wave
+  // for itself)
+  uint32_t mine = 0, first[kCountRegs];
+#pragma unroll
+  for (int j = 0; j < kCountRegs; ++j) {
+    const int r = j * 64 + lane;
+    first[j] = r < B ? counts[r] & (kListFull - 1u) : 0u;
+  }
+  const bool tables = tid >= kResThreads - kTableThreads;
+  if (tables) {  // what every row needs, on its way while the chunk is found
+    const int tt = tid - (kResThreads - kTableThreads);
+    const StageRegion rg[2] = {{tb.bclass, lds + WL.bcls, 256u},
+                               {(const uint8_t*)tb.term_info, lds + WL.tinfo, (uint32_t)tb.T * 4u}};
+    const uint32_t blk = dma_regions<2>(rg, tt, kTableThreads);
+    if (Full) {
+      const StageRegion rl[2] = {{(const uint8_t*)tb.live, lds + WL.live, (uint32_t)tb.S * 32u},
+                                 {(const uint8_t*)tb.dfa, lds + WL.dfa, (uint32_t)(tb.S * tb.C * 2)}};
+      dma_lr(tb, lds, WL.lr, tt, kTableThreads, dma_regions<2>(rl, tt, kTableThreads, blk));
     }
   }
-  return pos;
-}
-
-// Persistent, one workgroup per compute unit.  For each group of rows that
-// fits, a work item is one row against 64 consecutive spellings (one word of
-// one of the row's residue bitmaps, byte-walk items first since they take
-// longest); workgroup b takes items b, b + gridDim.x, ...
-// and reads their words, then the set bits are packed into waves in
-// spelling order, kWalkChunk byte-walk or kLexChunk lexicon spellings to a
-// wave -- lexicographic neighbours walk alike, and a wave's time is the sum
-// over its emission rounds of its slowest lane, so fewer lanes diverge less.  The grammar tables and the group's row blocks (header,
-// trailing-flag tables, stack window) are staged in LDS only when the
-// workgroup has residue spellings.  Each lane judges one spelling and sets
-// the mask bits of its ids.
-template <int MW>
-__global__ __launch_bounds__(kWalkThreads) void residue_kernel(Tables tb, const uint16_t* __restrict__ pool,
-                                                               uint32_t* __restrict__ mask, uint8_t* __restrict__ ws,
-                                                               size_t rbytes, int B) {
-  extern __shared__ __align__(16) uint8_t lds[];
-  __shared__ int chunk_ctr;
-  __shared__ uint32_t row_allowed[kRowGroup];  // the walk allowed a spelling of the group's row
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const ResLds WL = res_lds(tb, MW, B);
-  const RowLayout RL = row_layout(tb);
-  uint8_t* bcls = lds + WL.bcls;
-  uint32_t* tinfo_s = (uint32_t*)(lds + WL.tinfo);
-  uint32_t* I_s = (uint32_t*)(lds + WL.I);
-  uint32_t* live_s = (uint32_t*)(lds + WL.live);
-  uint64_t* umask_s = (uint64_t*)(lds + WL.umask);
-  uint32_t* upre_s = (uint32_t*)(lds + WL.upre);
-  const uint32_t* acc_off_s = (const uint32_t*)(lds + WL.acc_off);
-  const uint8_t* acc_list_s = lds + WL.acc_list;
-  uint8_t* rows_s = lds + WL.rows;
-  // lanes kLaneSlots and above of a wave never judge a spelling (chunks are smaller)
-  const mptr<true, uint16_t> lane_area =
-      in_mem<true>((uint16_t*)(lds + WL.lanes) + ((tid >> 6) * kLaneSlots + (lane & (kLaneSlots - 1))) * kFastLane);
-  uint8_t* rows = ws + kWsHead;
-  const int nsub = (tb.U + 63) / 64;
-  // the grammar tables go straight to LDS at once (direct global-to-LDS
-  // loads, waited for at the first barrier that follows); the live sets are
-  // staged as in global memory, 8 words per state
-  {
-    const StageRegion rg[10] = {{(const uint8_t*)tb.dfa, lds + WL.dfa, (uint32_t)(tb.S * tb.C * 2)},
-                                {tb.bclass, bcls, 256u},
-                                {(const uint8_t*)tb.acc_off, lds + WL.acc_off, (uint32_t)(tb.S + 1) * 4},
-                                {tb.acc_list, lds + WL.acc_list, (uint32_t)tb.n_acc},
-                                {(const uint8_t*)tb.live, (uint8_t*)live_s, (uint32_t)tb.S * 32u},
-                                {(const uint8_t*)tb.term_info, (uint8_t*)tinfo_s, (uint32_t)tb.T * 4u},
-                                parse_region(tb, lds, WL.pl, 0),
-                                parse_region(tb, lds, WL.pl, 1),
-                                parse_region(tb, lds, WL.pl, 2),
-                                parse_region(tb, lds, WL.pl, 3)};
-    dma_regions<10>(rg, tid, kWalkThreads);
-  }
-  if (tid < 8) I_s[tid] = tb.ign[tid];
-  for (int g0 = 0; g0 < B; g0 += WL.group) {
-    const int gr = min(WL.group, B - g0);
-    const int items = 2 * gr * nsub;  // walk items of the group's rows first, then lexicon items
-    const int mine = items > (int)blockIdx.x ? (items - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x : 0;
-    bool blocks = false;  // the group's row blocks are in LDS
-    if (tid < kRowGroup) row_allowed[tid] = 0u;
-    for (int k0 = 0; k0 < mine; k0 += kMaxItems) {
-      const int n_it = min(kMaxItems, mine - k0);
-      // this thread's item word, loaded before the wait for the table copies
-      static_assert(kMaxItems == kWalkThreads, "one item word per thread");
-      uint64_t uw = 0ull;
-      if (tid < n_it) {
-        const int j = (int)blockIdx.x + (k0 + tid) * (int)gridDim.x;
-        const int lex = j >= gr * nsub ? 1 : 0, jr = j - lex * gr * nsub;
-        const int r = jr / nsub;
-        const uint8_t* rw = rows + (size_t)(g0 + r) * rbytes;
-        const uint32_t v = ((const RowHeader*)rw)->valid;
-        const uint64_t word = ((const uint64_t*)(rw + RL.rbits))[(lex ? 0 : nsub) + jr - r * nsub];
-        uw = v == kRowValid ? word : 0ull;
-      }
-      dma_wait();
-      __syncthreads();  // the previous round is done with umask_s / upre_s; the tables are in LDS
-      if (tid < n_it) umask_s[tid] = uw;
-      if (tid == 0) chunk_ctr = 0;
-      __syncthreads();
-      if (tid < 64) {  // prefix counts of set bits over the items (one wave)
-        const int per = (n_it + 63) / 64;
-        uint32_t sum = 0;
-        for (int i = 0; i < per; ++i) {
-          const int t = lane * per + i;
-          if (t < n_it) sum += (uint32_t)__popcll(umask_s[t]);
-        }
-        uint32_t incl = sum;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const uint32_t x = __shfl_up(incl, d);
-          if (lane >= d) incl += x;
+  for (int j = 0; j < kCountRegs; ++j) mine += first[j];
+  for (int r = kCountRegs * 64 + lane; r < B; r += 64) mine += counts[r] & (kListFull - 1u);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d);
+  const uint32_t all = __builtin_amdgcn_readfirstlane(mine);
+  for (int r = (int)blockIdx.x * kResThreads + tid; r < B; r += (int)gridDim.x * kResThreads) {
+    RowHeader* hr = (RowHeader*)(ws + kWsHead + (size_t)r * rbytes);
+    if (counts[r] == 0u && hr->valid == kRowValid) {  // nothing open: the status is known
+      const int32_t st = hr->pstat | (!hr->nonempty && !hr->eos_ok ? GRID_ROW_EMPTY : 0);
+      if (status) status[r] = st;
+      hr->fstat = st;
+    }
+  }
+  // (a row's last chunk may be short, so up to B chunks more than full ones)
+  const uint32_t room = gridDim.x - min((uint32_t)B, gridDim.x / 2u);
+  const uint32_t per = (all + room - 1) / room;
+  const uint32_t K = min((uint32_t)kChunkMax, max((uint32_t)kChunkMin, (per + 31u) / 32u * 32u));
+  uint32_t in_row = 0;
+  int row = all ? find_chunk(counts, first, B, K, blockIdx.x, &in_row) : -1;
+  if (row < 0) {  // uniform over the workgroup
+    dma_wait();
+    return;
+  }
+  const uint8_t* rowblk = lds + WL.block;
+  const RowHeader& h = *(const RowHeader*)rowblk;
+  WalkView<MW, Full> wv;
+  wv.tb = &tb;
+  wv.lt = lr_tabs<Full>(tb, lds, WL.lr);
+  wv.step = DfaView{Full ? (const uint16_t*)(lds + WL.dfa) : tb.dfa, lds + WL.bcls, tb.C};
+  wv.win = in_mem<true>((const uint16_t*)(rowblk + RL.win));
+  RowView<MW>& rv = wv.rv;
+  rv.live = Full ? (const uint32_t*)(lds + WL.live) : tb.live;
+  rv.tinfo = (const uint32_t*)(lds + WL.tinfo);
+  wv.post = (const uint4*)(rowblk + RL.post);
+  uint32_t* qid = (uint32_t*)(lds + WL.qid);
+  uint16_t* qcls = (uint16_t*)(lds + WL.qcls);
+  uint32_t* slow = (uint32_t*)(lds + WL.slow);
+  uint16_t* areas = (uint16_t*)(lds + WL.areas);
+  const int steps = stream_steps(tb.V);
+  for (uint32_t c = blockIdx.x;;) {
+    const uint32_t from = in_row * K;
+    uint8_t* rw = ws + kWsHead + (size_t)row * rbytes;
+    const RowHeader* hdr = (const RowHeader*)rw;
+    const uint32_t have = counts[row];
+    if (tid == 0) {
+      q_cnt = 0;
+      n_walk = 0;
+      n_lex = 0;
+      s_cnt = 0;
+      group_ctr = kResWaves;  // the first groups are taken by wave number
+      slow_ctr = 0;
+      any_s = 0;
+      ovf_s = 0;
+      step_lo = steps;
+      step_hi = 0;
+    }
+    const bool listed = have <= (uint32_t)open_list_cap(tb.V);  // uniform
+    static_assert(kQueue <= kResThreads && kChunkMax % 64 == 0, "one id per thread");
+    const int n_listed = (int)min(K, have - from);
+    uint2 ent = make_uint2(0u, 0u);  // this thread's id and class
+    if (listed && tid < n_listed) ent = ((const uint2*)(rw + RL.list))[from + tid];
+    if (!tables) {
+      const StageRegion rg[1] = {{rw, lds + WL.block, (uint32_t)RL.block}};
+      dma_regions<1>(rg, tid, kChunkMax);
+    }
+    if (listed && tid < n_listed) {
+      // what the id's lane will read is asked for here, beside the staging: its
+      // first bytes are then in the cache
+      const uint32_t u = tb.spell_of_id[ent.x];
+      const uint32_t tf = tb.lex_token[(size_t)hdr->slot_id * tb.V + ent.x];
+      const uint32_t r0 = tb.crec[hdr->cls_base + (ent.y & 0xFFFFu)].x;
+      const uint32_t k0 = tb.spell_rec[u].x, t0 = tb.spell_tail[u].x;
+      asm volatile("" ::"v"(tf), "v"(r0), "v"(k0), "v"(t0));
+    }
+    if (!listed) {  // from the open bitmap: the wave steps whose open ids start at a position in [from, from + K)
+      const uint16_t* n_open = (const uint16_t*)(rw + RL.n_open);
+      uint32_t run = 0;
+      for (int s0 = 0; s0 < steps; s0 += kResThreads) {
+        const int s = s0 + tid;
+        const uint32_t v = s < steps ? n_open[s] : 0u;
+        uint32_t tot = 0;
+        const uint32_t ex = run + block_scan(v, sums, &tot);
+        if (v && ex >= from && ex < from + K) {
+          atomicMin(&step_lo, s);
+          atomicMax(&step_hi, s + 1);
         }
-        uint32_t run = incl - sum;
-        for (int i = 0; i < per; ++i) {
-          const int t = lane * per + i;
-          if (t < n_it) {
-            upre_s[t] = run;
-            run += (uint32_t)__popcll(umask_s[t]);
+        run += tot;
+      }
+      __syncthreads();
+      for (int s = step_lo + wave; s < step_hi; s += kResWaves) {  // a wave per step: its ids to the queue
+        if (n_open[s] == 0) continue;  // uniform
+        const uint32_t b = ((const uint8_t*)(rw + RL.open))[s * (kStepIds / 8) + lane];
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&q_cnt, (int)n_open[s]);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool o = (b >> j) & 1u;
+          const uint64_t bal = __ballot(o);
+          if (o) qid[base + lane_rank(bal)] = (uint32_t)(s * kStepIds + lane * 8 + j);
+          base += __popcll(bal);
+        }
+      }
+    }
+    dma_wait();
+    __syncthreads();
+    const int n_ids = listed ? n_listed : q_cnt;
+    uint32_t* mrow = mask + (size_t)row * tb.W;
+    // a CI token of a row that claimed a CI-words entry also goes there
+    uint32_t* cdst =
+        h.ci_claim >= 0 ? (uint32_t*)(tb.ci_cache + (size_t)h.ci_claim * tb.ci_stride + kCiHeader) : nullptr;
+    view_row(rv, tb, RL, rowblk);
+    wv.pool = pool + h.stk_off;
+    wv.depth = h.stk_depth;
+    wv.lo = h.stk_depth > (uint32_t)kWalkWin ? h.stk_depth - kWalkWin : 0u;
+    wv.q = h.q;
+    // the ids in two kinds, those of walk classes from the queue's start, those
+    // of lexicon classes from its end: a wave takes ids of one kind, so its lanes
+    // mostly take the same branches
+    const bool in = tid < n_ids;
+    if (!listed) {
+      const uint8_t* codes = rw + RL.codes;
+      if (in) {
+        const uint32_t cls = tb.cmap[(size_t)h.q * tb.V + qid[tid]];
+        ent = make_uint2(qid[tid], cls | (uint32_t)(codes[cls] & 3u) << 16);
+      }
+      __syncthreads();  // the queue is read before it is filled again
+    }
+    {
+      const bool walk = in && (ent.y >> 16) == kVerdictWalk;
+      const uint64_t bw = __ballot(walk), bl = __ballot(in && !walk);
+      int w0 = 0, l0 = 0;
+      if (lane == 0) {
+        if (bw) w0 = atomicAdd(&n_walk, __popcll(bw));
+        if (bl) l0 = atomicAdd(&n_lex, __popcll(bl));
+      }
+      w0 = __builtin_amdgcn_readfirstlane(w0);
+      l0 = __builtin_amdgcn_readfirstlane(l0);
+      const int at = walk ? w0 + lane_rank(bw) : kQueue - 1 - (l0 + lane_rank(bl));
+      if (in) {
+        qid[at] = ent.x;
+        qcls[at] = (uint16_t)ent.y;
+      }
+    }
+    __syncthreads();
+    // groups, one id per lane: the waves are shared out by the kinds' costs (a
+    // walk takes about three times a lexicon id's time)
+    const int nw = n_walk, nl = n_lex;
+    const int w_waves = nw == 0 ? 0 : (nl == 0 ? kResWaves : min(kResWaves - 1, max(1, kResWaves * 3 * nw / (3 * nw + nl))));
+    const int w_lanes = nw ? min(kLanesMax, (nw + w_waves - 1) / w_waves) : 1;
+    const int l_lanes = nl ? min(kLanesMax, (nl + kResWaves - w_waves - 1) / (kResWaves - w_waves)) : 1;
+    const int w_groups = (nw + w_lanes - 1) / w_lanes, groups = w_groups + (nl + l_lanes - 1) / l_lanes;
+    bool any = false;
+    for (int pass = 0; pass < 2; ++pass) {  // pass 1: the ids whose stack area was too small
+      const int n_all = pass == 0 ? groups : s_cnt;
+      const uint32_t cap = pass == 0 ? kFastLane : kSlowLane;
+      for (int g = pass == 0 ? wave : (wave < kSlowWaves ? wave_grab(&slow_ctr) : n_all); g < n_all;
+           g = wave_grab(pass == 0 ? &group_ctr : &slow_ctr)) {  // uniform per wave
+        const bool gw = pass == 0 && g < w_groups;  // a group of walk ids
+        const int pos = gw ? g * w_lanes + lane : (g - w_groups) * l_lanes + lane;
+        const bool in = pass == 1 ? lane == 0 : (gw ? lane < w_lanes && pos < nw : lane < l_lanes && pos < nl);
+        const mptr<true, uint16_t> base =
+            in_mem<true>(areas + (pass == 0 ? wave * kLanesMax * kFastLane : wave * kSlowLane));
+        uint32_t v = kVerdictReject, k = 0, m = 0, X[MW];
+        int id = 0, here = 0;
+        uint4 rec = make_uint4(0, 0, 0, 0);
+        if (in) {
+          const int at = pass == 1 ? (int)slow[g] : (gw ? pos : kQueue - 1 - pos);
+          id = (int)qid[at];
+          here = at;
+          const uint32_t cls = qcls[at], u = tb.spell_of_id[id];
+          LexLane lx;
+          lx.tf = tb.lex_token[(size_t)h.slot_id * tb.V + id];
+          rec = tb.crec[h.cls_base + cls];
+          const uint4 rk = tb.spell_rec[u], tl = tb.spell_tail[u];
+          lx.tb = &tb;
+          lx.sl = slot_of(h.slot);
+          lx.n = rk.w & 0xFFu;
+          lx.b0 = (uint64_t)rk.x | (uint64_t)rk.y << 32;
+          lx.b1 = lx.n > 8 ? (uint64_t)tl.x | (uint64_t)tl.y << 32 : 0ull;
+          lx.b2 = lx.n > 8 ? (uint64_t)tl.z | (uint64_t)tl.w << 32 : 0ull;
+          lx.rem = (uint64_t)h.rem_lo | (uint64_t)h.rem_hi << 32;
+          lx.rem_len = h.rem_len;
+          lx.lexnode = h.lexnode;
+          v = walk_token<MW, Full>(wv, rec, lx, rk.w >> 8, base + lane * kFastLane, cap, k, m, X);
+        }
+        // a trailing lexeme past the kept stacks: the wave tries its terminals
+        // together, one lane each
+        for (uint64_t todo = __ballot(v == kWalkTrail); todo; todo &= todo - 1ull) {
+          const int src = __ffsll((unsigned long long)todo) - 1;
+          const uint32_t sk = __builtin_amdgcn_readlane(k, src), sm = __builtin_amdgcn_readlane(m, src);
+          const ChainStack st{wv.pool, wv.win, wv.lo, sk, base + src * kFastLane, sm};
+          bool ok = false;
+#pragma unroll
+          for (int w = 0; w < MW; w += 2) {
+            const uint32_t x0 = __builtin_amdgcn_readlane(X[w], src), x1 = __builtin_amdgcn_readlane(X[w + 1], src);
+            if ((x0 | x1) == 0u || ok) continue;  // uniform
+            uint32_t n = sk + sm - 1u, a = 0;
+            uint32_t sv = st.at(n);
+            bool moved = false;
+            if (((lane < 32 ? x0 : x1) >> (lane & 31)) & 1u)
+              a = lr_chain<Full>(wv.lt, st, (uint32_t)(w * 32 + lane), n, sv, moved);
+            ok = __any(a != 0u);
           }
-        }
-        if (lane == 63) upre_s[n_it] = incl;
-      }
-      __syncthreads();
-      const int n_und = (int)upre_s[n_it];
-      if (n_und == 0) continue;  // uniform
-      if (!blocks) {  // the rows' blocks, two 16-byte chunks per thread in flight at a time
-        const uint32_t n16 = WL.block / 16u, tot16 = (uint32_t)gr * n16;
-        for (uint32_t i = tid; i < tot16; i += 2u * kWalkThreads) {
-          const uint32_t i2 = i + kWalkThreads;
-          const uint32_t r = i / n16, r2 = i2 / n16;
-          const uint4 v = reinterpret_cast<const uint4*>(rows + (size_t)(g0 + r) * rbytes)[i - r * n16];
-          uint4 v2 = make_uint4(0, 0, 0, 0);
-          if (i2 < tot16) v2 = reinterpret_cast<const uint4*>(rows + (size_t)(g0 + r2) * rbytes)[i2 - r2 * n16];
-          reinterpret_cast<uint4*>(rows_s)[i] = v;
-          if (i2 < tot16) reinterpret_cast<uint4*>(rows_s)[i2] = v2;
-        }
-        blocks = true;
-      }
-      __syncthreads();
-      const ParseTabs<true> pt = lds_parse(tb, lds, WL.pl);
-      const DfaView step{(const uint16_t*)(lds + WL.dfa), bcls, tb.C};
-      const WalkShared<MW> sh{&tb, pt, step, tinfo_s, I_s, live_s, acc_off_s, acc_list_s, pool};
-      // positions [0, n_wpos) belong to byte-walk items (they come first), the
-      // rest to lexicon items; a wave takes kWalkChunk walk positions or
-      // kLexChunk lexicon positions at a time (fewer lanes, less divergence)
-      const int t_lex0 = min(max((gr * nsub - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x - k0, 0), n_it);
-      const int n_wpos = (int)upre_s[t_lex0];
-      const int nwc = (n_wpos + kWalkChunk - 1) / kWalkChunk;
-      for (;;) {
-        const int c = wave_grab(&chunk_ctr);
-        int pos;
-        bool in;
-        if (c < nwc) {
-          pos = c * kWalkChunk + lane;
-          in = lane < kWalkChunk && pos < n_wpos;
-        } else {
-          if (n_wpos + (c - nwc) * kLexChunk >= n_und) break;
-          pos = n_wpos + (c - nwc) * kLexChunk + lane;
-          in = lane < kLexChunk && pos < n_und;
+          if (lane == src) v = ok ? kVerdictAllow : kVerdictReject;
         }
         if (in) {
-          // the item holding position pos: last t with upre_s[t] <= pos
-          int lo = 0, hi = n_it - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if ((int)upre_s[mid] <= pos) lo = mid;
-            else hi = mid - 1;
-          }
-          const int bit = nth_set_bit(umask_s[lo], pos - (int)upre_s[lo]);
-          const int j = (int)blockIdx.x + (k0 + lo) * (int)gridDim.x;
-          const int lex = j >= gr * nsub ? 1 : 0, jr = j - lex * gr * nsub;
-          const int r = jr / nsub;
-          const uint32_t u = (uint32_t)((jr - r * nsub) * 64 + bit);
-          const uint8_t* rowblk = rows_s + (size_t)r * WL.block;
-          uint8_t* rw = rows + (size_t)(g0 + r) * rbytes;
-          const uint4 rk = tb.spell_rec[u];
-          // a lexicon spelling's class: the class map at its first id (its
-          // aliases share it)
-          const uint32_t cls =
-              lex ? (uint32_t)tb.cmap[(size_t)((const RowHeader*)rowblk)->q * tb.V + (rk.z & 0x7FFFFFFFu)] : 0u;
-          const RowHeader& hh = *(const RowHeader*)rowblk;
-          // a lexicon spelling of a CI class also goes to the row's claimed CI-words entry
-          const bool ci_tok = lex && hh.ci_claim >= 0 && ci_class(tb.crec[hh.cls_base + cls].x);
-          if (residue_token<MW>(sh, hh, rowblk, rw, RL, u, rk, lex != 0, cls, lane_area) > 0) {
-            allow_spelling(tb, mask + (size_t)(g0 + r) * tb.W, u, rk);
-            if (ci_tok)
-              allow_spelling(tb, (uint32_t*)(tb.ci_cache + (size_t)hh.ci_claim * tb.ci_stride + kCiHeader), u, rk);
-            row_allowed[r] = 1u;
+          if (v == kVerdictAllow) {
+            atomicOr(mrow + (id >> 5), 1u << (id & 31));
+            if (cdst && ci_class(rec.x)) atomicOr(cdst + (id >> 5), 1u << (id & 31));
+            any = true;
+          } else if (v == kWalkFull) {
+            if (pass == 0) slow[atomicAdd(&s_cnt, 1)] = (uint32_t)here;
+            else ovf_s = 1;
           }
         }
       }
+      if (pass == 0 && any) any_s = 1;
+      __syncthreads();
+      if (s_cnt == 0) break;  // uniform
+      if (pass == 1) {
+        if (any) any_s = 1;
+        __syncthreads();
+      }
     }
-    __syncthreads();  // every wave is done with the group: one header store per row that got a token
-    if (tid < gr && row_allowed[tid]) ((RowHeader*)(rows + (size_t)(g0 + tid) * rbytes))->nonempty = 1u;
+    if (tid == 0) {
+      // chunks ended, those that allowed an id, those that overflowed, 21 bits
+      // each in one word: the last chunk needs no other memory of the others
+      const unsigned long long add = 1ull | (any_s ? 1ull << 21 : 0ull) | (ovf_s ? 1ull << 42 : 0ull);
+      const unsigned long long sum = atomicAdd(&((RowHeader*)rw)->done, add) + add;
+      constexpr unsigned long long kField = (1ull << 21) - 1ull;
+      if ((sum & kField) == ((have & (kListFull - 1u)) + K - 1u) / K) {
+        int32_t st = h.pstat;
+        if (sum >> 42) st |= GRID_ROW_OVERFLOW;
+        if (!((sum >> 21) & kField) && !h.nonempty && !h.eos_ok) st |= GRID_ROW_EMPTY;
+        if (status) status[row] = st;
+        ((RowHeader*)rw)->fstat = st;
+        ((RowHeader*)rw)->done = 0ull;
+      }
+    }
+    c += gridDim.x;
+    row = find_chunk(counts, first, B, K, c, &in_row);
+    if (row < 0) break;  // uniform
+    __syncthreads();  // the row's block and counters are free
   }
-  dma_wait();  // a workgroup without items still has its table copies in flight
 }
 
-// ---------------------------------------------------------------- finalize
-// One workgroup per row.  Spellings the residue walk handed over (their lane
-// stack area was too small) are walked again from the row's configuration
-// with a large stack area per thread in the workspace, reading the tables
-// from global memory; then the row status is written.
-template <int MW>
-__global__ __launch_bounds__(kBlock) void finalize_kernel(Tables tb, const grid_config* __restrict__ cfgs,
-                                                          const uint16_t* __restrict__ pool,
-                                                          uint32_t* __restrict__ mask, uint8_t* __restrict__ ws,
-                                                          size_t rbytes, int32_t* __restrict__ status) {
-  const int row = blockIdx.x;
-  const int tid = threadIdx.x;
-  uint8_t* rw = ws + kWsHead + (size_t)row * rbytes;
-  RowHeader* hdr = (RowHeader*)rw;
-  const RowLayout RL = row_layout(tb);
-  if (hdr->valid == kRowCached) {  // served from the mask cache by the prologue
-    if (threadIdx.x == 0 && status) status[row] = hdr->pstat;
-    return;
-  }
-  const bool valid = hdr->valid == kRowValid;
-  const uint32_t count = valid ? min(hdr->slow_count, (uint32_t)kSlowCap) : 0u;
-  __shared__ uint32_t I_s[8];
-  __shared__ int slow_ok;
-  if (tid == 0) slow_ok = 0;
-  if (count > 0) {  // uniform
-    if (tid < 8) I_s[tid] = tb.ign[tid];
-    const ParseTabs<false> pt = global_parse(tb);  // rare: tables stay in global memory
-    __syncthreads();
-    if (tid < kSlowThreads) {
-      const grid_config cfg = cfgs[row];
-      RowCtx<false> rc;
-      rc.tb = &tb;
-      rc.pt = pt;
-      rc.bs = BaseStack<false>{pool + cfg.stk_off, nullptr, cfg.stk_depth, cfg.stk_depth};
-      rc.sl = load_slot(tb, cfg.slot);
-      rc.tv = TermView{tb.term_info, I_s, hdr->R, tb.live, 8};
-      rc.acc_off = tb.acc_off;
-      rc.acc_list = tb.acc_list;
-      rc.a2 = (const uint32_t*)(rw + RL.a2);
-      rc.a2_stride = 8;
-      rc.post = (const Post*)(rw + RL.post);
-      rc.clsA = nullptr;
-      rc.clsW = nullptr;
-      rc.winner = -1;
-      uint16_t* ov = (uint16_t*)(rw + RL.slow_ov) + tid * kSlowLane;
-      const DfaView step{tb.dfa, tb.bclass, tb.C};
-      LexState lex0;
-      lex0.len = cfg.flags & 1u ? 0u : cfg.rem_len;
-      lex0.node = cfg.lexnode;
-      lex0.need = rc.sl.restricted != 0 ? 1u : 0u;
-      lex0.w = 0;
-      for (int k = 0; k < 8; ++k) lex0.w |= (uint64_t)cfg.rem_head[k] << (8 * k);
-      for (uint32_t k = tid; k < count; k += kSlowThreads) {
-        const uint32_t su = ((const uint32_t*)(rw + RL.slow))[k];
-        Lane<MW> ln;
-        ln.mode = 0;
-        ln.t1 = -1;
-        ln.k = 0;
-        ln.m = 0;
-#pragma unroll
-        for (int w = 0; w < MW; ++w) ln.acur[w] = hdr->A[w];
-        const uint32_t base = tb.spell_off[su];
-        auto byte_at = [&](uint32_t i) -> uint32_t { return tb.spell_bytes[base + i]; };
-        const int ok = walk_bytes<false, MW>(rc, ln, cfg.q, lex0, 0u, tb.spell_off[su + 1] - base, byte_at, step,
-                                             ov, kSlowLane, 1u);
-        if (ok > 0) {
-          const uint4 rk = tb.spell_rec[su];
-          allow_spelling(tb, mask + (size_t)row * tb.W, su, rk);
-          if (hdr->ci_claim >= 0) {  // a CI-class spelling also goes to the row's claimed entry
-            const uint32_t cls = tb.cmap[(size_t)cfg.q * tb.V + (rk.z & 0x7FFFFFFFu)];
-            if (ci_class(tb.crec[hdr->cls_base + cls].x))
-              allow_spelling(tb, (uint32_t*)(tb.ci_cache + (size_t)hdr->ci_claim * tb.ci_stride + kCiHeader), su, rk);
-          }
-          slow_ok = 1;
-        } else if (ok < 0) {
-          atomicOr(&hdr->wstat, GRID_ROW_OVERFLOW);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int32_t st;
-    if (valid) {
-      st = hdr->pstat | hdr->wstat;
-      if (hdr->slow_count > (uint32_t)kSlowCap) st |= GRID_ROW_OVERFLOW;
-      if (!hdr->nonempty && !slow_ok && !hdr->eos_ok) st |= GRID_ROW_EMPTY;
-    } else {
-      st = hdr->pstat | GRID_ROW_BAD_CONFIG;
-    }
-    if (status) status[row] = st;
-    hdr->fstat = st;
-    if (valid && hdr->ci_claim >= 0) {  // publish the row's CI-words entry, or give the slot back
-      uint32_t* e = (uint32_t*)(tb.ci_cache + (size_t)hdr->ci_claim * tb.ci_stride);
-      __threadfence();
-      __hip_atomic_store(e, st == GRID_ROW_OK ? 2u : 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
+// Publishes the CI-words entry of every row that claimed one and ended OK, or
+// gives the slot back.
+__global__ __launch_bounds__(64) void ci_publish_kernel(Tables tb, const uint8_t* __restrict__ ws, size_t rbytes, int B) {
+  const int row = (int)(blockIdx.x * 64u + threadIdx.x);
+  if (row >= B) return;
+  const RowHeader* hdr = (const RowHeader*)(ws + kWsHead + (size_t)row * rbytes);
+  if (hdr->valid != kRowValid || hdr->ci_claim < 0) return;
+  uint32_t* e = (uint32_t*)(tb.ci_cache + (size_t)hdr->ci_claim * tb.ci_stride);
+  __threadfence();
+  __hip_atomic_store(e, hdr->fstat == GRID_ROW_OK ? 2u : 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Mask cache write-back: each row that claimed an entry in the prologue
@@ -3141,68 +2858,69 @@ bool raise_lds(const void* fn, uint32_t bytes) {
   return true;
 }
 
-// Resident residue workgroups on the current device (compute units x
-// occupancy) for an LDS size; raises the kernel's LDS limit first.
-template <int MW>
-int residue_grid_size(uint32_t lds) {
-  if (!raise_lds((const void*)residue_kernel<MW>, lds)) return -1;
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return -1;
-  // the answer per (device, LDS size), looked up once: the occupancy query
-  // costs more host time than a small batch's whole mask on the device
-  struct Entry {
-    int dev;
-    uint32_t lds;
-    int blocks;
-  };
-  static std::mutex mu;
-  static Entry seen[64];
-  static int n_seen = 0;
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < n_seen; ++i)
-      if (seen[i].dev == dev && seen[i].lds == lds) return seen[i].blocks;
+// Compute units of the current device, looked up once per device.
+int compute_units() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> seen[kDevices];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return 256;
+  cus = seen[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
+    seen[dev].store(cus, std::memory_order_relaxed);
   }
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, residue_kernel<MW>, kWalkThreads, lds) != hipSuccess ||
-      per_cu <= 0)
-    per_cu = 1;
-  std::lock_guard<std::mutex> lock(mu);
-  if (n_seen < 64) seen[n_seen++] = {dev, lds, cus * per_cu};
-  return cus * per_cu;
+  return cus;
 }
 
 template <int MW>
 int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint16_t* pool, uint32_t* mask,
                 uint8_t* eos, int32_t* status, uint8_t* ws, size_t rb, uint32_t phases, hipStream_t s) {
-  const uint32_t parse_bytes = prologue_lds(tb).total;
-  if (!raise_lds((const void*)prologue_kernel<MW>, parse_bytes))
-    return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
   if (phases & GRID_PHASE_PROLOGUE) {
-    hipLaunchKernelGGL(prologue_kernel<MW>, dim3(B), dim3(kProThreads), parse_bytes, s, tb, cfg_dev, pool, mask, eos,
-                       ws, rb);
-    const uint32_t vy = ((uint32_t)tb.max_classes + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(verdict_kernel<MW>, dim3(B, vy), dim3(kBlock), verdict_lds(tb).total, s, tb, ws, rb);
+    const uint32_t pro = prologue_lds(tb).total, jud = judge_lds(tb).total;
+    const bool in_lds = lr_in_lds(tb);
+    const auto prologue = in_lds ? prologue_kernel<MW, true> : prologue_kernel<MW, false>;
+    if (!raise_lds((const void*)prologue, pro) || !raise_lds((const void*)judge_kernel<MW>, jud))
+      return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
+    hipLaunchKernelGGL(prologue, dim3(B), dim3(kProThreads), pro, s, tb, cfg_dev, pool, mask, eos, status, ws, rb);
+    // a row's classes: as many parts as leave one workgroup per compute unit for
+    // the batch (each stages the tables anew), at most one block of classes each
+    const int blocks = std::max(1, (tb.max_classes + kJudgeThreads - 1) / kJudgeThreads);
+    const int parts = std::max(1, std::min(4 * compute_units() / B, blocks));
+    hipLaunchKernelGGL(judge_kernel<MW>, dim3((uint32_t)B * (uint32_t)parts), dim3(kJudgeThreads), jud, s, tb, ws, rb, parts);
   }
   if (phases & GRID_PHASE_WALK) {
-    const long long blocks = 8ll * B * stream_groups(tb.V);
+    const uint32_t lds = stream_lds(tb).total;
+    if (!raise_lds((const void*)stream_kernel, lds)) return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
+    // a row's slices: four workgroups per compute unit over the batch (their
+    // LDS lets them share one), at least one wave step each
+    const int steps = stream_steps(tb.V);
+    const int want = std::max(1, std::min(3 * compute_units() / B, steps));
+    const int slice_ids = (steps + want - 1) / want * kStepIds;
+    const int slices = (tb.V + slice_ids - 1) / slice_ids;
+    const long long blocks = (long long)B * slices;
     if (blocks > 0x7FFFFFFFll) return fail(GRID_E_CAPACITY, "grid_mask: batch x vocabulary too large");
-    hipLaunchKernelGGL(stream_kernel, dim3((uint32_t)blocks), dim3(kBlock), 0, s, tb, mask, ws, rb, B);
+    hipLaunchKernelGGL(stream_kernel, dim3((uint32_t)blocks), dim3(kStreamThreads), lds, s, tb, mask, ws, rb, B, slices,
+                       slice_ids);
   }
-  if ((phases & GRID_PHASE_RESIDUE) && tb.U > 0) {
-    const ResLds RL = res_lds(tb, MW, B);
-    const int resident = residue_grid_size<MW>(RL.total);
-    if (resident <= 0) return fail(GRID_E_HIP, "grid_mask: cannot raise the residue walk's LDS limit");
-    // no more workgroups than work items (a small vocabulary has few)
-    const long long items = 2ll * std::min(B, RL.group) * ((tb.U + 63) / 64);
-    const int blocks = (int)std::max(1ll, std::min((long long)resident, items));
-    hipLaunchKernelGGL(residue_kernel<MW>, dim3(blocks), dim3(kWalkThreads), RL.total, s, tb, pool, mask, ws, rb, B);
+  if (phases & GRID_PHASE_RESIDUE) {
+    const ResLds RL = res_lds(tb);
+    const void* fn = RL.full ? (const void*)residue_kernel<MW, true> : (const void*)residue_kernel<MW, false>;
+    if (!raise_lds(fn, RL.total)) return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
+    // one workgroup per compute unit, no more than the batch can have chunks
+    const long long chunks = (long long)B * ((tb.V + kChunkMin - 1) / kChunkMin);
+    const dim3 grid((uint32_t)std::min((long long)compute_units(), chunks));
+    if (RL.full)
+      hipLaunchKernelGGL((residue_kernel<MW, true>), grid, dim3(kResThreads), RL.total, s, tb, pool, mask, ws, rb, B,
+                         status);
+    else
+      hipLaunchKernelGGL((residue_kernel<MW, false>), grid, dim3(kResThreads), RL.total, s, tb, pool, mask, ws, rb, B,
+                         status);
   }
   if (phases & GRID_PHASE_FINALIZE) {
-    hipLaunchKernelGGL(finalize_kernel<MW>, dim3(B), dim3(kBlock), 0, s, tb, cfg_dev, pool, mask, ws, rb, status);
+    if (tb.ci_cache && (tb.ci_flags & GRID_CI_INSERT))
+      hipLaunchKernelGGL(ci_publish_kernel, dim3((uint32_t)(B + 63) / 64), dim3(64), 0, s, tb, ws, rb, B);
     if (tb.cache && (tb.cache_flags & GRID_CACHE_INSERT))
       hipLaunchKernelGGL(cache_publish_kernel, dim3(B), dim3(kBlock), 0, s, tb, mask, ws, rb);
-
   }
   return GRID_OK;
 }
@@ -3211,12 +2929,14 @@ int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint1
 
 int grid::overlay_capacity() { return kFastLane; }
 
-// head, then B rows
 static size_t row_bytes(const grid_compiled* g) {
-  return row_layout(g->parser.T, g->dfa.S, (int)g->vocab.spell_off.size() - 1, (int)g->classes.max_classes).total;
+  return row_layout(g->parser.T, g->dfa.S, g->vocab.V, (int)g->max_classes()).total;
 }
 
-static size_t workspace_size(const grid_compiled* g, int B) { return kWsHead + row_bytes(g) * (size_t)B; }
+// head, B rows, then the number of open ids of every row
+static size_t workspace_size(const grid_compiled* g, int B) {
+  return kWsHead + row_bytes(g) * (size_t)B + (((size_t)B * 4 + 255) & ~(size_t)255);
+}
 
 extern "C" size_t grid_mask_workspace_bytes(const grid_compiled* g, int32_t B) {
   if (!g || B <= 0) return 0;
@@ -3233,13 +2953,16 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
                                GRID_ART_ALIAS_OFF,   GRID_ART_ALIAS_IDS,   GRID_ART_LEX_FLAGS,
                                GRID_ART_LEX_HASH,    GRID_ART_LEX_SLOTS,   GRID_ART_PARSE_STATE,
                                GRID_ART_PARSE_REDX,  GRID_ART_GOTO_HASH,   GRID_ART_LEX_PREFIX,
-                               GRID_ART_SPELL_OF_ID, GRID_ART_CLASS_MAP, GRID_ART_CLASS_OFF,
-                               GRID_ART_CLASS_REC,   GRID_ART_LEX_STRIDE,  GRID_ART_LEX_TOKEN,
+                               GRID_ART_SPELL_OF_ID, GRID_ART_LEX_STRIDE,  GRID_ART_LEX_TOKEN,
                                GRID_ART_PARSE_SHIFT, GRID_ART_GOTO_SKIP,
                                GRID_ART_STATE_SYMBOL, GRID_ART_LEX_CHILD, GRID_ART_ID_HEAD,
                                GRID_ART_LEX_TOKSUM};
   for (int w : needed)
     if (!bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
+  // the classes: of the reduced programs, or of the full ones where those are not bound
+  const bool prog = g->dev[GRID_ART_PROG_MAP] && g->dev[GRID_ART_PROG_OFF] && g->dev[GRID_ART_PROG_REC];
+  for (int w : {GRID_ART_CLASS_MAP, GRID_ART_CLASS_OFF, GRID_ART_CLASS_REC})
+    if (!prog && !bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
   tb.dfa = (const uint16_t*)g->dev[GRID_ART_DFA_CLASS];
   tb.bclass = (const uint8_t*)g->dev[GRID_ART_BYTE_CLASS];
   tb.acc_off = (const uint32_t*)g->dev[GRID_ART_DFA_ACCEPT_OFF];
@@ -3256,8 +2979,6 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.spell_bytes = (const uint8_t*)g->dev[GRID_ART_SPELL_BYTES];
   tb.spell_rec = (const uint4*)g->dev[GRID_ART_SPELL_REC];
   tb.spell_tail = (const uint4*)g->dev[GRID_ART_SPELL_TAIL];
-  tb.alias_off = (const uint32_t*)g->dev[GRID_ART_ALIAS_OFF];
-  tb.alias_ids = (const int32_t*)g->dev[GRID_ART_ALIAS_IDS];
   tb.lex_flags = (const uint16_t*)g->dev[GRID_ART_LEX_FLAGS];
   tb.lex_hash = (const uint32_t*)g->dev[GRID_ART_LEX_HASH];
   tb.lex_slots = (const uint32_t*)g->dev[GRID_ART_LEX_SLOTS];
@@ -3270,10 +2991,11 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.spell_of_id = (const uint32_t*)g->dev[GRID_ART_SPELL_OF_ID];
   tb.state_sym = (const uint32_t*)g->dev[GRID_ART_STATE_SYMBOL];
   tb.stack_hash = nullptr;
-  tb.cmap = (const uint16_t*)g->dev[GRID_ART_CLASS_MAP];
-  tb.coff = (const uint32_t*)g->dev[GRID_ART_CLASS_OFF];
-  tb.crec = (const uint4*)g->dev[GRID_ART_CLASS_REC];
-  tb.max_classes = (int)g->classes.max_classes;
+  tb.prog = prog ? 1 : 0;
+  tb.cmap = (const uint16_t*)g->dev[prog ? GRID_ART_PROG_MAP : GRID_ART_CLASS_MAP];
+  tb.coff = (const uint32_t*)g->dev[prog ? GRID_ART_PROG_OFF : GRID_ART_CLASS_OFF];
+  tb.crec = (const uint4*)g->dev[prog ? GRID_ART_PROG_REC : GRID_ART_CLASS_REC];
+  tb.max_classes = (int)g->max_classes();
   tb.S = g->dfa.S;
   tb.C = g->dfa.C;
   tb.T = g->parser.T;
@@ -3288,7 +3010,11 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.tw = g->parser.tw;
   tb.n_pstate = (int)g->parser.pstate.size();
   tb.n_predx = (int)g->parser.predx.size();
-  tb.n_pshift = (int)g->parser.pshift.size();
+  tb.n_pshift = (int)g->parser.n_shift_runs;
+  tb.mact = tb.pshift + g->parser.mact_off;
+  tb.mred = (const uint32_t*)(tb.pshift + g->parser.mact_red_off);
+  tb.mbits = g->parser.mact_bits;
+  tb.prod = (const uint32_t*)g->dev[GRID_ART_PROD];
   tb.n_acc = (int)g->dfa.accept_list.size();
   tb.hbits = g->parser.goto_hbits;
   for (int w = 0; w < 8; ++w) tb.ign[w] = 0;
@@ -3347,9 +3073,9 @@ static int mask_call(const grid_compiled* g, int32_t B, const grid_config* cfg_d
     tb.ci_flags = ci_flags;
   }
   const int mw = tb.tw;
-  const ResLds WL = res_lds(tb, mw, B);
-  if (tb.T > 255 || (mw != 2 && mw != 4 && mw != 8) || WL.total + 64 > kWalkLdsMax ||
-      prologue_parse_lds(tb).total > kPrologueParseMax || verdict_lds(tb).total > 64 * 1024)
+  if (tb.T > 255 || (mw != 2 && mw != 4 && mw != 8) || table_bytes(tb) > kTablesMax ||
+      res_lds(tb).total > kLdsMax - kLdsStatic || stream_lds(tb).total > kLdsMax - kLdsStatic || prologue_parse_lds(tb).total > kPrologueParseMax ||
+      verdict_bytes(tb) > 64 * 1024)
     return fail(GRID_E_CAPACITY, "grid_mask: lexer DFA or LR tables too large for the LDS staging");
   hipStream_t s = (hipStream_t)stream;
   uint8_t* ws = (uint8_t*)workspace_dev;

@@ -72,6 +72,25 @@ GRID_HD uint32_t lexs_hash(uint32_t anc, uint32_t lo, uint32_t hi, uint32_t len)
 // Local class 0 of every state is "rejected by the lexer alone" (also special
 // and empty tokens); local class 1 is "walk the bytes" (tokens of a state
 // whose class count exceeds 65536).
+//
+// Reduced programs (PROG_MAP / PROG_OFF / PROG_REC, the same layout): what no
+// configuration can tell apart is left out, so that fewer classes are judged
+// and fewer tokens end more lexemes than a record holds.
+//  - A lexeme whose state's first accept-list entry is an ignored terminal
+//    without a category (white space, comments) is dropped: that entry wins
+//    under any stack and leaves it as it is.  The lexeme after it starts fresh
+//    in the start state; kProgFresh: what was dropped held the pending bytes.
+//  - A state after the last byte in which such a terminal is live accepts any
+//    trailing lexeme; all of them are one.
+//  - Byte positions are kept only where a lexicon may be asked about: for a
+//    lexeme whose state accepts a category terminal, a trailing lexeme whose
+//    state has one live, and the last recorded end of a token with more.
+//   w0: as above | kProgFresh | start of lexeme 1 << 8 | start of lexeme 2 << 16
+//       | start of the trailing lexeme << 24
+//   w1, w2: as above (0 for the state after the last byte of a token with more
+//       ends than the record holds)
+//   w3: end of lexeme 0, 1, 2 (8 bits each) | start of lexeme 0 << 24
+constexpr uint32_t kProgFresh = 1u << 6;
 constexpr int kClassEnds = 3;
 constexpr uint32_t kClassMore = 4;
 constexpr uint32_t kClassEndsMask = 7u;

@@ -390,6 +390,89 @@ std::vector<int> skip_unit_states(Parser& P) {
   return unit;
 }
 
+// The mask kernels' action of every (state, terminal, end of input last), with
+// everything that (state, terminal) alone decides done ahead: the reductions by
+// empty productions, and those that pop nothing but what these pushed, are run
+// here on the states pushed above the state.  What is left is one of
+//   0                  error
+//   kMactShift | state  shift (or accept: state 0); the target as in the mask run
+//                      of shift targets; kMactPushed when empty reductions push
+//                      states before the shift
+//   pops << bits | lhs  pop that many entries (at least 1: the state itself, the
+//                      pushed states already taken off), GOTO_SKIP on lhs
+// so a reduce chain keeps one state above the stack at every step and needs one
+// table read per action.  When a left side and its pops do not fit 15 bits, the
+// reduce entries are 1 + an index into a list of (lhs | pops << 16).
+void build_mask_actions(Parser& P, const std::vector<int>& unit) {
+  const int T1 = P.T + 1, NS = P.n_states, N = P.N;
+  P.n_shift_runs = (uint32_t)P.pshift.size();
+  std::vector<uint32_t> act((size_t)NS * T1, 0);  // 0, shift (bit 31), or lhs | pops << 16
+  uint32_t max_pops = 1;
+  for (int s = 0; s < NS; ++s)
+    for (int t = 0; t < T1; ++t) {
+      std::vector<uint16_t> up;  // states pushed above s
+      for (int guard = 0; guard <= 4 * NS + 16; ++guard) {
+        const int top = up.empty() ? s : up.back();
+        const uint16_t a = P.act(top, t), kind = a & 0xC000;
+        if (a == 0) break;
+        if (kind == kActAccept) {
+          act[(size_t)s * T1 + t] = 1u << 31 | (up.empty() ? 0u : 1u << 30);
+          break;
+        }
+        if (kind == kActShift) {
+          uint16_t tgt = (uint16_t)(a & 0x3FFF);
+          if (unit[tgt] >= 0) {
+            const uint16_t g = P.go_skip[(size_t)top * N + (P.prod[unit[tgt]] & 0xFFFF)];
+            if (g != kNoGoto) tgt = g;
+          }
+          act[(size_t)s * T1 + t] = 1u << 31 | (up.empty() ? 0u : 1u << 30) | tgt;
+          break;
+        }
+        const uint32_t pr = P.prod[a & 0x3FFF], len = pr >> 16, X = pr & 0xFFFF;
+        if (len > up.size()) {
+          const uint32_t pops = len - (uint32_t)up.size();
+          act[(size_t)s * T1 + t] = X | pops << 16;
+          max_pops = std::max(max_pops, pops);
+          break;
+        }
+        up.resize(up.size() - len);
+        const uint16_t g = P.go_skip[(size_t)(up.empty() ? s : up.back()) * N + X];
+        if (g == kNoGoto) break;
+        up.push_back(g);
+      }
+    }
+  int bits = 1;
+  while ((1 << bits) < N) ++bits;
+  P.mact_bits = bits < 15 && max_pops < (1u << (15 - bits)) ? bits : 0;
+  while (P.pshift.size() % 8) P.pshift.push_back(0);
+  P.mact_off = (uint32_t)P.pshift.size();
+  std::map<uint32_t, uint32_t> index;
+  std::vector<uint32_t> red;
+  for (uint32_t a : act) {
+    uint16_t e = 0;
+    if (a >> 31) {
+      e = (uint16_t)(kMactShift | ((a >> 30) & 1u ? kMactPushed : 0) | (a & 0x3FFF));
+    } else if (a) {
+      if (P.mact_bits) {
+        e = (uint16_t)((a >> 16) << P.mact_bits | (a & 0xFFFF));
+      } else {
+        auto it = index.emplace(a, (uint32_t)red.size());
+        if (it.second) red.push_back(a);
+        if (it.first->second + 1 >= kMactShift) throw Error(GRID_E_CAPACITY, "more than 32766 reductions");
+        e = (uint16_t)(it.first->second + 1);
+      }
+    }
+    P.pshift.push_back(e);
+  }
+  while (P.pshift.size() % 8) P.pshift.push_back(0);
+  P.mact_red_off = (uint32_t)P.pshift.size();
+  P.n_mact_red = (uint32_t)red.size();
+  for (uint32_t r : red) {
+    P.pshift.push_back((uint16_t)r);
+    P.pshift.push_back((uint16_t)(r >> 16));
+  }
+}
+
 // Compact tables for simulating a whole set of lookahead terminals at once:
 // per state the terminals that shift (or accept, end-of-input column), the
 // terminals reduced by the state's main production, and any further reduce
@@ -528,6 +611,7 @@ void compact_tables(Parser& P) {
       if (g != kNoGoto) gotos.push_back({goto_key(s, a), g});
     }
   }
+  build_mask_actions(P, unit);
   // load factor at most 2/3, so a lookup probes few slots
   int hb = 6;
   while ((size_t)1 << hb < gotos.size() + gotos.size() / 2) ++hb;

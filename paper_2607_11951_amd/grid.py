@@ -30,7 +30,9 @@ ART_NAMES = ["DFA_DENSE", "DFA_CLASS", "BYTE_CLASS", "DFA_ACCEPT_OFF", "DFA_ACCE
              "SPELL_REC", "PARSE_STATE", "PARSE_REDX", "GOTO_HASH", "SPELL_TAIL", "LEX_PREFIX",
              "SPELL_RANGE", "SPELL_OF_ID", "CLASS_MAP", "CLASS_OFF", "CLASS_REC", "LEX_STRIDE",
              "LEX_TOKEN", "ID_FIRST", "PARSE_SHIFT", "STATE_SYMBOL", "LEX_CHILD", "ID_HEAD",
-             "LEX_TOKSUM", "GOTO_SKIP"]
+             "LEX_TOKSUM", "GOTO_SKIP", "PROG_MAP", "PROG_OFF", "PROG_REC"]
+# the classes of the full lexeme programs: the kernels read those of the reduced ones (PROG_*) instead
+HOST_ONLY = {"CLASS_MAP", "CLASS_OFF", "CLASS_REC"}
 ART = {n: i for i, n in enumerate(ART_NAMES)}
 
 CONFIG_DTYPE = np.dtype([("stk_off", "<u4"), ("stk_depth", "<u4"), ("lexnode", "<u4"), ("q", "<u2"),
@@ -202,9 +204,9 @@ class Grid:
             _check(lib().grid_bind_device(self.h, ART[name], ctypes.c_void_p(ptr)))
 
     def to_device(self, device="cuda"):
-        """Copies every artifact to device memory and binds it."""
+        """Copies the artifacts the kernels read to device memory and binds them."""
         self.device = device
-        self._upload(device, ART_NAMES)
+        self._upload(device, [n for n in ART_NAMES if n not in HOST_ONLY])
         return self
 
     def config(self, w, slot=0, cap=1 << 16):

@@ -1,0 +1,84 @@
+"""The mask kernels' other routes, each against the CPU oracle word for word:
+the classes of the full lexeme programs in place of the reduced ones, rows
+with more open ids than their list holds, and tables too large for LDS."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from workloads import make_workload  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import paper_2607_11951_amd as pkg
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pkg.lib()
+    return pkg
+
+
+def _check(g, o, prefixes, slot=0, lexicon=None):
+    cfgs, pool = g.configs(prefixes, [slot] * len(prefixes))
+    m, e, s = g.mask(*g.configs_to_device(cfgs, pool), len(prefixes))
+    torch.cuda.synchronize()
+    assert (s.cpu().numpy() == 0).all(), s.cpu().tolist()
+    for i, w in enumerate(prefixes):
+        want, want_eos = o.mask(w, mode=1, **({"lexicon": lexicon} if lexicon is not None else {}))
+        assert np.array_equal(m[i].cpu().numpy().view(np.uint32), want), w
+        assert int(e[i]) == want_eos, w
+
+
+@pytest.mark.parametrize("classes", ["PROG", "CLASS"])
+@pytest.mark.parametrize("workload", [1, 2, 3])
+def test_either_class_tables(G, oracle_mod, workload, classes):
+    wl = make_workload(workload, rows=16)
+    g, slot_map = G.from_workload(wl)
+    other = "CLASS" if classes == "PROG" else "PROG"
+    g.device = "cuda"
+    g._upload("cuda", [n for n in G.grid.ART_NAMES if n not in {other + x for x in ("_MAP", "_OFF", "_REC")}])
+    o = oracle_mod.from_workload(wl)
+    _check(g, o, wl.prefixes[:16], slot_map[wl.slots[0]])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 511, 513, 8191, 8192, 8193, 12000])
+def test_open_ids_up_to_and_past_the_list(G, oracle_mod, n):
+    """n tokens of two shifts and more ("a,b,", which every row leaves open)."""
+    text = "start S\ntoken ID /[a-z]+/\ntoken C \",\"\ntoken E \";\"\nS : L E ;\nL : L C ID | ID ;\n"
+    letters = [bytes([97 + i // 26 % 26, 97 + i % 26]) for i in range(676)]
+    many = [letters[i % 676] + b"," + letters[i // 676] + (b"," if i % 3 else b",,") for i in range(n)]
+    vocab = [bytes([b]) for b in range(256)] + many + [b""]
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos)
+    slot = g.add_lexicon({})
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
+    _check(g, o, [b"", b"q", b"q,", b"q;"], slot)
+
+
+# keyword statements: (statements, words of each) sets the size of the LR tables
+@pytest.mark.parametrize("statements,words", [(4, 3), (20, 6), (40, 6)])
+def test_tables_in_and_past_lds(G, oracle_mod, statements, words):
+    text, vocab = _statements(statements, words)
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos)
+    slot = g.add_lexicon({})
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
+    _check(g, o, [b"", b"k0 ", b"k1 w1", b"k1 w1 ( w1 ( ", b"k1 w1 (w1) w2 (k", b"k3"], slot)
+
+
+def _statements(n, words):
+    """n keyword statements of nested word groups, and a vocabulary over them."""
+    toks = "".join(f'token K{i} "k{i}"\n' for i in range(n)) + "".join(f'token W{i} "w{i}"\n' for i in range(words))
+    forms = " | ".join(f"K{i} " + " ".join(f"W{(i + j) % words} A{i}" for j in range(words - 1)) + " E" for i in range(n))
+    args = "".join(f"A{i} : LP S{i} RP | %empty ;\nS{i} : W{i % words} A{i} | K{i} ;\n" for i in range(n))
+    text = ("start P\n" + toks + 'token LP "("\ntoken RP ")"\ntoken E ";"\ntoken WS /[ ]+/ ignore\n'
+            "P : P F | F ;\nF : " + forms + " ;\n" + args)
+    vocab = [bytes([b]) for b in range(256)]
+    vocab += [f"k{i}".encode() for i in range(n)] + [f" w{i}".encode() for i in range(words)]
+    vocab += [f"k{i} w{j} (w{k}".encode() for i in range(0, n, 3) for j in range(words) for k in range(words)]
+    vocab += [f" w{j} (".encode() for j in range(words)] + [b") w1 ", b"))", b" ; k1 w1", b""]
+    return text, vocab
