@@ -2476,6 +2476,66 @@ __global__ __launch_bounds__(kBlock) void apply_kernel(const uint32_t* __restric
   }
 }
 
+// ------------------------------------------------------------- rolling hash
+// x of lane (me + k) % 4 of the quad, by DPP quad_perm.
+template <int K>
+__device__ __forceinline__ uint64_t quad_rot(uint64_t x) {
+  constexpr int ctrl = (K & 3) | ((K + 1) & 3) << 2 | ((K + 2) & 3) << 4 | ((K + 3) & 3) << 6;
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, ctrl, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), ctrl, 0xF, 0xF, true);
+  return (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32;
+}
+
+// node_hash by the four lanes of a quad, all with the same arguments: lane j
+// holds column j of BLAKE2b's 4 x 4 state, so the four G of a half round run
+// side by side and the rows are turned by lane moves for the diagonals.  Two of
+// the 16 message words are not zero; each is kept masked for each lane, and a
+// half round adds only where its schedule has one of the two.
+// (One hash is a serial chain of 24 G, about 1 us; by one lane, 96 of them took
+// 4.5 us: 32 rows of depth 30 hashed in 140 us.)
+__device__ __forceinline__ uint64_t node_hash4(uint64_t parent, uint32_t state, uint32_t sym) {
+  const uint32_t j = threadIdx.x & 3u;
+  const uint64_t m[2] = {parent, (uint64_t)state | (uint64_t)sym << 32};
+  uint64_t mine[2][4];
+#pragma unroll
+  for (int w = 0; w < 2; ++w)
+#pragma unroll
+    for (uint32_t l = 0; l < 4; ++l) mine[w][l] = m[w] & (0ull - (uint64_t)(j == l));
+  auto pick = [&](uint64_t x0, uint64_t x1, uint64_t x2, uint64_t x3) {
+    return j == 0 ? x0 : (j == 1 ? x1 : (j == 2 ? x2 : x3));
+  };
+  constexpr uint64_t h0 = kBlake2bIv[0] ^ 0x01010000ull ^ 16ull;  // digest length 16, no key, fanout 1, depth 1
+  uint64_t a = pick(h0, kBlake2bIv[1], kBlake2bIv[2], kBlake2bIv[3]);
+  uint64_t b = pick(kBlake2bIv[4], kBlake2bIv[5], kBlake2bIv[6], kBlake2bIv[7]);
+  uint64_t c = pick(kBlake2bIv[0], kBlake2bIv[1], kBlake2bIv[2], kBlake2bIv[3]);
+  uint64_t d = pick(kBlake2bIv[4] ^ 16ull, kBlake2bIv[5], ~kBlake2bIv[6], kBlake2bIv[7]);  // counter 16, final block
+#pragma unroll
+  for (int r = 0; r < 12; ++r) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {  // columns, then diagonals
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {  // a's two additions
+        a += b;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+          const int w = kBlake2bSigma[r % 10][8 * half + 2 * l + y];
+          if (w < 2) a += mine[w][l];
+        }
+        d = rotr64(d ^ a, y ? 16 : 32);
+        c += d;
+        b = rotr64(b ^ c, y ? 63 : 24);
+      }
+      b = half ? quad_rot<3>(b) : quad_rot<1>(b);
+      c = quad_rot<2>(c);
+      d = half ? quad_rot<1>(d) : quad_rot<3>(d);
+    }
+  }
+  const uint64_t v = a ^ c;  // lane 0: words 0 and 8
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0, 0xF, 0xF, true);
+  return h0 ^ ((uint64_t)lo | (uint64_t)hi << 32);
+}
+
 // ------------------------------------------------------------------ accept
 // The whole stack stk[0, d) as a read-only base for simulations: in LDS it
 // is the window, in global memory the pool.
@@ -2790,16 +2850,16 @@ __global__ __launch_bounds__(kBlock) void accept_kernel(Tables tb, const grid_co
     if (st != GRID_ROW_OK)  // a refused token leaves the row's input stack in its area
       for (uint32_t i = lo; i < d0; ++i) out_stk[i] = pool[cfg.stk_off + i];
   }
-  if (tid != 0) return;
-  if (st == GRID_ROW_OK && hash) {  // rolling hashes of the rewritten entries, each from its parent's
-    const uint32_t off = out.stk_off;
-    uint64_t h = hash[off + lo - 1];  // lo >= 1: the bottom entry is never popped
-    for (uint32_t i = lo; i < d; ++i) {
-      const uint32_t sv = fits ? (uint32_t)stk_l[i] : (uint32_t)out_stk[i];
-      h = node_hash(h, sv, tb.state_sym[sv]);
-      hash[off + i] = h;
+  if (s_st == GRID_ROW_OK && hash && tid < 4) {  // rolling hashes of the rewritten entries, each from its parent's
+    const uint32_t off = out.stk_off, top = s_d;
+    uint64_t hv = hash[off + s_lo - 1];  // s_lo >= 1: the bottom entry is never popped
+    for (uint32_t i = s_lo; i < top; ++i) {
+      const uint32_t sv = stk_l[i];
+      hv = node_hash4(hv, sv, tb.state_sym[sv]);
+      if (tid == 0) hash[off + i] = hv;
     }
   }
+  if (tid != 0) return;
   if (inplace && st != GRID_ROW_OK) {
     if (status) status[row] = st;
     return;
@@ -2816,20 +2876,33 @@ __global__ __launch_bounds__(kBlock) void accept_kernel(Tables tb, const grid_co
   if (status) status[row] = st;
 }
 
-// Rolling hash of every stack entry of every row (one thread per row: each
-// entry's hash needs its parent's): entry 0 is the root (hash 0), entry i > 0
-// hashes the one below it, its LR state and that state's accessing symbol.
+// Rolling hash of every stack entry of every row: entry 0 is the root (hash 0),
+// entry i > 0 hashes the one below it, its LR state and that state's accessing
+// symbol.  Four lanes per row, 16 rows per wave; each entry's hash needs its
+// parent's, so a row's time is its depth times one hash, and the next entries'
+// states and symbols are read while it runs.
 __global__ __launch_bounds__(64) void stack_hash_kernel(Tables tb, const grid_config* __restrict__ cfgs,
                                                        const uint16_t* __restrict__ pool, uint64_t* __restrict__ hash,
                                                        int B) {
-  const int row = (int)(blockIdx.x * 64u + threadIdx.x);
-  if (row >= B) return;
+  const int row = (int)(blockIdx.x * 16u + threadIdx.x / 4u);
+  if (row >= B) return;  // uniform over the four lanes
   const grid_config cfg = cfgs[row];
+  const uint32_t n = cfg.stk_depth;
+  const uint16_t* st = pool + cfg.stk_off;
+  uint64_t* out = hash + cfg.stk_off;
+  auto state = [&](uint32_t i) -> uint32_t { return i < n ? st[i] : kNoState; };
+  auto symbol = [&](uint32_t sv) -> uint32_t { return sv < (uint32_t)tb.NS ? tb.state_sym[sv] : kNoSymbol; };
+  const bool writes = (threadIdx.x & 3u) == 0u;
+  if (n && writes) out[0] = 0ull;
   uint64_t h = 0;
-  for (uint32_t i = 0; i < cfg.stk_depth; ++i) {
-    const uint32_t sv = pool[cfg.stk_off + i];
-    if (i > 0) h = node_hash(h, sv, sv < (uint32_t)tb.NS ? tb.state_sym[sv] : kNoSymbol);
-    hash[cfg.stk_off + i] = h;
+  uint32_t s0 = state(1), s1 = state(2), y0 = symbol(s0);
+  for (uint32_t i = 1; i < n; ++i) {
+    const uint32_t s2 = state(i + 2), y1 = symbol(s1);
+    h = node_hash4(h, s0, y0);
+    if (writes) out[i] = h;
+    s0 = s1;
+    s1 = s2;
+    y0 = y1;
   }
 }
 
@@ -3123,7 +3196,7 @@ extern "C" int grid_stack_hash(const grid_compiled* g, int32_t B, const grid_con
   Tables tb;
   const int rc = bind_tables(g, tb);
   if (rc != GRID_OK) return rc;
-  hipLaunchKernelGGL(stack_hash_kernel, dim3((unsigned)((B + 63) / 64)), dim3(64), 0, (hipStream_t)stream, tb, cfg_dev,
+  hipLaunchKernelGGL(stack_hash_kernel, dim3((unsigned)((B + 15) / 16)), dim3(64), 0, (hipStream_t)stream, tb, cfg_dev,
                      stack_pool_dev, stack_hash_dev, B);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(GRID_E_HIP, std::string("grid_stack_hash launch: ") + hipGetErrorString(e));
