@@ -2588,6 +2588,36 @@ __device__ int chain_shift(const ParseTabs<L>& pt, mptr<L, uint16_t> stk, uint32
   return -1;
 }
 
+// The same without commit, one lane's: the pushes go to the lane's own area tmp
+// of kAccLane entries; 3 when the chain needs a larger one.
+constexpr int kAccLane = 16;
+template <bool L, int MW>
+__device__ int chain_test(const ParseTabs<L>& pt, mptr<L, const uint16_t> stk, uint32_t d, uint32_t cap, uint32_t x,
+                          mptr<true, uint16_t> tmp) {
+  if (d >= cap) return -1;
+  const uint32_t w = x >> 5, bit = 1u << (x & 31);
+  uint32_t k = d, t = 0, s = stk[d - 1u];
+  for (int guard = 0; guard < kGuard; ++guard) {
+    const uint32_t a = action_of<L, MW>(pt, s, w, bit);
+    if (a >= kActShiftP) return a == kActShiftP ? 1 : 0;
+    const uint32_t len = a >> 16, dt = min(t, len);
+    if (len - dt >= k) return 0;
+    t -= dt;
+    k -= len - dt;
+    uint32_t sb = s;
+    if (len) {
+      if (t) sb = tmp[t - 1u];
+      else sb = stk[k - 1u];
+    }
+    s = goto_of<L>(pt, sb, a & 0xFFFFu);
+    if (s == kNoGoto) return 0;
+    if (t >= cap - d) return -1;
+    if (t >= (uint32_t)kAccLane) return 3;
+    tmp[t++] = (uint16_t)s;
+  }
+  return -1;
+}
+
 // The lexer tables an advance reads (global memory, or their LDS copies).
 struct LexPtrs {
   const uint16_t* dfa;
@@ -2598,25 +2628,48 @@ struct LexPtrs {
   const uint32_t* live;
 };
 
-struct AccLex {  // a row's lexer side: DFA state, lexicon node, pending lexeme
-  uint32_t q, lex, rem;
-  uint8_t head[8];
+// A row's lexer side: DFA state, lexicon node and its flags, pending lexeme
+// (length, first 8 bytes).
+struct AccLex {
+  uint32_t q, lex, flags, rem;
+  uint64_t head;
 };
 
-// One row's advance by token tok (section 6.1, per-token step 7) on the stack
-// stk[0, d) of capacity cap, with the LR tables pt; lo_mod falls to the
-// lowest stack index the advance rewrites (entries below it are unchanged).  The token's bytes go
-// through the lexer with maximal munch; a byte that kills the DFA emits the
-// pending lexeme as the highest-priority candidate that is ignored or shifts
-// and passes its category's lexicon, and a shifted terminal runs its reduce
-// chain on the stack.  The new pending lexeme must still complete to an
-// allowed or ignored terminal (Definition 2).  The end-of-sequence token is
-// accepted when the end-of-sequence gate holds (section 3.2).  Returns the
-// row status; with GRID_ROW_OK, d and lx are the new configuration's.
+// A token's bytes: the first kAccBytes in registers, the rest in the tail table.
+constexpr uint32_t kAccBytes = 24;
+struct AccToken {
+  uint64_t b0, b1, b2;
+  uint32_t n, chunk;  // length (0: special or empty), first overflow chunk
+  __device__ __forceinline__ uint32_t at(const Tables& tb, uint32_t i) const {
+    if (i >= kAccBytes) return reinterpret_cast<const uint8_t*>(tb.spell_tail + chunk)[i - kAccBytes];
+    return (uint32_t)(window8(b0, b1, b2, i) & 0xFFu);
+  }
+};
+
+// The lexicon nodes the token's bytes lead to, and their flags: entry
+// [o * kAccBytes + i] after bytes o..i from the trie's root, and, for o =
+// kAccBytes, after bytes 0..i from the pending lexeme's node.
+struct AccTrie {
+  uint32_t node[(kAccBytes + 1) * kAccBytes], flags[(kAccBytes + 1) * kAccBytes];
+};
+
+// One row's advance by token tok (section 6.1, per-token step 7), by one wave, on
+// the stack stk[0, d) of capacity cap, with the LR tables pt; lo_mod falls to the
+// lowest stack index the advance rewrites (entries below it are unchanged).  The
+// token's bytes go through the lexer with maximal munch; a byte that kills the DFA
+// emits the pending lexeme as the highest-priority candidate that is ignored or
+// shifts and passes its category's lexicon, and a shifted terminal runs its reduce
+// chain on the stack (lane 0).  The new pending lexeme must still complete to an
+// allowed or ignored terminal (Definition 2; a lane per terminal, the lowest that
+// does not fail decides, as if tried in order).  The end-of-sequence token is
+// accepted when the end-of-sequence gate holds (section 3.2).  Returns the row
+// status in every lane; with GRID_ROW_OK, d and lx (lane 0's) are the new
+// configuration's.
 template <bool L, int MW>
 __device__ __forceinline__ int advance_row(const Tables& tb, const LexPtrs lp, const ParseTabs<L>& pt, const Slot& sl,
-                           mptr<L, uint16_t> stk, uint32_t& d, uint32_t cap, int tok, AccLex& lx,
-                           uint32_t& lo_mod) {
+                           mptr<L, uint16_t> stk, uint32_t& d, uint32_t cap, int tok, const AccToken& tk,
+                           const AccTrie& trie, mptr<true, uint16_t> areas, AccLex& lx, uint32_t& lo_mod) {
+  const uint32_t lane = threadIdx.x & 63u;
   auto ignored = [&](int t) { return (lp.term_info[t] & 1u) != 0; };
   auto restricted_cat = [&](int t) -> int {  // category the row's lexicon restricts, or -1
     const uint32_t c = (lp.term_info[t] >> 8) & 0xFFu;
@@ -2626,14 +2679,14 @@ __device__ __forceinline__ int advance_row(const Tables& tb, const LexPtrs lp, c
   // above the stack, which stays as it is)?
   // 1 shift, 2 accept (the end of input), 0 error, -1 capacity
   auto shifts = [&](int t) -> int { return chain_shift<L, MW>(pt, stk, d, cap, t, false, lo_mod); };
-  // the pending lexeme's winner in state q (lexicon node lex), its reduce
-  // chain and shift applied to the stack when it is not ignored: -1 none,
-  // else the terminal; capacity problems surface as -2
+  // the pending lexeme's winner in state q, its reduce chain and shift applied to
+  // the stack when it is not ignored: -1 none, else the terminal; capacity
+  // problems surface as -2
   auto winner = [&]() -> int {
     for (uint32_t j = lp.acc_off[lx.q]; j < lp.acc_off[lx.q + 1]; ++j) {
       const int t = lp.acc_list[j];
       const int c = restricted_cat(t);
-      if (c >= 0 && !((lex_flags_of(tb, sl, lx.lex) >> (8 + c)) & 1u)) continue;
+      if (c >= 0 && !((lx.flags >> (8 + c)) & 1u)) continue;
       if (ignored(t)) return t;
       const int r = chain_shift<L, MW>(pt, stk, d, cap, t, true, lo_mod);
       if (r < 0) return -2;
@@ -2641,56 +2694,76 @@ __device__ __forceinline__ int advance_row(const Tables& tb, const LexPtrs lp, c
     }
     return -1;
   };
-  if (tok == tb.eos_id) {  // the configuration itself stays as it is
-    int ok = 0;
-    if (lx.rem == 0) {
-      ok = shifts(tb.T) == 2;
-    } else {
-      const int w = winner();
-      if (w == -2) return GRID_ROW_OVERFLOW;
-      if (w >= 0) ok = shifts(tb.T) == 2;
+  constexpr int kTrailing = -1;  // all bytes taken: the pending lexeme's test is left
+  auto bytes = [&]() -> int {
+    if (tok == tb.eos_id) {  // the configuration itself stays as it is
+      int ok = 0;
+      if (lx.rem == 0) {
+        ok = shifts(tb.T) == 2;
+      } else {
+        const int w = winner();
+        if (w == -2) return GRID_ROW_OVERFLOW;
+        if (w >= 0) ok = shifts(tb.T) == 2;
+      }
+      return ok ? GRID_ROW_FINISHED : GRID_ROW_NOT_VIABLE;
     }
-    return ok ? GRID_ROW_FINISHED : GRID_ROW_NOT_VIABLE;
-  }
-  const uint32_t su = tb.spell_of_id[tok];
-  if (su == 0xFFFFFFFFu) return GRID_ROW_NOT_VIABLE;  // special or empty token
-  const uint32_t b0 = tb.spell_off[su], n = tb.spell_off[su + 1] - b0;
-  for (uint32_t i = 0; i < n; ++i) {
-    const uint32_t b = tb.spell_bytes[b0 + i];
-    const int nq = lp.dfa[lx.q * tb.C + lp.bclass[b]];
-    if (nq != kDead) {
+    if (tk.n == 0) return GRID_ROW_NOT_VIABLE;  // special or empty token
+    uint32_t from = kAccBytes;                  // where the lexeme starts (kAccBytes: the pending one)
+    for (uint32_t i = 0; i < tk.n; ++i) {
+      const uint32_t b = tk.at(tb, i), bc = lp.bclass[b];
+      int nq = lp.dfa[lx.q * tb.C + bc];
+      if (nq == kDead) {  // b kills the pending lexeme: emit it
+        if (lx.rem == 0 || lp.acc_off[lx.q + 1] == lp.acc_off[lx.q]) return GRID_ROW_NOT_VIABLE;
+        const int w = winner();
+        if (w == -2) return GRID_ROW_OVERFLOW;
+        if (w < 0) return GRID_ROW_NOT_VIABLE;
+        nq = lp.dfa[kStart * tb.C + bc];
+        if (nq == kDead) return GRID_ROW_NOT_VIABLE;
+        lx.lex = 0;
+        lx.rem = 0;
+        lx.head = 0;
+        from = i;
+      }
       lx.q = (uint32_t)nq;
-      lx.lex = lex_child(tb, sl, lx.lex, b);
-      if (lx.rem < 8) lx.head[lx.rem] = (uint8_t)b;
+      if (i < kAccBytes) {
+        lx.lex = trie.node[from * kAccBytes + i];
+        lx.flags = trie.flags[from * kAccBytes + i];
+      } else {
+        lx.lex = lex_child(tb, sl, lx.lex, b);
+        lx.flags = lex_flags_of(tb, sl, lx.lex);
+      }
+      if (lx.rem < 8) lx.head = (lx.head & ~(0xFFull << (8u * lx.rem))) | (uint64_t)b << (8u * lx.rem);
       ++lx.rem;
-      continue;
     }
-    // b kills the pending lexeme: emit it
-    if (lx.rem == 0 || lp.acc_off[lx.q + 1] == lp.acc_off[lx.q]) return GRID_ROW_NOT_VIABLE;
-    const int w = winner();
-    if (w == -2) return GRID_ROW_OVERFLOW;
-    if (w < 0) return GRID_ROW_NOT_VIABLE;
-    const int q1 = lp.dfa[kStart * tb.C + lp.bclass[b]];
-    if (q1 == kDead) return GRID_ROW_NOT_VIABLE;
-    lx.q = (uint32_t)q1;
-    lx.lex = lex_child(tb, sl, 0u, b);
-    lx.rem = 1;
-    lx.head[0] = (uint8_t)b;
-    for (int k = 1; k < 8; ++k) lx.head[k] = 0;
-  }
-  if (lx.rem == 0) return GRID_ROW_OK;
+    return kTrailing;
+  };
+  int st = 0;
+  if (lane == 0) st = bytes();
+  st = __builtin_amdgcn_readfirstlane(st);
+  if (st != kTrailing) return st;
   // Definition 2 for the pending lexeme
-  const uint32_t* lv = lp.live + (size_t)lx.q * 8;
-  for (int wd = 0; wd < 8; ++wd) {
-    for (uint32_t bits = lv[wd]; bits != 0u; bits &= bits - 1u) {  // live terminals in id order
-      const int t = wd * 32 + __builtin_ctz(bits);
-      if (t >= tb.T) break;
+  const uint32_t q = __builtin_amdgcn_readfirstlane(lx.q), fl = __builtin_amdgcn_readfirstlane(lx.flags);
+  const uint32_t dd = __builtin_amdgcn_readfirstlane(d);
+  const uint32_t* lv = lp.live + (size_t)q * 8;
+  for (int g = 0; g < (tb.T + 63) / 64; ++g) {
+    const int t = g * 64 + (int)lane;
+    int r = 0;
+    if (t < tb.T && ((lv[t >> 5] >> (t & 31)) & 1u)) {
       const int c = restricted_cat(t);
-      if (c >= 0 && !((lex_flags_of(tb, sl, lx.lex) >> c) & 1u)) continue;
-      if (ignored(t)) return GRID_ROW_OK;
-      const int r = shifts(t);
-      if (r < 0) return GRID_ROW_OVERFLOW;
-      if (r == 1) return GRID_ROW_OK;
+      if (c < 0 || ((fl >> c) & 1u))
+        r = ignored(t) ? 1 : chain_test<L, MW>(pt, stk, dd, cap, (uint32_t)t, areas + lane * kAccLane);
+    }
+    uint64_t todo = __ballot(r != 0);
+    while (todo) {
+      const int f = __ffsll((unsigned long long)todo) - 1;
+      int rf = __builtin_amdgcn_readlane(r, f);
+      if (rf == 3) {  // its area was too small: above the stack, by lane 0
+        if (lane == 0) rf = shifts(g * 64 + f);
+        rf = __builtin_amdgcn_readfirstlane(rf);
+      }
+      if (rf < 0) return GRID_ROW_OVERFLOW;
+      if (rf == 1) return GRID_ROW_OK;
+      todo &= todo - 1ull;
     }
   }
   return GRID_ROW_NOT_VIABLE;
@@ -2726,9 +2799,15 @@ constexpr uint32_t kAccStack = 8192;  // stack entries an accept workgroup keeps
 
 __host__ __device__ inline uint32_t accept_stack_cap(uint32_t cap) { return cap < kAccStack ? cap : kAccStack; }
 
-// Device incremental advance: one workgroup per row.  The LR tables and the
-// row's stack are staged in LDS and one thread advances the row there (the
-// chain of dependent table reads is the cost, so every read is an LDS read).
+// Device incremental advance: one workgroup per row.  The LR tables, the lexer
+// tables and the row's stack are staged in LDS and one wave advances the row
+// there (the chain of dependent table reads is the cost, so every read is an LDS
+// read).  While the other waves stage, wave 0 reads the token's bytes and follows
+// the lexicon trie from every byte it may start a lexeme at, a lane each, and
+// wave 1 copies the stack: read by the advancing thread in turn, a byte's trie
+// node was a global read each.  256 DML rows out of place take 13.2 us (15.7 with
+// one thread reading the token and the trie after the staging and trying the
+// trailing lexeme's terminals in turn).
 // Every row's output is self-contained, whatever its status: the input stack
 // is copied to the row's own area pool_out + b * cap (checking every entry is
 // an LR state) and the configuration written to cfg_out points there; an
@@ -2747,16 +2826,46 @@ __host__ __device__ inline uint32_t accept_stack_cap(uint32_t cap) { return cap 
 // hash per pushed node).  A row that is not advanced keeps its stack and
 // configuration untouched; a stack too deep for the LDS area is reported as
 // an overflow (the out-of-place call handles it).
+constexpr int kAccThreads = 512;
+constexpr uint32_t kAccFirst = 1024;  // stack entries wave 1 copies alone
 template <int MW>
-__global__ __launch_bounds__(kBlock) void accept_kernel(Tables tb, const grid_config* cfgs, const uint16_t* pool,
-                                                        const int32_t* __restrict__ tokens, grid_config* cfg_out,
-                                                        uint16_t* pool_out, uint64_t* hash, uint32_t cap,
-                                                        int32_t* status, int use_lds, int use_lex, int inplace,
-                                                        int tok_stride) {
+__global__ __launch_bounds__(kAccThreads) void accept_kernel(Tables tb, const grid_config* cfgs, const uint16_t* pool,
+                                                             const int32_t* __restrict__ tokens, grid_config* cfg_out,
+                                                             uint16_t* pool_out, uint64_t* hash, uint32_t cap,
+                                                             int32_t* status, int use_lds, int use_lex, int inplace,
+                                                             int tok_stride) {
   extern __shared__ __align__(16) uint8_t alds[];
   __shared__ int s_st, s_bad;
   __shared__ uint32_t s_d, s_lo;
-  const int row = (int)blockIdx.x, tid = (int)threadIdx.x;
+  __shared__ AccTrie trie;
+  __shared__ uint16_t areas[64 * kAccLane];
+  const int row = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const ParseLds PL = prologue_parse_lds(tb);
+  const uint32_t lcap = accept_stack_cap(cap);
+  const mptr<true, uint16_t> stk_l = in_mem<true>((uint16_t*)(alds + PL.total));
+  // the tables by waves 2 and up; the lexer's too when they fit: every byte step
+  // is then an LDS read
+  const AccLexLds XL = accept_lex_lds(tb);
+  uint8_t* xl = alds + PL.total + pad16(lcap * 2u);
+  LexPtrs lp{tb.dfa, tb.bclass, tb.term_info, tb.acc_off, tb.acc_list, tb.live};
+  if (use_lds && use_lex)
+    lp = LexPtrs{(const uint16_t*)(xl + XL.dfa), xl + XL.bclass, (const uint32_t*)(xl + XL.tinfo),
+                 (const uint32_t*)(xl + XL.acc_off), xl + XL.acc_list, (const uint32_t*)(xl + XL.live)};
+  if (use_lds && wave >= 2) {
+    const int t2 = tid - 128, nt = kAccThreads - 128;
+    const StageRegion rg[4] = {parse_region(tb, alds, PL, 0), parse_region(tb, alds, PL, 1),
+                               parse_region(tb, alds, PL, 2), parse_region(tb, alds, PL, 3)};
+    const uint32_t first = dma_regions<4>(rg, t2, nt);
+    if (use_lex) {
+      const StageRegion rx[6] = {{(const uint8_t*)tb.dfa, xl + XL.dfa, (uint32_t)(tb.S * tb.C * 2)},
+                                 {tb.bclass, xl + XL.bclass, 256u},
+                                 {(const uint8_t*)tb.term_info, xl + XL.tinfo, (uint32_t)tb.T * 4u},
+                                 {(const uint8_t*)tb.acc_off, xl + XL.acc_off, (uint32_t)(tb.S + 1) * 4u},
+                                 {tb.acc_list, xl + XL.acc_list, (uint32_t)tb.n_acc},
+                                 {(const uint8_t*)tb.live, xl + XL.live, (uint32_t)tb.S * 32u}};
+      dma_regions<6>(rx, t2, nt, first);
+    }
+  }
   const grid_config cfg = cfgs[row];
   const int tok = tokens[(size_t)row * tok_stride];
   const uint32_t d0 = cfg.stk_depth;
@@ -2764,92 +2873,109 @@ __global__ __launch_bounds__(kBlock) void accept_kernel(Tables tb, const grid_co
   const bool copyable = d0 >= 1 && d0 <= cap && (!inplace || cfg.stk_off == (uint32_t)row * cap);  // uniform
   bool bad = !copyable || cfg.q >= (uint32_t)tb.S || cfg.q == (uint32_t)kDead || cfg.slot >= (uint32_t)tb.n_slots ||
              tok < 0 || tok >= tb.V;
+  const bool fits = use_lds && d0 < lcap;  // uniform
   Slot sl{};
-  if (!bad) {
+  AccToken tk{};
+  uint32_t flags0 = 0;
+  if (wave == 0 && !bad) {
     sl = load_slot(tb, (int)cfg.slot);
     bad = cfg.lexnode != kNoLex && cfg.lexnode >= sl.nodes;
   }
-  if (tid == 0) s_bad = 0;
-  const ParseLds PL = prologue_parse_lds(tb);
-  const uint32_t lcap = accept_stack_cap(cap);
-  const mptr<true, uint16_t> stk_l = in_mem<true>((uint16_t*)(alds + PL.total));
-  if (use_lds && !bad) {
-    const StageRegion rg[4] = {parse_region(tb, alds, PL, 0), parse_region(tb, alds, PL, 1),
-                               parse_region(tb, alds, PL, 2), parse_region(tb, alds, PL, 3)};
-    dma_regions<4>(rg, tid, kBlock);
-  }
-  // the lexer tables too when they fit: every byte step is then an LDS read
-  const AccLexLds XL = accept_lex_lds(tb);
-  uint8_t* xl = alds + PL.total + pad16(lcap * 2u);
-  LexPtrs lp{tb.dfa, tb.bclass, tb.term_info, tb.acc_off, tb.acc_list, tb.live};
-  if (use_lds && use_lex && !bad) {
-    const StageRegion rg[6] = {{(const uint8_t*)tb.dfa, xl + XL.dfa, (uint32_t)(tb.S * tb.C * 2)},
-                               {tb.bclass, xl + XL.bclass, 256u},
-                               {(const uint8_t*)tb.term_info, xl + XL.tinfo, (uint32_t)tb.T * 4u},
-                               {(const uint8_t*)tb.acc_off, xl + XL.acc_off, (uint32_t)(tb.S + 1) * 4u},
-                               {tb.acc_list, xl + XL.acc_list, (uint32_t)tb.n_acc},
-                               {(const uint8_t*)tb.live, xl + XL.live, (uint32_t)tb.S * 32u}};
-    dma_regions<6>(rg, tid, kBlock, 1000u);
-    lp = LexPtrs{(const uint16_t*)(xl + XL.dfa), xl + XL.bclass, (const uint32_t*)(xl + XL.tinfo),
-                 (const uint32_t*)(xl + XL.acc_off), xl + XL.acc_list, (const uint32_t*)(xl + XL.live)};
-  }
-  const bool fits = use_lds && !bad && d0 < lcap;  // uniform
-  dma_wait();
-  __syncthreads();  // s_bad is cleared, the tables are in LDS
-  if (copyable) {  // the input stack to the row's output area (and to LDS), entries checked
-    for (uint32_t i = (uint32_t)tid; i < d0; i += kBlock) {
-      const uint16_t v = pool[cfg.stk_off + i];
-      if (v >= (uint32_t)tb.NS) s_bad = 1;
-      if (!inplace) out_stk[i] = v;
-      if (fits) stk_l[i] = v;
+  if (wave == 0 && !bad) {
+    const uint32_t su = tb.spell_of_id[tok];
+    if (su != 0xFFFFFFFFu) {
+      const uint4 rk = tb.spell_rec[su], tl = tb.spell_tail[su];
+      tk.n = rk.w & 0xFFu;
+      tk.chunk = rk.w >> 8;
+      tk.b0 = (uint64_t)rk.x | (uint64_t)rk.y << 32;
+      if (tk.n > 8) {
+        tk.b1 = (uint64_t)tl.x | (uint64_t)tl.y << 32;
+        tk.b2 = (uint64_t)tl.z | (uint64_t)tl.w << 32;
+      }
+    }
+    flags0 = lex_flags_of(tb, sl, cfg.lexnode);
+    const uint32_t n = min(tk.n, kAccBytes);
+    if (lane <= (int)kAccBytes) {  // lane o follows the trie from byte o, lane kAccBytes from the pending node
+      uint32_t node = lane < (int)kAccBytes ? 0u : cfg.lexnode;
+      for (uint32_t i = lane < (int)kAccBytes ? (uint32_t)lane : 0u; i < n; ++i) {
+        node = lex_child(tb, sl, node, (uint32_t)(window8(tk.b0, tk.b1, tk.b2, i) & 0xFFu));
+        trie.node[lane * kAccBytes + i] = node;
+        trie.flags[lane * kAccBytes + i] = lex_flags_of(tb, sl, node);
+      }
     }
   }
-  __syncthreads();
-  bad = bad || s_bad != 0;  // uniform
+  bool foreign = false;  // an entry that is no LR state
+  auto copy = [&](uint32_t i) {  // the input stack to the row's output area and to LDS, entries checked
+    const uint16_t v = pool[cfg.stk_off + i];
+    foreign = foreign || v >= (uint32_t)tb.NS;
+    if (!inplace) out_stk[i] = v;
+    if (fits) stk_l[i] = v;
+  };
+  if (wave == 1) {
+    if (copyable)
+      for (uint32_t i = (uint32_t)lane; i < min(d0, kAccFirst); i += 64u) copy(i);
+    foreign = __any(foreign);
+    if (lane == 0) s_bad = foreign ? 1 : 0;
+  }
+  dma_wait();
+  __syncthreads();  // the tables and the stack's first entries are in LDS
+  if (copyable && d0 > kAccFirst) {  // uniform
+    for (uint32_t i = kAccFirst + (uint32_t)tid; i < d0; i += kAccThreads) copy(i);
+    if (foreign) s_bad = 1;
+    __syncthreads();
+  }
   grid_config out = cfg;
   if (!inplace) {
     if (copyable) out.stk_off = (uint32_t)row * cap;
     else out.stk_depth = 0;
   }
-  if (bad) {
-    if (tid == 0) {
-      if (!inplace) cfg_out[row] = out;
-      if (status) status[row] = GRID_ROW_BAD_CONFIG;
-    }
-    return;
-  }
-  AccLex lx;
-  lx.q = cfg.q;
-  lx.lex = cfg.lexnode;
-  lx.rem = (cfg.flags & 1u) ? 0u : cfg.rem_len;
-  for (int k = 0; k < 8; ++k) lx.head[k] = lx.rem > 0 ? cfg.rem_head[k] : 0;
   int st = -1;  // -1: not advanced in LDS
   uint32_t d = d0, lo = d0;
-  if (tid == 0) {
-    if (fits) {
-      st = advance_row<true, MW>(tb, lp, lds_parse(tb, alds, PL), sl, stk_l, d, lcap, tok, lx, lo);
-      if (st == GRID_ROW_OVERFLOW && lcap < cap) st = -1;
+  AccLex lx{};
+  if (wave == 0) {
+    uint64_t head0 = 0;
+    for (int k = 0; k < 8; ++k) head0 |= (uint64_t)cfg.rem_head[k] << (8 * k);
+    auto start = [&]() {
+      lx.q = cfg.q;
+      lx.lex = cfg.lexnode;
+      lx.flags = flags0;
+      lx.rem = (cfg.flags & 1u) ? 0u : cfg.rem_len;
+      lx.head = lx.rem > 0 ? head0 : 0ull;
+      d = d0;
+      lo = d0;
+    };
+    if (bad || s_bad) {
+      st = GRID_ROW_BAD_CONFIG;
+    } else {
+      const mptr<true, uint16_t> ar = in_mem<true>(areas);
+      if (fits) {
+        start();
+        st = advance_row<true, MW>(tb, lp, lds_parse(tb, alds, PL), sl, stk_l, d, lcap, tok, tk, trie, ar, lx, lo);
+        if (st == GRID_ROW_OVERFLOW && lcap < cap) st = -1;
+      }
+      if (inplace && st == -1) st = GRID_ROW_OVERFLOW;  // in place, only the LDS route
+      if (st == -1) {  // the global route, from the start, on the output copy
+        start();
+        const LexPtrs lg{tb.dfa, tb.bclass, tb.term_info, tb.acc_off, tb.acc_list, tb.live};
+        st = advance_row<false, MW>(tb, lg, global_parse(tb), sl, in_mem<false>(out_stk), d, cap, tok, tk, trie, ar, lx, lo);
+        if (lane == 0) {
+          if (st != GRID_ROW_OK)  // a refused token leaves the row's input stack in its area
+            for (uint32_t i = lo; i < d0; ++i) out_stk[i] = pool[cfg.stk_off + i];
+          s_st = -1;
+        }
+      } else if (lane == 0) {
+        s_st = st;
+      }
     }
-    if (inplace && st == -1) st = GRID_ROW_OVERFLOW;  // in place, only the LDS route
-    s_st = st;
-    s_d = d;
-    s_lo = lo;
+    if (lane == 0) {
+      if (st == GRID_ROW_BAD_CONFIG) s_st = st;
+      s_d = d;
+      s_lo = lo;
+    }
   }
   __syncthreads();
-  if (s_st == GRID_ROW_OK) {  // the entries the advance rewrote
-    for (uint32_t i = s_lo + (uint32_t)tid; i < s_d; i += kBlock) out_stk[i] = stk_l[i];
-  } else if (s_st == -1 && tid == 0) {  // the global route, from the start, on the output copy
-    lx.q = cfg.q;
-    lx.lex = cfg.lexnode;
-    lx.rem = (cfg.flags & 1u) ? 0u : cfg.rem_len;
-    for (int k = 0; k < 8; ++k) lx.head[k] = lx.rem > 0 ? cfg.rem_head[k] : 0;
-    d = d0;
-    lo = d0;
-    const LexPtrs lg{tb.dfa, tb.bclass, tb.term_info, tb.acc_off, tb.acc_list, tb.live};
-    st = advance_row<false, MW>(tb, lg, global_parse(tb), sl, out_stk, d, cap, tok, lx, lo);
-    if (st != GRID_ROW_OK)  // a refused token leaves the row's input stack in its area
-      for (uint32_t i = lo; i < d0; ++i) out_stk[i] = pool[cfg.stk_off + i];
-  }
+  if (s_st == GRID_ROW_OK)  // the entries the advance rewrote
+    for (uint32_t i = s_lo + (uint32_t)tid; i < s_d; i += kAccThreads) out_stk[i] = stk_l[i];
   if (s_st == GRID_ROW_OK && hash && tid < 4) {  // rolling hashes of the rewritten entries, each from its parent's
     const uint32_t off = out.stk_off, top = s_d;
     uint64_t hv = hash[off + s_lo - 1];  // s_lo >= 1: the bottom entry is never popped
@@ -2870,7 +2996,7 @@ __global__ __launch_bounds__(kBlock) void accept_kernel(Tables tb, const grid_co
     out.q = (uint16_t)lx.q;
     out.flags = lx.rem == 0 ? 1u : 0u;
     out.rem_len = lx.rem;
-    for (int k = 0; k < 8; ++k) out.rem_head[k] = lx.head[k];
+    for (int k = 0; k < 8; ++k) out.rem_head[k] = (uint8_t)(lx.head >> (8 * k));
   }
   cfg_out[row] = out;
   if (status) status[row] = st;
@@ -3293,7 +3419,7 @@ static int accept_call(const grid_compiled* g, int32_t B, const grid_config* cfg
                               : (tb.tw == 4 ? (const void*)accept_kernel<4> : (const void*)accept_kernel<8>);
   if (!raise_lds(fn, lds)) return fail(GRID_E_HIP, "grid_accept: cannot raise the LDS limit");
   hipStream_t s = (hipStream_t)stream;
-  const dim3 grid((unsigned)B), block(kBlock);
+  const dim3 grid((unsigned)B), block(kAccThreads);
   if (tb.tw == 2)
     hipLaunchKernelGGL(accept_kernel<2>, grid, block, lds, s, tb, cfg_dev, stack_pool_dev, token_dev, cfg_out_dev,
                        stack_out_dev, hash_dev, stack_cap, status_dev, use_lds, use_lex, inplace, tok_stride);

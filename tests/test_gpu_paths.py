@@ -82,3 +82,47 @@ def _statements(n, words):
     vocab += [f"k{i} w{j} (w{k}".encode() for i in range(0, n, 3) for j in range(words) for k in range(words)]
     vocab += [f" w{j} (".encode() for j in range(words)] + [b") w1 ", b"))", b" ; k1 w1", b""]
     return text, vocab
+
+
+# stacks whose entries one wave copies, exactly and with one more; token lengths
+# within and past the bytes a token keeps in registers; a chain of more pushes than
+# a lane's area; a capacity the stack just fits, and one too small
+@pytest.mark.parametrize("depth", [1, 1020, 1024, 1025, 1500])
+@pytest.mark.parametrize("cap", [1023, 4096])
+def test_advance_edges(G, oracle_mod, depth, cap):
+    nulls = " ".join(f"Z{i}" for i in range(20))
+    text = ("start S\ntoken NAME /[a-z]+/ category\ntoken LP \"(\"\ntoken X /X+/\ntoken DOT \".\"\n"
+            + "".join(f"token Y{i} \"Y{i}y\"\n" for i in range(20))
+            + f"S : LP S | E ;\nE : NAME | E DOT NAME | {nulls} X ;\n"
+            + "".join(f"Z{i} : %empty | Y{i} ;\n" for i in range(20)))
+    words = ["a", "ab", "abc" * 3, "q" * 23, "q" * 24, "q" * 25, "q" * 40, "q" * 24 + "rs"]
+    toks = [w.encode() for w in words] + [b"ab.", b".ab", b"abc.ab.a", b"." + b"q" * 23, b"." + b"q" * 24, b"q" * 30,
+                                          b"X", b"XX", b"X" * 30, b"((", b"(a.", b"zz", b"q" * 41, b"a.zz", b".X"]
+    vocab = [bytes([b]) for b in range(256)] + [t for t in toks if len(t) > 1] + [b""]
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos)
+    slot = g.add_lexicon({"NAME": words})
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {"NAME": words}, vocab, [eos], eos)
+    base = b"(" * max(0, depth - 2)
+    rows = [(base + w, t) for w in (b"", b"a", b"qqq", b"ab.") for t in toks]
+    cfgs, pool = g.configs([w for w, _ in rows], [slot] * len(rows))
+    ids = torch.tensor([vocab.index(t) for _, t in rows], dtype=torch.int32, device="cuda")
+    c2, p2, st = g.accept(*g.configs_to_device(cfgs, pool), ids, len(rows), cap)
+    torch.cuda.synchronize()
+    out, area, st = c2.cpu().numpy().view(G.CONFIG_DTYPE), p2.cpu().numpy().view(np.uint16), st.cpu().numpy()
+    for r, (w, t) in enumerate(rows):
+        at = cfgs[r]
+        if int(at["stk_depth"]) > cap:
+            assert st[r] == G.ROW_BAD_CONFIG and out[r]["stk_depth"] == 0
+            continue
+        if st[r] == G.ROW_OVERFLOW:  # only where the chain's pushes come near the capacity
+            assert int(at["stk_depth"]) + 24 > cap, (r, t)
+            want, stack = g.config(w, slot)
+        else:
+            assert (st[r] == G.ROW_OK) == bool(o.viable(w + t)), (r, w[-8:], t, int(st[r]))
+            want, stack = g.config(w + t if st[r] == G.ROW_OK else w, slot)
+        for f in ("q", "lexnode", "flags", "rem_len", "slot"):
+            assert int(out[r][f]) == int(want[f]), (r, f, w[-8:], t)
+        assert bytes(out[r]["rem_head"]) == bytes(want["rem_head"]), (r, t)
+        assert np.array_equal(area[r * cap:r * cap + len(stack)], stack) and int(out[r]["stk_depth"]) == len(stack), (r, t)
