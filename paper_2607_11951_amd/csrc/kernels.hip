@@ -2033,6 +2033,71 @@ __device__ __forceinline__ uint32_t walk_token(const WalkView<MW, L>& wv, uint4 
   return any ? kWalkTrail : kVerdictReject;
 }
 
+// The trailing lexemes a wave's walks left (lanes with todo): does any terminal of
+// the lane's set X shift from the lane's stack?  The (lane, terminal) pairs of all
+// lanes are dealt to the 64 lanes in turn, so a round runs 64 chains side by side
+// whichever walks they belong to.  (A round per walk took 4 us of a wave's 13 at
+// 32 DML rows, up to 15 in the slowest.)
+template <int MW, bool L>
+__device__ __forceinline__ bool trail_pairs(const WalkView<MW, L>& wv, bool todo, const uint32_t (&X)[MW], uint32_t k,
+                                            uint32_t m, mptr<true, const uint16_t> base) {
+  const int lane = threadIdx.x & 63;
+  uint32_t cnt = 0;
+  if (todo) {
+#pragma unroll
+    for (int w = 0; w < MW; ++w) cnt += (uint32_t)__popc(X[w]);
+  }
+  uint32_t incl = cnt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t x = __shfl_up(incl, d);
+    if (lane >= d) incl += x;
+  }
+  const uint32_t excl = incl - cnt, all = __builtin_amdgcn_readlane(incl, 63);
+  bool ok = false;
+  for (uint32_t p0 = 0; p0 < all; p0 += 64) {  // uniform
+    const uint32_t p = p0 + (uint32_t)lane;
+    int src = 0;  // the first lane whose pairs end after p
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+      if ((uint32_t)__shfl(incl, src + d - 1) <= p) src += d;
+    src &= 63;
+    uint32_t j = p - (uint32_t)__shfl(excl, src), word = 0, at = 0;
+    bool found = false;
+#pragma unroll
+    for (int w = 0; w < MW; ++w) {  // the set's j-th terminal: its word
+      const uint32_t x = (uint32_t)__shfl(X[w], src), c = (uint32_t)__popc(x);
+      const bool here = !found && j < c;
+      word = here ? x : word;
+      at = here ? (uint32_t)w * 32u : at;
+      j -= found || here ? 0u : c;
+      found = found || here;
+    }
+#pragma unroll
+    for (uint32_t h = 16; h >= 1; h >>= 1) {  // and its bit
+      const uint32_t low = word & ((1u << h) - 1u), c = (uint32_t)__popc(low);
+      const bool up = j >= c;
+      j -= up ? c : 0u;
+      word = up ? word >> h : low;
+      at += up ? h : 0u;
+    }
+    const uint32_t sk = (uint32_t)__shfl(k, src), sm = (uint32_t)__shfl(m, src);
+    uint32_t a = 0;
+    if (p < all) {
+      const ChainStack st{wv.pool, wv.win, wv.lo, sk, base + src * kFastLane, sm};
+      uint32_t n = sk + sm - 1u, sv = st.at(n);
+      bool moved = false;
+      a = lr_chain<L>(wv.lt, st, at, n, sv, moved);
+    }
+    const uint64_t hit = __ballot(a != 0u);
+    // this lane's pairs of the round: [excl, incl) less p0
+    const uint32_t b0 = excl > p0 ? min(excl - p0, 64u) : 0u, b1 = incl > p0 ? min(incl - p0, 64u) : 0u;
+    const uint64_t below1 = b1 >= 64u ? ~0ull : (1ull << b1) - 1ull, below0 = b0 >= 64u ? ~0ull : (1ull << b0) - 1ull;
+    ok = ok || (hit & below1 & ~below0) != 0ull;
+  }
+  return ok;
+}
+
 // Sum of v over the threads below this one (workgroup of kResThreads), and the
 // total; sums holds a word per wave.  Every thread calls it.
 __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* sums, uint32_t* total) {
@@ -2323,25 +2388,9 @@ __global__ __launch_bounds__(kResThreads) void residue_kernel(Tables tb, const u
           lx.lexnode = h.lexnode;
           v = walk_token<MW, Full>(wv, rec, lx, rk.w >> 8, base + lane * kFastLane, cap, k, m, X);
         }
-        // a trailing lexeme past the kept stacks: the wave tries its terminals
-        // together, one lane each
-        for (uint64_t todo = __ballot(v == kWalkTrail); todo; todo &= todo - 1ull) {
-          const int src = __ffsll((unsigned long long)todo) - 1;
-          const uint32_t sk = __builtin_amdgcn_readlane(k, src), sm = __builtin_amdgcn_readlane(m, src);
-          const ChainStack st{wv.pool, wv.win, wv.lo, sk, base + src * kFastLane, sm};
-          bool ok = false;
-#pragma unroll
-          for (int w = 0; w < MW; w += 2) {
-            const uint32_t x0 = __builtin_amdgcn_readlane(X[w], src), x1 = __builtin_amdgcn_readlane(X[w + 1], src);
-            if ((x0 | x1) == 0u || ok) continue;  // uniform
-            uint32_t n = sk + sm - 1u, a = 0;
-            uint32_t sv = st.at(n);
-            bool moved = false;
-            if (((lane < 32 ? x0 : x1) >> (lane & 31)) & 1u)
-              a = lr_chain<Full>(wv.lt, st, (uint32_t)(w * 32 + lane), n, sv, moved);
-            ok = __any(a != 0u);
-          }
-          if (lane == src) v = ok ? kVerdictAllow : kVerdictReject;
+        if (__any(v == kWalkTrail)) {  // trailing lexemes past the kept stacks
+          const bool ok = trail_pairs<MW, Full>(wv, v == kWalkTrail, X, k, m, base);
+          if (v == kWalkTrail) v = ok ? kVerdictAllow : kVerdictReject;
         }
         if (in) {
           if (v == kVerdictAllow) {

@@ -126,3 +126,22 @@ def test_advance_edges(G, oracle_mod, depth, cap):
             assert int(out[r][f]) == int(want[f]), (r, f, w[-8:], t)
         assert bytes(out[r]["rem_head"]) == bytes(want["rem_head"]), (r, t)
         assert np.array_equal(area[r * cap:r * cap + len(stack)], stack) and int(out[r]["stk_depth"]) == len(stack), (r, t)
+
+
+@pytest.mark.parametrize("keywords", [1, 2, 33, 64, 65, 150])
+def test_many_terminals_of_a_trailing_lexeme(G, oracle_mod, keywords):
+    """Tokens whose trailing lexeme, past two shifts, begins every keyword, only
+    every third of which fits there."""
+    text = "start S\ntoken ID /[a-j]+/\ntoken C \",\"\ntoken B \"!\"\n"
+    text += "".join(f'token K{i} "k{i:03d}"\n' for i in range(keywords))
+    text += "S : I | S C I ;\nI : ID | B Q" + "".join(f" | K{i}" for i in range(0, keywords, 3)) + " ;\n"
+    text += "Q : ID" + "".join(f" | K{i}" for i in range(keywords)) + " ;\n"
+    heads = [b"a,b,", b",b,", b"a,", b"c,!", b"!a,", b"!c,d,!", b"a,!b,"]
+    tails = [b"k", b"k0", b"k00", b"k01", b"k002", b"k12", b"k149", b"ka", b"!k0", b"!k1"]
+    vocab = [bytes([b]) for b in range(256)] + [h + t for h in heads for t in tails] + [b""]
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos)
+    slot = g.add_lexicon({})
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
+    _check(g, o, [b"", b"a", b"a,", b"!", b"!k", b"a,!a", b"k"], slot)
