@@ -691,13 +691,17 @@ __device__ inline uint64_t low_bytes(uint64_t w, uint32_t n) { return n >= 8 ? w
 // stride table).
 __device__ __forceinline__ uint32_t lex_flags_bytes(const Tables& tb, const Slot& sl, uint64_t b0, uint64_t b1,
                                                     uint64_t b2, uint32_t len) {
-  if (len <= 8) return lexp_find(tb, sl, low_bytes(b0, len), len).x;
-  uint32_t node = lexp_find(tb, sl, b0, 8).y;
-  if (node == kNoLex) return 0u;
-  if (len <= 16) return lexs_find(tb, sl, node, low_bytes(b1, len - 8), len - 8).x;
-  node = lexs_find(tb, sl, node, b1, 8).y;
-  if (node == kNoLex) return 0u;
-  return lexs_find(tb, sl, node, low_bytes(b2, len - 16), len - 16).x;
+  uint32_t n = min(len, 8u);
+  uint2 f = lexp_find(tb, sl, low_bytes(b0, n), n);  // (flags, node)
+  while (len > 8u) {                                 // eight more bytes a stride
+    if (f.y == kNoLex) return 0u;
+    len -= 8u;
+    b0 = b1;
+    b1 = b2;
+    n = min(len, 8u);
+    f = lexs_find(tb, sl, f.y, low_bytes(b0, n), n);
+  }
+  return f.x;
 }
 
 __device__ inline bool bit_of(const uint32_t* s, int t) { return (s[t >> 5] >> (t & 31)) & 1u; }
@@ -1828,26 +1832,6 @@ struct LexLane {
   uint64_t rem;         // pending bytes (first 8)
   uint32_t rem_len, lexnode;
   uint32_t tf;          // token-flag entry
-  __device__ __forceinline__ uint32_t span(uint32_t o, uint32_t e, bool pending) const {
-    if (e > 24) return kLexOut;
-    if (pending && rem_len > 0) {
-      if (rem_len > 8) {  // continue from the pending lexeme's node
-        uint32_t node = lexnode;
-        for (uint32_t i = 0; i < e && node != kNoLex; ++i)
-          node = lex_child(*tb, sl, node, (uint32_t)(window8(b0, b1, b2, i) & 0xFFu));
-        return lex_flags_of(*tb, sl, node);
-      }
-      const uint32_t len = rem_len + e;
-      if (len > 24) return kLexOut;
-      const uint32_t s = 8u * rem_len;  // 8..64 bits: the token's bytes move up by rem_len
-      const uint64_t c0 = rem | (s < 64 ? b0 << s : 0ull);
-      const uint64_t c1 = (b0 >> (64 - s)) | (s < 64 ? b1 << s : 0ull);
-      const uint64_t c2 = (b1 >> (64 - s)) | (s < 64 ? b2 << s : 0ull);
-      return lex_flags_bytes(*tb, sl, c0, c1, c2, len);
-    }
-    return lex_flags_bytes(*tb, sl, window8(b0, b1, b2, o), window8(b0, b1, b2, o + 8), window8(b0, b1, b2, o + 16),
-                           e - o);
-  }
 };
 
 // What a byte walk reads besides the row's sets.
@@ -1890,6 +1874,9 @@ constexpr uint32_t kWalkFull = 5;   // the stack area is too small
 // by their reduce chains, and the first that shifts is committed -- no allowed
 // set is needed until the trailing lexeme, whose terminals X are left to the
 // whole wave (see residue_kernel).
+// (The lookup of a lexeme's flags appears here four times and is kept small: with
+// the strides and the two placings of the bytes written out it made the kernel 40 %
+// larger, past what the instruction cache holds, and every call 2 to 5 % slower.)
 template <int MW, bool L>
 __device__ __forceinline__ uint32_t walk_token(const WalkView<MW, L>& wv, uint4 rec, const LexLane& lex, uint32_t chunk,
                                                mptr<true, uint16_t> ov, uint32_t cap, uint32_t& k, uint32_t& m,
@@ -1911,10 +1898,20 @@ __device__ __forceinline__ uint32_t walk_token(const WalkView<MW, L>& wv, uint4 
   };
   // lexicon flags of bytes [o, e) (with the pending bytes before them)
   auto flags = [&](uint32_t e) -> uint32_t {
-    const bool cont = pending && lex.rem_len > 0;
+    const bool cont = pending && lex.rem_len > 0;  // (then o is 0)
     if (!cont && o <= 1u) return (lex.tf >> (16u * o)) & 0xFFFFu;  // the token-flag table
-    const uint32_t f = lex.span(o, e, pending);
-    if (f != kLexOut) return f;
+    const uint32_t len = e - o + (cont ? lex.rem_len : 0u);
+    if (e <= 24u && len <= 24u && !(cont && lex.rem_len > 8u)) {  // the prefix and stride tables
+      const uint32_t sh = 8u * lex.rem_len;  // the pending bytes go before: 8..64 bits
+      uint64_t c0 = window8(lex.b0, lex.b1, lex.b2, o), c1 = window8(lex.b0, lex.b1, lex.b2, o + 8),
+               c2 = window8(lex.b0, lex.b1, lex.b2, o + 16);
+      if (cont) {
+        c2 = (c1 >> (64 - sh)) | (sh < 64 ? c2 << sh : 0ull);
+        c1 = (c0 >> (64 - sh)) | (sh < 64 ? c1 << sh : 0ull);
+        c0 = lex.rem | (sh < 64 ? c0 << sh : 0ull);
+      }
+      return lex_flags_bytes(tb, lex.sl, c0, c1, c2, len);
+    }
     // byte by byte through the lexicon trie
     uint32_t node = cont ? lex.lexnode : 0u;
     for (uint32_t i = o; i < e && node != kNoLex; ++i) node = lex_child(tb, lex.sl, node, byte_at(i));

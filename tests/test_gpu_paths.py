@@ -145,3 +145,23 @@ def test_many_terminals_of_a_trailing_lexeme(G, oracle_mod, keywords):
     g.to_device("cuda")
     o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
     _check(g, o, [b"", b"a", b"a,", b"!", b"!k", b"a,!a", b"k"], slot)
+
+
+@pytest.mark.parametrize("pending", [0, 1, 7, 8, 9, 16])
+def test_lexeme_lengths_of_lexicon_lookups(G, oracle_mod, pending):
+    """Words at and around the strides of the lexicon tables, cut into tokens at
+    every place, with pending bytes up to and past those kept."""
+    text = 'start S\ntoken N /[a-z]+/ category\ntoken D "."\ntoken WS / +/ ignore\nS : N | S D N ;\n'
+    words = [("abcdefghijklmnopqrstuvwxyz" * 2)[:n] for n in (1, 7, 8, 9, 15, 16, 17, 18, 23, 24, 25, 26, 33, 40)]
+    words += [w[:-1] + "z" for w in words if len(w) > 1]
+    toks = {w[pending:] + t for w in words for t in ("", ".", ".a", ".ab", " .abcdefg", ".abcdefgh.")}
+    toks |= {"." + w + t for w in words for t in ("", ".", ". a")} | {"a." + w + ".a" for w in words}
+    toks |= {w[pending:k] for w in words for k in range(pending + 1, len(w))}
+    vocab = [bytes([b]) for b in range(256)] + sorted(t.encode() for t in toks if 1 < len(t) <= 60) + [b""]
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos)
+    slot = g.add_lexicon({"N": words})
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {"N": words}, vocab, [eos], eos)
+    head = b"abcdefghijklmnopqrstuvwxyz"[:pending]
+    _check(g, o, [head, b"a." + head, b"abcdefg . " + head], slot)
