@@ -549,10 +549,10 @@ def main():
                    "achieved_gbs": stream_bytes / ph_mean_s[1] / 1e9,
                    "frac": stream_bytes / ph_mean_s[1] / 1e9 / HBM_PEAK_GBS},
         "residue": {"us": ph_mean_s[2] * 1e6},
-        "finalize": {"us": ph_mean_s[3] * 1e6},
+        "publish": {"us": ph_mean_s[3] * 1e6},
         "apply": {"us": ph_mean_s[4] * 1e6},
     }
-    dominant = max(("prologue+verdicts", "stream", "residue", "finalize"), key=lambda k: per_phase[k]["us"])
+    dominant = max(("prologue+verdicts", "stream", "residue", "publish"), key=lambda k: per_phase[k]["us"])
 
     out = {
         "metric": "cold next-token masks/s at B=32, V=151,936; p50/p99 us per mask",

@@ -81,7 +81,7 @@ struct Parser {
   std::vector<uint16_t> go_skip;  // [n_states*N]: GOTO with transitions into unit states redirected
   std::vector<uint32_t> prod;     // lhs | len << 16
   std::vector<uint8_t> term_used; // terminal appears in the reduced grammar
-  // compact form for set simulation (TW = words per terminal set incl. end of
+  // compact form for the device advance (TW = words per terminal set incl. end of
   // input, a power of two): per state, parse_record_words(TW) words
   // [shift bits TW][main reduce bits TW][main production][extra groups | offset << 8]
   // (productions as lhs | length << 16, 0xFFFFFFFF none)

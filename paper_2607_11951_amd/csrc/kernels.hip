@@ -836,12 +836,13 @@ __host__ __device__ inline ProLds prologue_lds(const Tables& tb) {
 }
 
 // ---------------------------------------------------------------- prologue
-// One workgroup per row.  Phase 1: every terminal's reduce chain and shift
-// from sigma (A(sigma) is the set that shifted) and, for an allowed terminal,
-// the allowed set of the stack after its shift, with the end-of-sequence gate
-// run speculatively after every candidate winner's shift and from sigma; then
-// the pending lexeme's winner; then the trailing-flag tables, the lexicon
-// continuation bits of the pending lexeme and the row header.
+// One workgroup per row.  Phase 1: every terminal's reduce chain and shift from
+// sigma, a thread each (A(sigma) is the ballot of those that shifted), with the
+// lexicon continuation bits of the pending lexeme beside them; then the allowed
+// set of the stack after each allowed terminal's shift, a wave per 64 terminals,
+// the end of input one of them; then the pending lexeme's winner and the row
+// block.  Bound by the longest reduce chain and the staging of the tables: 12.6 us
+// at 32 DML rows (V = 151,936), 17.7 with the compact tables and a set simulation.
 template <int MW, bool L>
 __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const grid_config* __restrict__ cfgs,
                                                           const uint16_t* __restrict__ pool,
@@ -1581,7 +1582,11 @@ __device__ __forceinline__ int lane_rank(uint64_t bal) {
 // the row's continuation tables, or from its token-flag summary), or when that
 // question is a trailing one the token's prefix flags answer.  What stays
 // open is listed for the residue kernel, and marked in the row's open bitmap for
-// the row that has more than its list holds.  Rows served from the mask cache are skipped; rows with a bad
+// the row that has more than its list holds.  16 bytes of class map per lane: 13.2 us
+// at 32 rows of 151,936 ids and 65 us at 256 (64 ids per wave and one 2-byte load
+// per lane: 20.8 and 123 us).  Bound by the open ids' chains of dependent lookups:
+// neither packing the queue with half the instructions nor settling the lexicon
+// classes in place before it (from 96 open ids on) made it faster.  Rows served from the mask cache are skipped; rows with a bad
 // configuration get zero words.
 __global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, uint32_t* __restrict__ mask,
                                                                 uint8_t* __restrict__ ws, size_t rbytes, int B,
@@ -2155,6 +2160,10 @@ __device__ __forceinline__ int find_chunk(const uint32_t* counts, const uint32_t
   return -1;
 }
 
+// The largest part of a call: 42 us at 32 DML rows, 149 at 256 with a schema each
+// (55.9 and 261 when a workgroup took whole words of a row's bitmap and simulated
+// allowed sets), 20 to 26 us for the smallest calls, where a single id's chain
+// is all of it.
 // The ids the stream left open, dealt evenly to the workgroups: a chunk is K
 // open ids of one row, K set by the batch's total, so a row with many costs no
 // workgroup more than a row with few.  The waves of the workgroup take a few ids
