@@ -1583,16 +1583,19 @@ __device__ __forceinline__ int lane_rank(uint64_t bal) {
 // question is a trailing one the token's prefix flags answer.  What stays
 // open is listed for the residue kernel, and marked in the row's open bitmap for
 // the row that has more than its list holds.  16 bytes of class map per lane: 13.2 us
-// at 32 rows of 151,936 ids and 65 us at 256 (64 ids per wave and one 2-byte load
+// at 32 rows of 151,936 ids and 58 us at 256 (64 ids per wave and one 2-byte load
 // per lane: 20.8 and 123 us).  Bound by the open ids' chains of dependent lookups:
-// neither packing the queue with half the instructions nor settling the lexicon
-// classes in place before it (from 96 open ids on) made it faster.  Rows served from the mask cache are skipped; rows with a bad
+// reading a batch's first lookups while the one before it is settled took it from 65
+// to 58 us at 256 rows; neither packing the queue with half the instructions nor
+// settling the lexicon classes in place before it (from 96 open ids on) made it
+// faster.  Rows served from the mask cache are skipped; rows with a bad
 // configuration get zero words.
 __global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, uint32_t* __restrict__ mask,
                                                                 uint8_t* __restrict__ ws, size_t rbytes, int B,
                                                                 int n_slices, int slice_ids) {
   extern __shared__ __align__(16) uint8_t slds[];
   __shared__ int open_s, base_s;
+  __shared__ uint8_t cont[256];  // first bytes that continue the pending bytes in the lexicon
   __shared__ uint32_t mbits[kStreamWaves][kStepIds / 32], cbits[kStreamWaves][kStepIds / 32],
       obits[kStreamWaves][kStepIds / 32];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1628,9 +1631,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, ui
   // a row that claimed an entry writes its CI tokens' bits there (the residue
   // pass adds those it decides)
   uint32_t* cdst = claim >= 0 ? (uint32_t*)(tb.ci_cache + (size_t)claim * tb.ci_stride + kCiHeader) : nullptr;
-  uint32_t cont[8];
-#pragma unroll
-  for (int w = 0; w < 8; ++w) cont[w] = hdr->cont[w];
+  if (tid < 256) cont[tid] = (uint8_t)((hdr->cont[tid >> 5] >> (tid & 31)) & 1u);
   // the class ids of this lane in a step, 0 (rejected) past the vocabulary
   auto load_ids = [&](int id0) -> Ids8 {
     Ids8 v = {{0, 0, 0, 0}};
@@ -1677,32 +1678,38 @@ __global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, ui
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     int left = 0;  // of them, left to the residue (uniform)
+    // a batch's entries and what their shortcuts ask first, read a batch ahead
+    uint32_t e = 0, rule = 0, word = 0;
+    auto fetch = [&](int i0) {
+      e = rule = word = 0;
+      if (i0 + lane < n) {
+        e = queue[i0 + lane];
+        rule = codes[e >> 16];
+        const int id = wb + (int)(e & 0xFFFFu);
+        if ((rule & (3u | kNoValid)) == (kVerdictLexicon | kNoValid))
+          word = (rule >> 2) & 3u ? (uint32_t)tsum[id] : tb.id_head[id];
+      }
+    };
+    fetch(0);
     for (int i0 = 0; i0 < n; i0 += 64) {
-      const bool in = i0 + lane < n;
-      const uint32_t e = in ? queue[i0 + lane] : 0u;
-      const uint32_t cls = e >> 16, lid = e & 0xFFFFu;
+      const uint32_t cls = e >> 16, lid = e & 0xFFFFu, rl = rule, wd0 = word;
       const int id = wb + (int)lid;
-      const uint32_t rule = in ? (uint32_t)codes[cls] : 0u;
-      uint32_t cd = rule & 3u;
-      if (cd == kVerdictLexicon && (rule & kNoValid)) {
-        const uint32_t kind = (rule >> 2) & 3u;
+      fetch(i0 + 64);
+      uint32_t cd = rl & 3u;
+      if (cd == kVerdictLexicon && (rl & kNoValid)) {
+        const uint32_t kind = (rl >> 2) & 3u;
         bool no;
         if (kind == 0) {  // on the pending bytes: the token's first byte, then its second
-          const uint32_t hd = tb.id_head[id];
-          const uint32_t fb = hd & 0xFFu, sb = (hd >> 8) & 0xFFu;
-          uint32_t cw = 0;
-#pragma unroll
-          for (int w = 0; w < 8; ++w)
-            if (w == (int)(fb >> 5)) cw = cont[w];
-          no = !((cw >> (fb & 31u)) & 1u);
-          if (!no && ((rule >> 4) & 1u) && (hd & 0x10000u)) no = !((cont2[fb * 8u + (sb >> 5)] >> (sb & 31u)) & 1u);
+          const uint32_t fb = wd0 & 0xFFu, sb = (wd0 >> 8) & 0xFFu;
+          no = !cont[fb];
+          if (!no && ((rl >> 4) & 1u) && (wd0 & 0x10000u)) no = !((cont2[fb * 8u + (sb >> 5)] >> (sb & 31u)) & 1u);
         } else {
-          const uint32_t o = (rule >> 4) & 1u;
-          no = (((uint32_t)tsum[id] >> (2u * o + (kind == 2u ? 1u : 0u))) & 1u) == 0u;
+          const uint32_t o = (rl >> 4) & 1u;
+          no = ((wd0 >> (2u * o + (kind == 2u ? 1u : 0u))) & 1u) == 0u;
           // a trailing question is the last one: the token's prefix flags settle it
           if (!no && kind == 1u) cd = (tok[id] >> (16u * o)) & cats[cls] & 0xFFu ? kVerdictAllow : kVerdictReject;
         }
-        if (no) cd = (rule >> 5) & 3u;
+        if (no) cd = (rl >> 5) & 3u;
       }
       if (cd == kVerdictAllow) {
         atomicOr(&mbits[wave][lid >> 5], 1u << (lid & 31u));
@@ -1716,7 +1723,7 @@ __global__ __launch_bounds__(kStreamThreads, 8) void stream_kernel(Tables tb, ui
         if (cd >= kVerdictWalk) {
           atomicOr(&obits[wave][lid >> 5], 1u << (lid & 31u));
           const int at = base + lane_rank(bal);
-          if (at < kOpenLocal) list[at] = make_uint2((uint32_t)id, cls | (rule & 3u) << 16);
+          if (at < kOpenLocal) list[at] = make_uint2((uint32_t)id, cls | (rl & 3u) << 16);
         }
         left += __popcll(bal);
       }
