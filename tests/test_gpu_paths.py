@@ -165,3 +165,20 @@ def test_lexeme_lengths_of_lexicon_lookups(G, oracle_mod, pending):
     o = oracle_mod.Oracle(text, (), {"N": words}, vocab, [eos], eos)
     head = b"abcdefghijklmnopqrstuvwxyz"[:pending]
     _check(g, o, [head, b"a." + head, b"abcdefg . " + head], slot)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("first", [0, 1, 2, 5, 7])
+@pytest.mark.parametrize("V", [7, 8, 9, 63, 1001])
+def test_apply_rows_at_every_alignment(G, dtype, first, V):
+    B, stride = 5, V + 3
+    gen = torch.Generator().manual_seed(V * 8 + first)
+    flat = torch.randn(first + B * stride, generator=gen).to(dtype)
+    words = torch.randint(-2**31, 2**31, (B, (V + 31) // 32), generator=gen, dtype=torch.int64)
+    words[1], words[2] = 0, -1
+    bits = ((words[:, torch.arange(V) // 32] >> (torch.arange(V) % 32)) & 1).bool()
+    want = flat.clone()
+    want[first:].view(B, stride)[:, :V].masked_fill_(~bits, float("-inf"))
+    dev = flat.cuda()
+    G.apply(words.to(torch.int32).cuda(), dev[first:].view(B, stride)[:, :V])
+    assert torch.equal(dev.cpu().view(torch.uint8), want.view(torch.uint8))
