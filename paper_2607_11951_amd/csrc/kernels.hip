@@ -600,8 +600,8 @@ __device__ __forceinline__ uint32_t lr_chain(const LrTabs<L>& lt, const ChainSta
 }
 
 // The stack after a chain's shift (a its last action): base entries kept and
-// overlay, written over ov[0, m).  False if the overlay outgrows cap (or the
-// base its 16 bits, for a record).
+// overlay, written over ov[0, m).  False if the overlay outgrows cap, or empty
+// reductions before the shift take more than kGuard steps.
 __device__ __forceinline__ bool lr_commit(const Tables& tb, uint32_t a, uint32_t x, uint32_t n, uint32_t s, bool moved,
                                           uint32_t& k, uint32_t& m, mptr<true, uint16_t> ov, uint32_t cap) {
   if (moved) {
@@ -613,9 +613,10 @@ __device__ __forceinline__ bool lr_commit(const Tables& tb, uint32_t a, uint32_t
   if (a & kMactPushed) {  // the states the empty reductions push first (rare: the LALR tables in global memory)
     const uint32_t floor = m, T1 = (uint32_t)tb.T + 1u;
     uint32_t top = s;
-    for (int guard = 0; guard < kGuard; ++guard) {
+    for (int guard = 0;; ++guard) {
       const uint32_t la = tb.action[top * T1 + x];
       if ((la & 0xC000u) != kActReduce) break;
+      if (guard >= kGuard) return false;
       const uint32_t pr = tb.prod[la & 0x3FFFu], len = pr >> 16;
       if (len > m - floor) return false;
       m -= len;

@@ -11,6 +11,7 @@
 // (section 3.2), so it is exact with or without table compression.
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <set>
 
@@ -406,40 +407,47 @@ std::vector<int> skip_unit_states(Parser& P) {
 void build_mask_actions(Parser& P, const std::vector<int>& unit) {
   const int T1 = P.T + 1, NS = P.n_states, N = P.N;
   P.n_shift_runs = (uint32_t)P.pshift.size();
-  std::vector<uint32_t> act((size_t)NS * T1, 0);  // 0, shift (bit 31), or lhs | pops << 16
+  // 0, shift (bit 31; bit 30 with states pushed before it), or lhs | pops << 16.
+  // An entry follows from those of the states pushed above its own, so each is
+  // worked out once, however many reductions it stands for (their number can
+  // double with every nonterminal).
+  std::vector<uint32_t> act((size_t)NS * T1, 0);
+  std::vector<uint8_t> known((size_t)NS * T1, 0);  // 1 in work, 2 done
+  std::function<uint32_t(int, int)> entry = [&](int s, int t) -> uint32_t {
+    const size_t at = (size_t)s * T1 + t;
+    if (known[at]) return known[at] == 2 ? act[at] : 0u;  // (in work: a run that never ends)
+    known[at] = 1;
+    uint32_t r = 0;
+    const uint16_t a = P.act(s, t), kind = a & 0xC000;
+    if (kind == kActAccept) {
+      r = 1u << 31;
+    } else if (kind == kActShift) {
+      uint16_t tgt = (uint16_t)(a & 0x3FFF);
+      if (unit[tgt] >= 0) {
+        const uint16_t g = P.go_skip[(size_t)s * N + (P.prod[unit[tgt]] & 0xFFFF)];
+        if (g != kNoGoto) tgt = g;
+      }
+      r = 1u << 31 | tgt;
+    } else if (kind == kActReduce) {
+      r = (P.prod[a & 0x3FFF] & 0xFFFF) | (P.prod[a & 0x3FFF] >> 16) << 16;
+      // pops nothing of s: GOTO from s, and on with the entry of the state pushed
+      for (int guard = 0; r >> 16 == 0; ++guard) {
+        const uint16_t g = P.go_skip[(size_t)s * N + (r & 0xFFFF)];
+        r = g == kNoGoto || guard > NS ? 0u : entry(g, t);
+        if (r == 0) break;
+        if (r >> 31) r |= 1u << 30;
+        else r -= 1u << 16;  // its first pop is the state pushed
+      }
+    }
+    act[at] = r;
+    known[at] = 2;
+    return r;
+  };
   uint32_t max_pops = 1;
   for (int s = 0; s < NS; ++s)
     for (int t = 0; t < T1; ++t) {
-      std::vector<uint16_t> up;  // states pushed above s
-      for (int guard = 0; guard <= 4 * NS + 16; ++guard) {
-        const int top = up.empty() ? s : up.back();
-        const uint16_t a = P.act(top, t), kind = a & 0xC000;
-        if (a == 0) break;
-        if (kind == kActAccept) {
-          act[(size_t)s * T1 + t] = 1u << 31 | (up.empty() ? 0u : 1u << 30);
-          break;
-        }
-        if (kind == kActShift) {
-          uint16_t tgt = (uint16_t)(a & 0x3FFF);
-          if (unit[tgt] >= 0) {
-            const uint16_t g = P.go_skip[(size_t)top * N + (P.prod[unit[tgt]] & 0xFFFF)];
-            if (g != kNoGoto) tgt = g;
-          }
-          act[(size_t)s * T1 + t] = 1u << 31 | (up.empty() ? 0u : 1u << 30) | tgt;
-          break;
-        }
-        const uint32_t pr = P.prod[a & 0x3FFF], len = pr >> 16, X = pr & 0xFFFF;
-        if (len > up.size()) {
-          const uint32_t pops = len - (uint32_t)up.size();
-          act[(size_t)s * T1 + t] = X | pops << 16;
-          max_pops = std::max(max_pops, pops);
-          break;
-        }
-        up.resize(up.size() - len);
-        const uint16_t g = P.go_skip[(size_t)(up.empty() ? s : up.back()) * N + X];
-        if (g == kNoGoto) break;
-        up.push_back(g);
-      }
+      const uint32_t r = entry(s, t);
+      if (!(r >> 31)) max_pops = std::max(max_pops, r >> 16);
     }
   int bits = 1;
   while ((1 << bits) < N) ++bits;

@@ -1,0 +1,186 @@
+"""The tables the mask kernels read, on the host: the dense action table (the
+reductions that a state and a lookahead decide alone done ahead) against the
+LALR tables."""
+
+import numpy as np
+import pytest
+
+from workloads import grammar_text
+
+
+@pytest.fixture(scope="module")
+def G():
+    import paper_2607_11951_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+class Tables:
+    """A compiled grammar's LALR tables and the mask kernels' dense ones, with a
+    reduce-chain simulation over either.  A kernel chain is what the kernels
+    run: one state above a prefix of the stack, one action a step; the states
+    that empty reductions push before a shift come from the LALR actions."""
+
+    SHIFT, PUSHED = 0x8000, 0x4000
+
+    def __init__(self, g):
+        info = g.info()
+        self.NS, self.T, self.N = NS, T, N = info["n_lr_states"], info["n_terminals"], info["n_nonterminals"]
+        self.action = np.frombuffer(g.artifact("ACTION"), np.uint16).reshape(NS, T + 1).astype(int)
+        self.go = np.frombuffer(g.artifact("GOTO"), np.uint16).reshape(NS, N).astype(int)
+        self.skip = np.frombuffer(g.artifact("GOTO_SKIP"), np.uint16).reshape(NS, N).astype(int)
+        self.prod = np.frombuffer(g.artifact("PROD"), np.uint32).astype(int)
+        tw = 2
+        while 32 * tw < T + 1:
+            tw *= 2
+        rec = np.frombuffer(g.artifact("PARSE_STATE"), np.uint32).reshape(NS, (2 * tw + 5) // 4 * 4)
+        shifts = np.array([sum(bin(int(w)).count("1") for w in r[:tw]) for r in rec])
+        ends = [int(rec[s][2 * tw + k]) + int(shifts[s]) for s in range(NS) for k in (2, 3)]
+        raw = g.artifact("PARSE_SHIFT")
+        at = (max(ends) + 7) // 8 * 8
+        cells = NS * (T + 1)
+        self.act = np.frombuffer(raw, np.uint16)[at:at + cells].reshape(NS, T + 1).astype(int)
+        red = raw[2 * ((at + cells + 7) // 8 * 8):]
+        self.red = np.frombuffer(red, np.uint32).astype(int)  # reductions of indexed entries
+        self.bits = 0 if len(red) else max(1, (N - 1).bit_length())
+
+    def lalr(self, stack, x):
+        """The stack after shifting x, "accept", or None."""
+        st = list(stack)
+        while True:
+            a = int(self.action[st[-1], x])
+            if a == 0:
+                return None
+            if a & 0xC000 == 0x4000:
+                return st + [a & 0x3FFF]
+            if a & 0xC000 == 0xC000:
+                return "accept"
+            p = int(self.prod[a & 0x3FFF])
+            if p >> 16:
+                del st[-(p >> 16):]
+            if not st or self.go[st[-1], p & 0xFFFF] == 0xFFFF:
+                return None
+            st.append(int(self.go[st[-1], p & 0xFFFF]))
+
+    def kernel(self, stack, x):
+        below, s = list(stack[:-1]), int(stack[-1])
+        units = 0  # one-entry reductions since the stack last shrank
+        while True:
+            a = int(self.act[s, x])
+            if a == 0:
+                return None
+            if a & self.SHIFT:
+                break
+            lhs, pops = a & ((1 << self.bits) - 1), a >> self.bits
+            if self.bits == 0:
+                lhs, pops = int(self.red[a - 1]) & 0xFFFF, int(self.red[a - 1]) >> 16
+            assert pops >= 1
+            if pops > len(below):
+                return None
+            units = units + 1 if pops == 1 else 0
+            assert units <= self.NS  # no state comes twice above one entry
+            if pops > 1:
+                del below[-(pops - 1):]
+            s = int(self.skip[below[-1], lhs])
+            if s == 0xFFFF:
+                return None
+        if x == self.T:
+            return "accept"
+        st = below + [s]
+        if a & self.PUSHED:
+            floor, top = len(st), s
+            while True:
+                la = int(self.action[top, x])
+                if la & 0xC000 != 0x8000:
+                    break
+                p = int(self.prod[la & 0x3FFF])
+                assert p >> 16 <= len(st) - floor
+                if p >> 16:
+                    del st[-(p >> 16):]
+                top = int(self.skip[st[-1], p & 0xFFFF])
+                assert top != 0xFFFF
+                st.append(top)
+        return st + [a & 0x3FFF]
+
+
+def walk(tb, seed, walks, steps):
+    """Random walks through the LALR automaton: at every stack, and after the shift
+    of every terminal (each side going on from its own stack), both sides allow
+    the same terminals.  The number of stacks compared."""
+    rng = np.random.default_rng(seed)
+    allowed = lambda run, st: {x for x in range(tb.T + 1) if run(st, x) is not None}
+    n = 0
+    for _ in range(walks):
+        stack = [0]
+        for _ in range(int(rng.integers(1, steps))):
+            full = allowed(tb.lalr, stack)
+            assert allowed(tb.kernel, stack) == full, stack
+            nxt = sorted(full - {tb.T})
+            for x in nxt if len(nxt) <= 12 else rng.choice(nxt, 12, replace=False):
+                assert allowed(tb.kernel, tb.kernel(stack, x)) == allowed(tb.lalr, tb.lalr(stack, x)), (stack, x)
+                n += 1
+            if not nxt:
+                break
+            stack = tb.lalr(stack, int(rng.choice(nxt)))
+    return n
+
+
+@pytest.mark.parametrize("name,drop", [("expr", []), ("lexi", []), ("crud", []), ("sql_select", []),
+                                       ("sql_dml", ["insert", "update", "delete"]), ("sql_dml", [])])
+def test_dense_actions_on_random_parses(G, name, drop):
+    assert walk(Tables(G.Grid(grammar_text(name), drop, [b"a"])), 3, 8, 30) > 0
+
+
+def test_dense_actions_on_random_grammars(G):
+    from workloads.randgram import RandomGrammar
+    done = pushed = 0
+    for seed in range(400):
+        try:
+            tb = Tables(G.Grid(RandomGrammar(seed).text(), (), [b"x"]))
+        except G.GridError as e:
+            assert "GRID_E_LALR_CONFLICT" in str(e), (seed, str(e))
+            continue
+        walk(tb, seed, 4, 20)
+        pushed += int((tb.act & 0xC000 == 0xC000).sum())
+        done += 1
+        if done == 40:
+            break
+    assert done == 40 and pushed > 0
+
+
+def indexed_grammar(names):
+    """A left side among many and a production of many symbols: together more than
+    15 bits, so the reduce entries are indices."""
+    alts = " | ".join(f"N{i} X{i % 3}" for i in range(names))
+    text = ("start S\n" + "".join(f'token X{i} "x{i}"\n' for i in range(3)) + 'token Y "y"\ntoken Z "z"\n'
+            "S : " + alts + " | L ;\n" + "L : " + " ".join(["Y"] * 140) + " Z | Z L ;\n"
+            + "".join(f"N{i} : {'Z' if i % 2 else 'Y'} M{i} ;\nM{i} : X{i % 3} X{i % 2} {'X0 ' * (i // 6)}Y ;\n"
+                      for i in range(names)))
+    return text
+
+
+def test_indexed_reductions(G):
+    tb = Tables(G.Grid(indexed_grammar(66), (), [b"x"]))
+    assert tb.bits == 0 and len(tb.red) > 0
+    assert walk(tb, 5, 12, 150) > 0
+
+
+def nullable_grammar(levels):
+    """Every A{i} derives the empty string alone, in 2^(levels - i) steps: on X the
+    start state reduces 2^(levels + 1) - 1 times before the shift, and as often
+    after B before a pop of what the reductions pushed and of B."""
+    text = ('start S\ntoken X "x"\ntoken Y "y"\ntoken B "b"\ntoken C "c"\n'
+            "S : A0 X | Y | Q C S ;\nQ : B A0 R ;\nR : %empty ;\n")
+    return text + "".join(f"A{i} : A{i + 1} A{i + 1} ;\n" for i in range(levels)) + f"A{levels} : %empty ;\n"
+
+
+@pytest.mark.parametrize("levels", [1, 4, 7, 9])
+def test_long_runs_of_empty_reductions(G, levels):
+    tb = Tables(G.Grid(nullable_grammar(levels), (), [b"x"]))
+    assert walk(tb, 7, 4, 8) > 0
+
+
+def test_runs_of_empty_reductions_compile_in_time(G):
+    # 2^41 reductions: a grammar like any other for the compiler
+    tb = Tables(G.Grid(nullable_grammar(40), (), [b"x"]))
+    assert tb.act[0].tolist().count(0) < tb.T + 1 and (tb.act[0] & 0xC000 == 0xC000).any()
