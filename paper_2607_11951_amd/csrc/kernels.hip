@@ -56,7 +56,9 @@ constexpr int kBlock = 256;          // workgroup size of most kernels
 constexpr int kProThreads = 1024;    // prologue workgroup size (one per row)
 constexpr int kStackWin = 256;       // top of the row's stack kept in LDS (prologue)
 constexpr int kPostCap = 14;         // overlay states recorded per first shift
-constexpr int kGuard = 4096;         // reduce-chain step bound
+constexpr int kGuard = 4096;         // reduce-chain steps without the stack falling, at most: only empty
+                                     // reductions can take more (see lr_chain and chain_shift)
+constexpr int kUnitGuard = 1 << 14;  // reductions of one entry in a row, at most: LR states have 14 bits
 constexpr uint32_t kRowValid = 0x600D;
 constexpr size_t kWsHead = 256;      // workspace head (reserved)
 
@@ -572,14 +574,17 @@ struct ChainStack {
 // Reduce chain of terminal x from the stack: in, s is its top state and n the
 // entries below it; out, the stack that x is shifted on is its first n entries
 // and s, moved tells whether some reduction ran.  Returns the last action: 0
-// (refused), or a kMactShift entry.
+// (refused), or a kMactShift entry.  A legal chain can be as long as the stack is
+// deep, so only the steps since the stack last fell are counted: those put one
+// state after another above the same entry, never one of them twice (a grammar
+// where they did would be ambiguous), so no chain reaches the count.
 template <bool L>
 __device__ __forceinline__ uint32_t lr_chain(const LrTabs<L>& lt, const ChainStack& st, uint32_t x, uint32_t& n,
                                              uint32_t& s, bool& moved) {
   uint32_t a = lt.act[__umul24(s, lt.T1) + x];
   uint32_t e = n ? st.at(n - 1u) : 0u;  // the state below s
   moved = false;
-  for (int guard = 0; guard < kGuard && a - 1u < kMactShift - 1u; ++guard) {  // a reduction
+  for (int guard = 0; guard < kUnitGuard && a - 1u < kMactShift - 1u; ++guard) {  // a reduction
     uint32_t lhs = a & ((1u << lt.bits) - 1u), pops = a >> lt.bits;
     if (lt.bits == 0) {  // uniform
       const uint32_t r = lt.red[a - 1u];
@@ -590,6 +595,7 @@ __device__ __forceinline__ uint32_t lr_chain(const LrTabs<L>& lt, const ChainSta
     if (pops > 1u) {
       n -= pops - 1u;
       e = st.at(n - 1u);
+      guard = 0;
     }
     s = lt.go[__umul24(e, lt.N) + lhs];
     moved = true;
@@ -2618,7 +2624,8 @@ __device__ inline BaseStack<L> whole_stack(mptr<L, uint16_t> stk, uint32_t d) {
 
 // Reduce chain of terminal x on the stack stk[0, d), pushes above d (the
 // stack below stays as it is).  1 shift, 2 accept (x is the end of input), 0
-// error, -1 capacity.  With commit, a shift makes the chain's result the
+// error, -1 capacity (the area, or more than kGuard steps since the stack last
+// fell).  With commit, a shift makes the chain's result the
 // stack: the pushed states move down onto the popped entries, then x's
 // shift target goes on top (so a winner costs one chain, not two).
 template <bool L, int MW>
@@ -2646,8 +2653,9 @@ __device__ int chain_shift(const ParseTabs<L>& pt, mptr<L, uint16_t> stk, uint32
       }
       return 1;
     }
-    const uint32_t len = a >> 16;
+    const uint32_t len = a >> 16, k0 = k;
     if (!pop_len(len, k, m, t)) return 0;
+    if (k < k0) guard = 0;
     const uint32_t sb = goto_source<L>(bs, len, s, below, k, m, tmp, t, tmp);
     const uint16_t g = goto_of<L>(pt, sb, a & 0xFFFFu);
     if (g == kNoGoto) return 0;
@@ -2673,6 +2681,7 @@ __device__ int chain_test(const ParseTabs<L>& pt, mptr<L, const uint16_t> stk, u
     if (a >= kActShiftP) return a == kActShiftP ? 1 : 0;
     const uint32_t len = a >> 16, dt = min(t, len);
     if (len - dt >= k) return 0;
+    if (len > dt) guard = 0;
     t -= dt;
     k -= len - dt;
     uint32_t sb = s;
