@@ -39,6 +39,7 @@
 #include <cstdint>
 #include <string>
 
+#include "fill.h"
 #include "host.h"
 #include "lexhash.h"
 #include "rolling_hash.h"
@@ -2496,19 +2497,12 @@ __global__ __launch_bounds__(kBlock) void cache_clear_kernel(uint8_t* cache, uin
 
 // ------------------------------------------------------------------- apply
 // Each thread covers 8 consecutive logits of one row; the mask byte for them
-// comes from one word.  A whole group takes 16-byte stores (read first
-// when it keeps entries, whose bits are written back unchanged), at whatever
-// element it starts: rows of an odd length are as unaligned as they come, and
-// the memory takes a 16-byte access at any element.  A group at a ragged row
-// end is written logit by logit.  (Logit by logit in every unaligned row, the fill of
+// comes from one word.  (Logit by logit in every unaligned row, the fill of
 // 47 rows of 50,257 cost 2 us more, 71.4 against 69.2 for mask and fill.)
 template <typename T>
-struct __attribute__((packed, aligned(sizeof(T)))) Logits16 {  // 16 bytes of logits
-  uint32_t w[4];
-};
-template <typename T>
 __global__ __launch_bounds__(kBlock) void apply_kernel(const uint32_t* __restrict__ mask, T* logits, int B,
-                                                       int V, int W, int64_t stride, uint32_t neg_inf_bits) {
+                                                       int V, int W, int64_t stride, uint32_t neg_inf_bits,
+                                                       bool aligned) {
   // row blockIdx.y; groups of 8 logits along it, grid-stride in x
   const int groups = (V + 7) >> 3;
   const int row = (int)blockIdx.y;
@@ -2517,39 +2511,7 @@ __global__ __launch_bounds__(kBlock) void apply_kernel(const uint32_t* __restric
     const int col = grp * 8;
     const uint32_t bits = (mask[(size_t)row * W + (col >> 5)] >> (col & 31)) & 0xFFu;
     if (bits == 0xFFu) continue;
-    T* p = logits + (int64_t)row * stride + col;
-    if (col + 8 <= V) {  // whole group: 16-byte stores, the kept logits read back unchanged
-      Logits16<T>* q = reinterpret_cast<Logits16<T>*>(p);
-      if (sizeof(T) == 2) {
-        Logits16<T> v = {{0, 0, 0, 0}};
-        if (bits) v = q[0];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t lo = (bits >> (2 * k)) & 1u ? v.w[k] & 0xFFFFu : neg_inf_bits;
-          const uint32_t hi = (bits >> (2 * k + 1)) & 1u ? v.w[k] & 0xFFFF0000u : neg_inf_bits << 16;
-          v.w[k] = lo | hi;
-        }
-        q[0] = v;
-      } else {
-        Logits16<T> v0 = {{0, 0, 0, 0}}, v1 = v0;
-        if (bits & 0x0Fu) v0 = q[0];
-        if (bits & 0xF0u) v1 = q[1];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          v0.w[k] = (bits >> k) & 1u ? v0.w[k] : neg_inf_bits;
-          v1.w[k] = (bits >> (4 + k)) & 1u ? v1.w[k] : neg_inf_bits;
-        }
-        q[0] = v0;
-        q[1] = v1;
-      }
-      continue;
-    }
-    for (int j = 0; j < 8 && col + j < V; ++j) {
-      if (!((bits >> j) & 1u)) {
-        if (sizeof(T) == 2) reinterpret_cast<uint16_t*>(p)[j] = (uint16_t)neg_inf_bits;
-        else reinterpret_cast<uint32_t*>(p)[j] = neg_inf_bits;
-      }
-    }
+    fill_group<T>(logits + (int64_t)row * stride + col, bits, V - col, aligned, neg_inf_bits);
   }
 }
 
@@ -3661,12 +3623,14 @@ extern "C" int grid_apply(const uint32_t* mask_dev, void* logits_dev, int32_t dt
   // of 8 logits, at most 512 (a grid-stride loop covers the rest)
   const dim3 blocks((unsigned)std::min((groups + kBlock - 1) / kBlock, 512), (unsigned)B);
   hipStream_t s = (hipStream_t)stream;
+  const int64_t esz = dtype == GRID_DTYPE_BF16 ? 2 : 4;
+  const bool aligned = (uintptr_t)logits_dev % 16 == 0 && row_stride * esz % 16 == 0;
   if (dtype == GRID_DTYPE_BF16)
     hipLaunchKernelGGL(apply_kernel<uint16_t>, blocks, dim3(kBlock), 0, s, mask_dev,
-                       (uint16_t*)logits_dev, B, V, W, row_stride, 0xFF80u);
+                       (uint16_t*)logits_dev, B, V, W, row_stride, 0xFF80u, aligned);
   else
     hipLaunchKernelGGL(apply_kernel<uint32_t>, blocks, dim3(kBlock), 0, s, mask_dev,
-                       (uint32_t*)logits_dev, B, V, W, row_stride, 0xFF800000u);
+                       (uint32_t*)logits_dev, B, V, W, row_stride, 0xFF800000u, aligned);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(GRID_E_HIP, std::string("grid_apply launch: ") + hipGetErrorString(e));
   return GRID_OK;
