@@ -321,8 +321,9 @@ int grid_mask(const grid_compiled* g, int32_t B, const grid_config* cfg_dev,
 #define GRID_PHASE_RESIDUE 4u       /* the listed tokens judged to their end with their
                                        own bytes; allowed bits are OR-ed into mask_dev;
                                        then the row status when status_dev is not null */
-#define GRID_PHASE_FINALIZE 8u      /* the caches' new entries published (nothing without
-                                       a cache) */
+#define GRID_PHASE_FINALIZE 8u      /* the caches' new entries published; without
+                                       GRID_PHASE_RESIDUE in the same call, the row status
+                                       when status_dev is not null */
 #define GRID_PHASE_ALL 15u
 int grid_mask_phases(const grid_compiled* g, int32_t B, const grid_config* cfg_dev,
                      const uint16_t* stack_pool_dev, uint32_t* mask_dev, uint8_t* eos_dev,

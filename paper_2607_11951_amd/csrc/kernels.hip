@@ -2454,6 +2454,15 @@ __global__ __launch_bounds__(kResThreads) void residue_kernel(Tables tb, const u
   }
 }
 
+// The rows' statuses when the last phase is asked for them in a call of its own.
+__global__ __launch_bounds__(64) void status_kernel(const uint8_t* __restrict__ ws, size_t rbytes, int B,
+                                                    int32_t* __restrict__ status) {
+  const int row = (int)(blockIdx.x * 64u + threadIdx.x);
+  if (row >= B) return;
+  const RowHeader* hdr = (const RowHeader*)(ws + kWsHead + (size_t)row * rbytes);
+  status[row] = hdr->valid == kRowValid ? hdr->fstat : hdr->pstat;
+}
+
 // Publishes the CI-words entry of every row that claimed one and ended OK, or
 // gives the slot back.
 __global__ __launch_bounds__(64) void ci_publish_kernel(Tables tb, const uint8_t* __restrict__ ws, size_t rbytes, int B) {
@@ -3158,6 +3167,9 @@ int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint1
                          status);
   }
   if (phases & GRID_PHASE_FINALIZE) {
+    // (beside the residue phase the statuses are written there)
+    if (status && !(phases & GRID_PHASE_RESIDUE))
+      hipLaunchKernelGGL(status_kernel, dim3((uint32_t)(B + 63) / 64), dim3(64), 0, s, ws, rb, B, status);
     if (tb.ci_cache && (tb.ci_flags & GRID_CI_INSERT))
       hipLaunchKernelGGL(ci_publish_kernel, dim3((uint32_t)(B + 63) / 64), dim3(64), 0, s, tb, ws, rb, B);
     if (tb.cache && (tb.cache_flags & GRID_CACHE_INSERT))

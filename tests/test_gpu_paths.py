@@ -182,3 +182,24 @@ def test_apply_rows_at_every_alignment(G, dtype, first, V):
     dev = flat.cuda()
     G.apply(words.to(torch.int32).cuda(), dev[first:].view(B, stride)[:, :V])
     assert torch.equal(dev.cpu().view(torch.uint8), want.view(torch.uint8))
+
+
+@pytest.mark.parametrize("rows", [1, 64, 65])
+def test_status_asked_of_the_last_phase_alone(G, rows):
+    """Status null in the first three phases and given to the last one: the whole
+    call's statuses, rows without a configuration among them."""
+    wl = make_workload(2, rows=rows)
+    g, slots = G.from_workload(wl)
+    g.to_device("cuda")
+    B = len(wl.prefixes)
+    cfgs, pool = g.configs(wl.prefixes, [slots[s] for s in wl.slots])
+    cfgs["q"][::3] = 0xFFFF
+    c, p = g.configs_to_device(cfgs, pool)
+    ws = g.new_workspace(B, "cuda")
+    m, e, want = g.mask(c, p, B, workspace=ws)
+    got = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    L, ptr = G.lib(), lambda t: t.data_ptr() if t is not None else None
+    for phases, st in ((7, None), (8, got)):
+        assert L.grid_mask_phases(g.h, B, ptr(c), ptr(p), ptr(m), ptr(e), ptr(st), ptr(ws), ws.numel(), phases,
+                                  torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(got.cpu(), want.cpu()) and (got.cpu()[::3] == G.ROW_BAD_CONFIG).all()
