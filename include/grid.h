@@ -293,7 +293,9 @@ int grid_config_from_prefix(const grid_compiled* g, int32_t slot, const uint8_t*
                             uint32_t* depth);
 
 /* --------------------------------------------------------------------- mask */
-/* Device workspace bytes grid_mask needs for B rows. */
+/* Device workspace bytes grid_mask needs for B rows: with the classes that are
+ * bound (PROG_*, else CLASS_*), or, with neither, with either (both are then
+ * built).  0 for B < 1, or when they do not fit into memory. */
 size_t grid_mask_workspace_bytes(const grid_compiled* g, int32_t B);
 
 /* The cold exact mask of B rows (Definition 4; per-token hot path steps 1, 2,

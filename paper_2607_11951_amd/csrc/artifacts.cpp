@@ -23,9 +23,13 @@
 // prefix table keyed by their bytes (lexhash.h).  Each word must be a
 // lexeme of its category's terminal (W_c subset of R_c, Proposition 8 (d)).
 #include <algorithm>
+#include <atomic>
 #include <cstring>
+#include <exception>
 #include <map>
+#include <mutex>
 #include <numeric>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 
@@ -157,13 +161,17 @@ VocabArtifacts build_vocab(const uint8_t* bytes, const uint64_t* off, int V, con
   return va;
 }
 
-void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
-                        ClassTables& full, ClassTables& reduced) {
-  const size_t U = va.spell_off.size() - 1;
+void check_class_map(const LexerDfa& dfa, const VocabArtifacts& va) {
   const size_t S = (size_t)dfa.S, V = (size_t)va.V;
   if (S * V > ((size_t)3 << 29))
     throw Error(GRID_E_CAPACITY, "class map of " + std::to_string(S) + " lexer states x " + std::to_string(V) +
                                      " tokens is larger than 3 GiB");
+}
+
+ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
+                               bool reduced) {
+  const size_t U = va.spell_off.size() - 1;
+  const size_t S = (size_t)dfa.S, V = (size_t)va.V;
   // what the reduced programs leave out, per state
   const size_t T = term_info.size();
   auto plain_ignored = [&](size_t t) { return (term_info[t] & 1u) && (term_info[t] >> 8) == 0xFFu; };
@@ -188,9 +196,8 @@ void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std
       asks_trail[q] = 0;
     }
   }
-  // the lexeme program of spelling u when the scan resumes in q (r), and the
-  // reduced one (p)
-  auto program = [&](uint32_t q, size_t u, uint32_t (&r)[4], uint32_t (&p)[4]) {
+  // the lexeme program of spelling u when the scan resumes in q, full or reduced
+  auto program = [&](uint32_t q, size_t u, uint32_t (&r)[4]) {
     const uint8_t* b = va.spell_bytes.data() + va.spell_off[u];
     const uint32_t n = va.spell_off[u + 1] - va.spell_off[u];
     uint32_t cur = q, ends = 0, qe[kClassEnds] = {0, 0, 0}, pe[kClassEnds] = {0, 0, 0}, flags = 0;
@@ -232,10 +239,13 @@ void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std
         return;
       }
     }
-    r[0] = (ends > (uint32_t)kClassEnds ? kClassMore : ends) | flags;
-    r[1] = cur | qe[0] << 16;
-    r[2] = qe[1] | qe[2] << 16;
-    r[3] = pe[0] | pe[1] << 8 | pe[2] << 16;
+    if (!reduced) {
+      r[0] = (ends > (uint32_t)kClassEnds ? kClassMore : ends) | flags;
+      r[1] = cur | qe[0] << 16;
+      r[2] = qe[1] | qe[2] << 16;
+      r[3] = pe[0] | pe[1] << 8 | pe[2] << 16;
+      return;
+    }
     const bool more = kept > (uint32_t)kClassEnds;
     for (int j = 0; j < kClassEnds; ++j)
       if (!asks[kq[j]]) {
@@ -243,10 +253,10 @@ void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std
         if (!(more && j == kClassEnds - 1)) ke[j] = 0;
       }
     const uint32_t st = more || !asks_trail[cur] ? 0u : start;
-    p[0] = (more ? kClassMore : kept) | kflags | ks[1] << 8 | ks[2] << 16 | st << 24;
-    p[1] = (more ? 0u : last[cur]) | kq[0] << 16;
-    p[2] = kq[1] | kq[2] << 16;
-    p[3] = ke[0] | ke[1] << 8 | ke[2] << 16 | ks[0] << 24;
+    r[0] = (more ? kClassMore : kept) | kflags | ks[1] << 8 | ks[2] << 16 | st << 24;
+    r[1] = (more ? 0u : last[cur]) | kq[0] << 16;
+    r[2] = kq[1] | kq[2] << 16;
+    r[3] = ke[0] | ke[1] << 8 | ke[2] << 16 | ks[0] << 24;
   };
   struct Key {
     uint32_t a, b, c, d;
@@ -259,74 +269,73 @@ void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std
       return (size_t)(h ^ (h >> 29));
     }
   };
-  // one table's classes of one state: the records and every spelling's class
-  struct State {
-    std::unordered_map<Key, uint32_t, KeyHash> seen;
-    std::vector<uint16_t> local;
-    void start(std::vector<uint32_t>& rq) {
-      seen.clear();
-      rq = {kClassReject, 0, 0, 0, kClassWalk, 0, 0, 0};  // local classes 0 and 1
-    }
-    void add(std::vector<uint32_t>& rq, size_t u, const uint32_t (&r)[4]) {
-      auto it = seen.find(Key{r[0], r[1], r[2], r[3]});
-      if (it != seen.end()) {
-        local[u] = (uint16_t)it->second;
-        return;
-      }
-      const uint32_t c = (uint32_t)(rq.size() / 4);
-      if (c >= kClassMaxLocal) {  // beyond capacity: this token walks its bytes
-        local[u] = 1;
-        return;
-      }
-      seen.emplace(Key{r[0], r[1], r[2], r[3]}, c);
-      rq.insert(rq.end(), {r[0], r[1], r[2], r[3]});
-      local[u] = (uint16_t)c;
-    }
-  };
-  ClassTables* const out[2] = {&full, &reduced};
-  std::vector<std::vector<uint32_t>> recs[2];
-  for (int k = 0; k < 2; ++k) {
-    out[k]->map.assign(S * V, 0);
-    recs[k].resize(S);
-  }
-  const int nt = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  std::vector<std::thread> pool;
-  for (int w = 0; w < nt; ++w)
-    pool.emplace_back([&, w]() {
-      State st[2];
-      for (State& x : st) x.local.resize(U);
-      for (size_t q = (size_t)w; q < S; q += (size_t)nt) {
-        for (int k = 0; k < 2; ++k) st[k].start(recs[k][q]);
+  ClassTables ct;
+  ct.map.assign(S * V, 0);
+  std::vector<std::vector<uint32_t>> recs(S);
+  // the states are dealt to the threads in turn, this one among them; the first
+  // exception of any ends the rest and is thrown here
+  std::atomic<size_t> next{0};
+  std::exception_ptr failed;
+  std::mutex failed_mu;
+  auto work = [&]() {
+    try {
+      std::vector<uint16_t> local(U);
+      std::unordered_map<Key, uint32_t, KeyHash> seen;
+      for (size_t q = next++; q < S; q = next++) {
+        seen.clear();
+        std::vector<uint32_t>& rq = recs[q];
+        rq = {kClassReject, 0, 0, 0, kClassWalk, 0, 0, 0};  // local classes 0 and 1
         for (size_t u = 0; u < U; ++u) {
-          uint32_t r[4], p[4];
-          program((uint32_t)q, u, r, p);
+          uint32_t r[4];
+          program((uint32_t)q, u, r);
           if (r[0] & kClassReject) {
-            st[0].local[u] = st[1].local[u] = 0;
+            local[u] = 0;
             continue;
           }
-          st[0].add(recs[0][q], u, r);
-          st[1].add(recs[1][q], u, p);
-        }
-        for (int k = 0; k < 2; ++k) {
-          uint16_t* m = out[k]->map.data() + q * V;
-          for (size_t id = 0; id < V; ++id) {
-            const uint32_t u = va.spell_of_id[id];
-            m[id] = u == 0xFFFFFFFFu ? (uint16_t)0 : st[k].local[u];
+          auto it = seen.find(Key{r[0], r[1], r[2], r[3]});
+          if (it != seen.end()) {
+            local[u] = (uint16_t)it->second;
+            continue;
           }
+          const uint32_t c = (uint32_t)(rq.size() / 4);
+          if (c >= kClassMaxLocal) {  // beyond capacity: this token walks its bytes
+            local[u] = 1;
+            continue;
+          }
+          seen.emplace(Key{r[0], r[1], r[2], r[3]}, c);
+          rq.insert(rq.end(), {r[0], r[1], r[2], r[3]});
+          local[u] = (uint16_t)c;
+        }
+        uint16_t* m = ct.map.data() + q * V;
+        for (size_t id = 0; id < V; ++id) {
+          const uint32_t u = va.spell_of_id[id];
+          m[id] = u == 0xFFFFFFFFu ? (uint16_t)0 : local[u];
         }
       }
-    });
-  for (auto& th : pool) th.join();
-  for (int k = 0; k < 2; ++k) {
-    ClassTables& ct = *out[k];
-    ct.off.assign(S + 1, 0);
-    for (size_t q = 0; q < S; ++q) {
-      ct.off[q + 1] = ct.off[q] + (uint32_t)(recs[k][q].size() / 4);
-      ct.max_classes = std::max(ct.max_classes, ct.off[q + 1] - ct.off[q]);
+    } catch (...) {
+      next = S;
+      std::lock_guard<std::mutex> lock(failed_mu);
+      if (!failed) failed = std::current_exception();
     }
-    ct.rec.reserve((size_t)ct.off[S] * 4);
-    for (size_t q = 0; q < S; ++q) ct.rec.insert(ct.rec.end(), recs[k][q].begin(), recs[k][q].end());
+  };
+  const int nt = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  std::vector<std::thread> pool;
+  pool.reserve((size_t)nt);
+  try {
+    for (int w = 1; w < nt; ++w) pool.emplace_back(work);
+  } catch (const std::system_error&) {  // no more threads: those there are do the work
   }
+  work();
+  for (auto& th : pool) th.join();
+  if (failed) std::rethrow_exception(failed);
+  ct.off.assign(S + 1, 0);
+  for (size_t q = 0; q < S; ++q) {
+    ct.off[q + 1] = ct.off[q] + (uint32_t)(recs[q].size() / 4);
+    ct.max_classes = std::max(ct.max_classes, ct.off[q + 1] - ct.off[q]);
+  }
+  ct.rec.reserve((size_t)ct.off[S] * 4);
+  for (size_t q = 0; q < S; ++q) ct.rec.insert(ct.rec.end(), recs[q].begin(), recs[q].end());
+  return ct;
 }
 
 uint32_t LexiconStore::child(int slot, uint32_t node, uint8_t b) const {

@@ -65,7 +65,7 @@ extern "C" int grid_compile(const grid_compile_args* a, grid_compiled** out) {
     }
     g->vocab = build_vocab(a->vocab_bytes, a->vocab_offsets, a->vocab_size, a->special_ids,
                            a->n_special, a->eos_id);
-    build_class_tables(g->dfa, g->vocab, g->term_info, g->classes, g->progs);
+    check_class_map(g->dfa, g->vocab);
     add_lexicon(g->lex, g->dfa, g->gram, g->vocab, g->term_cat, {});  // slot 0: no restrictions
     // FNV-1a over the tables a cached mask row depends on
     uint32_t fp = 2166136261u;
@@ -174,11 +174,7 @@ void put(const std::vector<T>& v, const void** p, size_t* n) {
   *p = v.data();
   *n = v.size() * sizeof(T);
 }
-}  // namespace
-
-extern "C" int grid_artifact(const grid_compiled* g, int32_t which, const void** p, size_t* n) {
-  clear_error();
-  if (!g || !p || !n) return fail(GRID_E_ARG, "null argument");
+int find_artifact(const grid_compiled* g, int32_t which, const void** p, size_t* n) {
   switch (which) {
     case GRID_ART_DFA_DENSE: put(g->dfa.dense, p, n); break;
     case GRID_ART_DFA_CLASS: put(g->dfa.next, p, n); break;
@@ -204,12 +200,12 @@ extern "C" int grid_artifact(const grid_compiled* g, int32_t which, const void**
     case GRID_ART_LEX_PREFIX: put(g->lex.prefix, p, n); break;
     case GRID_ART_SPELL_RANGE: put(g->vocab.sub_range, p, n); break;
     case GRID_ART_SPELL_OF_ID: put(g->vocab.spell_of_id, p, n); break;
-    case GRID_ART_CLASS_MAP: put(g->classes.map, p, n); break;
-    case GRID_ART_CLASS_OFF: put(g->classes.off, p, n); break;
-    case GRID_ART_CLASS_REC: put(g->classes.rec, p, n); break;
-    case GRID_ART_PROG_MAP: put(g->progs.map, p, n); break;
-    case GRID_ART_PROG_OFF: put(g->progs.off, p, n); break;
-    case GRID_ART_PROG_REC: put(g->progs.rec, p, n); break;
+    case GRID_ART_CLASS_MAP: put(g->classes().map, p, n); break;
+    case GRID_ART_CLASS_OFF: put(g->classes().off, p, n); break;
+    case GRID_ART_CLASS_REC: put(g->classes().rec, p, n); break;
+    case GRID_ART_PROG_MAP: put(g->progs().map, p, n); break;
+    case GRID_ART_PROG_OFF: put(g->progs().off, p, n); break;
+    case GRID_ART_PROG_REC: put(g->progs().rec, p, n); break;
     case GRID_ART_LEX_STRIDE: put(g->lex.stride, p, n); break;
     case GRID_ART_LEX_TOKEN: put(g->lex.token, p, n); break;
     case GRID_ART_ID_FIRST: put(g->vocab.id_first, p, n); break;
@@ -225,6 +221,17 @@ extern "C" int grid_artifact(const grid_compiled* g, int32_t which, const void**
     default: return fail(GRID_E_ARG, "unknown artifact " + std::to_string(which));
   }
   return GRID_OK;
+}
+}  // namespace
+
+extern "C" int grid_artifact(const grid_compiled* g, int32_t which, const void** p, size_t* n) {
+  clear_error();
+  if (!g || !p || !n) return fail(GRID_E_ARG, "null argument");
+  try {
+    return find_artifact(g, which, p, n);
+  } catch (const std::exception& e) {  // the class tables are built when they are asked for
+    return fail(GRID_E_CAPACITY, std::string("class tables: ") + e.what());
+  }
 }
 
 extern "C" int grid_bind_device(grid_compiled* g, int32_t which, void* dev) {

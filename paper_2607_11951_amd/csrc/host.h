@@ -1,6 +1,7 @@
 // host.h -- host-side artifacts of a compiled grammar + vocabulary + lexicons.
 #pragma once
 
+#include <atomic>
 #include <cstdint>
 #include <map>
 #include <memory>
@@ -146,10 +147,22 @@ struct ClassTables {
   std::vector<uint32_t> rec;   // [classes][4]
   uint32_t max_classes = 0;    // largest class count of one state
 };
-// The class tables of the exported lexeme programs, and those of the reduced
-// programs the kernels read (lexhash.h).
-void build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
-                        ClassTables& full, ClassTables& reduced);
+// The class tables of the lexeme programs, or those of the reduced programs
+// (lexhash.h).
+ClassTables build_class_tables(const LexerDfa& dfa, const VocabArtifacts& va, const std::vector<uint32_t>& term_info,
+                               bool reduced);
+// Throws when a class map would be too large.
+void check_class_map(const LexerDfa& dfa, const VocabArtifacts& va);
+
+// Class tables built when they are first asked for: a program binds the reduced
+// programs' or the full ones', and each kind takes 2 bytes per lexer state and
+// token (138 MB for the DML grammar on 151,936 tokens) and about as long as all
+// the rest of the compilation.
+struct LazyClasses {
+  std::mutex mu;
+  std::atomic<bool> built{false};
+  ClassTables tables;
+};
 
 // ---- lexicon slots
 struct LexiconStore {
@@ -187,9 +200,21 @@ struct grid_compiled {
   grid::Parser parser;
   grid::VocabArtifacts vocab;
   grid::LexiconStore lex;
-  grid::ClassTables classes;          // lexeme-program classes
-  grid::ClassTables progs;            // those of the reduced programs
-  uint32_t max_classes() const { return classes.max_classes > progs.max_classes ? classes.max_classes : progs.max_classes; }
+  mutable grid::LazyClasses lazy_classes, lazy_progs;
+  const grid::ClassTables& classes() const { return lazy(lazy_classes, false); }  // lexeme-program classes
+  const grid::ClassTables& progs() const { return lazy(lazy_progs, true); }       // those of the reduced programs
+  // The classes the kernels read: those of the reduced programs when these are
+  // bound, else the full ones.
+  bool uses_progs() const { return dev[GRID_ART_PROG_MAP] && dev[GRID_ART_PROG_OFF] && dev[GRID_ART_PROG_REC]; }
+  bool uses_classes() const {
+    return !uses_progs() && dev[GRID_ART_CLASS_MAP] && dev[GRID_ART_CLASS_OFF] && dev[GRID_ART_CLASS_REC];
+  }
+  // Largest class count of one lexer state in the tables in use; with neither
+  // bound, in either.
+  uint32_t max_classes() const {
+    const uint32_t c = uses_progs() ? 0u : classes().max_classes, p = uses_classes() ? 0u : progs().max_classes;
+    return c > p ? c : p;
+  }
   uint32_t fingerprint = 0;           // of the lexer, parser and vocabulary (mask-cache entries)
   uint32_t family_fp = 0;             // of the lexer and vocabulary only (shared by every role)
   std::vector<int> term_cat;          // category index per terminal or -1
@@ -199,4 +224,16 @@ struct grid_compiled {
   std::shared_ptr<void> writer;       // completion-writer tables (complete.cpp)
   void* dev[GRID_ART_COUNT] = {};
   size_t dev_bytes[GRID_ART_COUNT] = {};
+
+ private:
+  const grid::ClassTables& lazy(grid::LazyClasses& lc, bool reduced) const {
+    if (!lc.built.load(std::memory_order_acquire)) {
+      std::lock_guard<std::mutex> lock(lc.mu);
+      if (!lc.built.load(std::memory_order_relaxed)) {
+        lc.tables = grid::build_class_tables(dfa, vocab, term_info, reduced);
+        lc.built.store(true, std::memory_order_release);
+      }
+    }
+    return lc.tables;
+  }
 };

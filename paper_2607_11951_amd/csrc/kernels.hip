@@ -3182,13 +3182,20 @@ int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint1
 
 int grid::overlay_capacity() { return kFastLane; }
 
+// 0 when the class tables, built here if nothing has asked for them yet, do not
+// fit into memory.
 static size_t row_bytes(const grid_compiled* g) {
-  return row_layout(g->parser.T, g->dfa.S, g->vocab.V, (int)g->max_classes()).total;
+  try {
+    return row_layout(g->parser.T, g->dfa.S, g->vocab.V, (int)g->max_classes()).total;
+  } catch (const std::exception&) {
+    return 0;
+  }
 }
 
-// head, B rows, then the number of open ids of every row
+// head, B rows, then the number of open ids of every row (0 as row_bytes)
 static size_t workspace_size(const grid_compiled* g, int B) {
-  return kWsHead + row_bytes(g) * (size_t)B + (((size_t)B * 4 + 255) & ~(size_t)255);
+  const size_t rb = row_bytes(g);
+  return rb ? kWsHead + rb * (size_t)B + (((size_t)B * 4 + 255) & ~(size_t)255) : 0;
 }
 
 extern "C" size_t grid_mask_workspace_bytes(const grid_compiled* g, int32_t B) {
@@ -3213,7 +3220,7 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   for (int w : needed)
     if (!bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
   // the classes: of the reduced programs, or of the full ones where those are not bound
-  const bool prog = g->dev[GRID_ART_PROG_MAP] && g->dev[GRID_ART_PROG_OFF] && g->dev[GRID_ART_PROG_REC];
+  const bool prog = g->uses_progs();
   for (int w : {GRID_ART_CLASS_MAP, GRID_ART_CLASS_OFF, GRID_ART_CLASS_REC})
     if (!prog && !bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
   tb.dfa = (const uint16_t*)g->dev[GRID_ART_DFA_CLASS];
@@ -3248,7 +3255,7 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.cmap = (const uint16_t*)g->dev[prog ? GRID_ART_PROG_MAP : GRID_ART_CLASS_MAP];
   tb.coff = (const uint32_t*)g->dev[prog ? GRID_ART_PROG_OFF : GRID_ART_CLASS_OFF];
   tb.crec = (const uint4*)g->dev[prog ? GRID_ART_PROG_REC : GRID_ART_CLASS_REC];
-  tb.max_classes = (int)g->max_classes();
+  tb.max_classes = 0;  // (only the mask reads classes)
   tb.S = g->dfa.S;
   tb.C = g->dfa.C;
   tb.T = g->parser.T;
@@ -3291,11 +3298,13 @@ static int mask_call(const grid_compiled* g, int32_t B, const grid_config* cfg_d
   if (!g || B <= 0 || B > 65535 || !cfg_dev || !stack_pool_dev || !mask_dev || !workspace_dev)
     return fail(GRID_E_ARG, "grid_mask: null pointer or batch size out of range");
   const size_t rb = row_bytes(g);
+  if (rb == 0) return fail(GRID_E_CAPACITY, "grid_mask: out of memory for the class tables");
   if (workspace_bytes < workspace_size(g, B)) return fail(GRID_E_ARG, "grid_mask: workspace too small");
   if (((uintptr_t)workspace_dev & 255) != 0) return fail(GRID_E_ARG, "grid_mask: workspace not 256-byte aligned");
   Tables tb;
   const int brc = bind_tables(g, tb);
   if (brc != GRID_OK) return brc;
+  tb.max_classes = (int)g->max_classes();  // (built above)
   tb.cache = nullptr;
   tb.cache_mask = 0;
   tb.cache_flags = 0;

@@ -184,3 +184,68 @@ def test_runs_of_empty_reductions_compile_in_time(G):
     # 2^41 reductions: a grammar like any other for the compiler
     tb = Tables(G.Grid(nullable_grammar(40), (), [b"x"]))
     assert tb.act[0].tolist().count(0) < tb.T + 1 and (tb.act[0] & 0xC000 == 0xC000).any()
+
+
+_MEMORY = """
+import ctypes, numpy as np, paper_2607_11951_amd as G
+from workloads import configs as W, grammar_text, schema as sch, vocab as voc
+def held():
+    ctypes.CDLL(None).malloc_trim(0)
+    return int(open("/proc/self/statm").read().split()[1]) * 4096
+banned = sch.keyword_spellings(W.GRAMMAR_DIR / "sql_dml.grid")
+s = sch.make_schema(np.random.default_rng(3002), 200, 30, 30, banned)
+vocab, specials, eos = voc.geometric_vocab(3000, sorted(banned), list(s.tables) + s.all_columns()[:2000], 50257)
+def compiled():
+    return G.Grid(grammar_text("sql_dml"), W.READ_ONLY_ROLE, vocab, specials, eos)
+first = compiled()  # (the allocator's own growth)
+before = held()
+g = compiled()
+p, n, prog, maps = ctypes.c_void_p(), ctypes.c_size_t(), 0, 0
+after = held() - before
+for name in ("PROG_MAP", "PROG_OFF", "PROG_REC"):
+    assert G.lib().grid_artifact(g.h, G.grid.ART[name], ctypes.byref(p), ctypes.byref(n)) == 0
+    prog += n.value
+    maps = max(maps, n.value)
+print(after, held() - before, maps, prog)
+"""
+
+
+def test_class_tables_only_where_asked_for():
+    """A handle holds the class tables that were asked for: none after the
+    compilation, one map (not both) once the reduced programs' are read."""
+    import subprocess
+    import sys
+    from pathlib import Path
+    out = subprocess.run([sys.executable, "-c", _MEMORY], capture_output=True, text=True, check=True,
+                         cwd=Path(__file__).resolve().parent.parent, timeout=300).stdout
+    after, in_all, one_map, prog = map(int, out.split())
+    assert after < one_map
+    assert in_all < after + prog * 7 // 4  # (some of it the heap's, not given back)
+
+
+def test_class_tables_in_any_order(G):
+    """The tables, the workspace and the sizes do not depend on what was asked
+    for first, from how many threads, or what is bound."""
+    from concurrent.futures import ThreadPoolExecutor
+    import ctypes
+    from workloads import make_workload
+    wl = make_workload(2, rows=1)
+    kinds = [[f"{k}_{x}" for x in ("MAP", "OFF", "REC")] for k in ("PROG", "CLASS")]
+
+    def fresh():
+        return G.from_workload(wl)[0]
+
+    a, b, c = fresh(), fresh(), fresh()
+    got_a = {n: a.artifact(n) for k in kinds for n in k}
+    got_b = {n: b.artifact(n) for k in reversed(kinds) for n in k}
+    with ThreadPoolExecutor(8) as pool:
+        got_c = list(pool.map(lambda n: (n, c.artifact(n)), [n for k in kinds for n in k] * 4))
+    assert got_a == got_b and all(v == got_a[n] for n, v in got_c)
+    size = {}
+    for k in kinds:  # (binding reads nothing at the address)
+        g = fresh()
+        for n in k:
+            assert G.lib().grid_bind_device(g.h, G.grid.ART[n], ctypes.c_void_p(4096)) == 0
+        size[k[0]] = g.workspace_bytes(4)
+    free = fresh().workspace_bytes(4)
+    assert free == max(size.values())
