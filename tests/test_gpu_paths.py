@@ -203,3 +203,59 @@ def test_status_asked_of_the_last_phase_alone(G, rows):
         assert L.grid_mask_phases(g.h, B, ptr(c), ptr(p), ptr(m), ptr(e), ptr(st), ptr(ws), ws.numel(), phases,
                                   torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(got.cpu(), want.cpu()) and (got.cpu()[::3] == G.ROW_BAD_CONFIG).all()
+
+
+@pytest.mark.parametrize("B", [40, 256, 257, 1100])
+@pytest.mark.parametrize("inplace", [False, True])
+def test_advance_of_batches_with_and_without_tokens(G, B, inplace):
+    """Rows of a batch that may queue for the compute units, most without a
+    token (or with one past the vocabulary), some with a configuration that is
+    none: as the host's advance has them, the others as they were."""
+    wl = make_workload(2, rows=64)
+    g, slots = G.from_workload(wl)
+    g.to_device("cuda")
+    cap, rng = 256, np.random.default_rng(B)
+    base = [g.config(w, slots[wl.slots[i]]) for i, w in enumerate(wl.prefixes)]
+    cfgs, pool = np.zeros(B, G.CONFIG_DTYPE), np.zeros(B * cap, np.uint16)
+    toks = np.full(B, -1, np.int32)
+    for b in range(B):
+        c, st = base[b % len(base)]
+        cfgs[b] = c
+        cfgs[b]["stk_off"] = b * cap
+        pool[b * cap:b * cap + len(st)] = st
+        kind = rng.integers(0, 6)
+        if kind < 2:
+            toks[b] = int(rng.integers(0, wl.V))
+        elif kind == 2:
+            toks[b] = wl.V + int(rng.integers(0, 5))
+        elif kind == 3:
+            toks[b] = int(rng.integers(0, wl.V))
+            cfgs[b]["q"] = 0
+    hashes = torch.arange(B * cap, dtype=torch.int64, device="cuda")
+    c, p = g.configs_to_device(cfgs, pool)
+    ids = torch.from_numpy(toks).cuda()
+    if inplace:
+        st = g.accept_inplace(c, p, ids, B, cap, stack_hash=hashes)
+        c2, p2 = c, p
+    else:
+        c2, p2, st = g.accept(c, p, ids, B, cap)
+    torch.cuda.synchronize()
+    out, area, st = c2.cpu().numpy().view(G.CONFIG_DTYPE), p2.cpu().numpy().view(np.uint16), st.cpu().numpy()
+    hv, done = hashes.cpu().numpy(), 0
+    for b in range(B):
+        own = slice(b * cap, (b + 1) * cap)
+        if not 0 <= toks[b] < wl.V or cfgs[b]["q"] == 0:
+            assert st[b] == G.ROW_BAD_CONFIG, b
+        w = wl.prefixes[b % len(base)]
+        if st[b] == G.ROW_OK:
+            want, stack = g.config(w + wl.vocab[toks[b]], slots[wl.slots[b % len(base)]])
+            for f in ("q", "lexnode", "flags", "rem_len", "slot", "stk_depth"):
+                assert int(out[b][f]) == int(want[f]), (b, f)
+            assert np.array_equal(area[own][:len(stack)], stack), b
+            done += 1
+            continue
+        d = int(cfgs[b]["stk_depth"])
+        assert out[b].tobytes() == cfgs[b].tobytes(), b
+        assert np.array_equal(area[own][:d], pool[own][:d]), b
+        assert (hv[own] == np.arange(own.start, own.stop)).all(), b
+    assert done > 0
