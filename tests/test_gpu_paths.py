@@ -7,7 +7,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from workloads import make_workload  # noqa: E402
+from test_host_tables import indexed_grammar  # noqa: E402
+from workloads import grammar_text, make_workload  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -68,6 +69,107 @@ def test_tables_in_and_past_lds(G, oracle_mod, statements, words):
     g.to_device("cuda")
     o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
     _check(g, o, [b"", b"k0 ", b"k1 w1", b"k1 w1 ( w1 ( ", b"k1 w1 (w1) w2 (k", b"k3"], slot)
+
+
+def _lds_routes(info):
+    """Whether the LR tables fit beside what else the prologue and the residue
+    kernel keep in LDS (at most 96 KB of them, 156 KB in all)."""
+    NS, T, N, S, C = (info[k] for k in ("n_lr_states", "n_terminals", "n_nonterminals", "n_dfa_states",
+                                        "n_byte_classes"))
+    up = lambda x: (x + 15) // 16 * 16
+    lr = up(NS * (T + 1) * 2) + up(NS * N * 2)
+    row = 256 + 128 + 32 * (1 + T) + up(4 * S) + 32 * T
+    rest = row + 256 + up(4 * T) + 16 * 32 * 16 * 2 + 1024 * (4 + 2 + 4) + 32 * S + up(2 * S * C)
+    return lr <= 96 * 1024, rest + lr <= 156 * 1024
+
+
+# the DML grammar under the roles that may write: its tables are on either side of
+# both kernels' LDS limits
+@pytest.mark.parametrize("drop,routes", [((), (False, False)), (("delete",), (False, False)), (("insert",), (True, False)),
+                                         (("update", "delete"), (True, False)), (("insert", "update"), (True, True))])
+def test_roles_in_and_past_lds(G, oracle_mod, drop, routes):
+    import random
+    from workloads import configs as W, schema as sch, sentences as sen, vocab as voc
+    banned = sch.keyword_spellings(W.GRAMMAR_DIR / "sql_dml.grid")
+    s = sch.make_schema(np.random.default_rng(3002), 30, 8, 12, banned)
+    vocab, specials, eos = voc.geometric_vocab(3000, sorted(banned), list(s.tables) + s.all_columns(), 12000)
+    text, lex = grammar_text("sql_dml"), s.lexicon(with_alias=True)
+    g = G.Grid(text, drop, vocab, specials, eos)
+    assert _lds_routes(g.info()) == routes
+    slot = g.add_lexicon(lex)
+    g.to_device("cuda")
+    o = oracle_mod.Oracle(text, drop, lex, vocab, specials, eos)
+    r, t = random.Random(len(drop)), list(s.tables)[0].encode()
+    texts = [sen.DmlQueryGen(r, s).sentence().encode() for _ in range(12)]
+    texts += [b"INSERT INTO " + t + b" ", b"UPDATE " + t + b" SET ", b"DELETE FROM " + t + b" WHERE "]
+    prefixes = [b""]
+    for w in texts:
+        for cut in {r.randint(0, len(w)), len(w)}:
+            try:
+                g.config(w[:cut], slot)
+            except G.GridError as e:
+                assert "NOT_VIABLE" in str(e)
+                continue
+            prefixes.append(w[:cut])
+    assert len(prefixes) >= 20
+    _check(g, o, prefixes, slot)
+
+
+@pytest.mark.parametrize("names", [66, 70])
+def test_reductions_by_index(G, oracle_mod, names):
+    """Reduce entries that are indices: left sides and pops past 15 bits together."""
+    text = indexed_grammar(names)
+    toks = [b"yy", b"yyyy", b"zx0", b"x0x0", b"x1x0y", b"x0x1", b"yx0x0y", b"zz", b"x0yx0", b"y" * 9, b"x2x0", b"x0" * 11]
+    vocab = [bytes([b]) for b in range(256)] + toks + [b""]
+    eos = len(vocab) - 1
+    g = G.Grid(text, (), vocab, [eos], eos).to_device("cuda")
+    o = oracle_mod.Oracle(text, (), {}, vocab, [eos], eos)
+    prefixes = [b"", b"y", b"z", b"y" * 139, b"y" * 140, b"y" * 140 + b"z"]
+    for w in list(prefixes):  # the tokens each allows, and on from there
+        for _ in range(3):
+            words = o.mask(w, mode=1)[0]
+            t = [i for i in range(len(vocab) - 1) if int(words[i // 32]) >> (i % 32) & 1]
+            if not t:
+                break
+            w = w + vocab[t[len(t) // 2]]
+            prefixes.append(w)
+    _check(g, o, prefixes)
+    # the advance by every allowed token, against the host's
+    rows = [(w, t) for w in prefixes for t in range(256, eos) if o.mask(w, tokens=[t])[0][0]]
+    cfgs, pool = g.configs([w for w, _ in rows])
+    ids = torch.tensor([t for _, t in rows], dtype=torch.int32, device="cuda")
+    c2, _, st = g.accept(*g.configs_to_device(cfgs, pool), ids, len(rows), 512)
+    out = c2.cpu().numpy().view(G.CONFIG_DTYPE)
+    assert (st.cpu().numpy() == G.ROW_OK).all()
+    for r, (w, t) in enumerate(rows):
+        want, stack = g.config(w + vocab[t])
+        assert int(out[r]["q"]) == int(want["q"]) and int(out[r]["stk_depth"]) == len(stack), (r, w, t)
+
+
+@pytest.mark.parametrize("B", [255, 256, 257, 321, 1025])
+def test_more_rows_than_counts_in_registers(G, oracle_mod, B):
+    """Batches around the 256 rows whose counts a lane keeps, some rows with no
+    configuration: every row as in a batch of its own."""
+    wl = make_workload(2, rows=48)
+    g, slots = G.from_workload(wl)
+    g.to_device("cuda")
+    o = oracle_mod.from_workload(wl)
+    want = [o.mask(w, mode=1) for w in wl.prefixes]
+    rng = np.random.default_rng(B)
+    which = rng.integers(0, len(want), B)
+    one, pool = g.configs(wl.prefixes, [slots[i] for i in wl.slots])
+    cfgs = one[which].copy()
+    bad = rng.random(B) < 0.2
+    bad[-1] = False
+    cfgs["q"][bad] = 60000
+    m, e, s = g.mask(*g.configs_to_device(cfgs, pool), B)
+    torch.cuda.synchronize()
+    m, e, s = m.cpu().numpy().view(np.uint32), e.cpu().numpy(), s.cpu().numpy()
+    assert (s[bad] == G.ROW_BAD_CONFIG).all() and not m[bad].any() and not e[bad].any()
+    assert (s[~bad] == 0).all()
+    for b in np.flatnonzero(~bad):
+        words, eos = want[which[b]]
+        assert np.array_equal(m[b], words) and int(e[b]) == eos, b
 
 
 def _statements(n, words):
