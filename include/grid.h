@@ -131,7 +131,8 @@ int grid_add_lexicon(grid_compiled* g, const grid_lexicon_args* lex, int32_t* sl
 /* Device artifacts.  The caller allocates device memory of the reported size,
  * copies the host bytes there and binds the device pointer, which must be
  * 16-byte aligned (the kernels read artifacts with 16-byte loads; GRID_E_ARG
- * otherwise); grid_mask reads only bound artifacts (GRID_E_UNBOUND otherwise).
+ * otherwise); a call whose kernels read an artifact that is not bound fails with
+ * GRID_E_UNBOUND (an empty artifact needs no binding).
  * The device copy stays owned by the caller and must outlive its use. */
 enum {
   GRID_ART_DFA_DENSE = 0,   /* u16 [S][256] next state, 0 = dead */

@@ -107,9 +107,7 @@ struct Tables {
   const uint32_t* pstate;     // [NS][parse_record_words(tw)]
   const uint32_t* predx;
   const uint2* ghash;         // [H]: key, target
-  const uint32_t* spell_off;  // [U+1]
-  const uint8_t* spell_bytes;
-  const uint4* spell_rec;     // [U]: head lo, head hi, first id | multi << 31, length | chunk << 8
+  const uint4* spell_rec;     // [spellings]: head lo, head hi, first id | multi << 31, length | chunk << 8
   const uint4* spell_tail;    // chunk u: bytes 8..23 of spelling u; overflow chunks after
   const uint32_t* spell_of_id;  // [V]
   const uint16_t* lex_flags;
@@ -124,7 +122,7 @@ struct Tables {
   const uint16_t* cmap;       // class of each token per lexer state [S][V]
   const uint32_t* coff;       // [S+1] first class record of each state
   const uint4* crec;          // class records
-  int S, C, T, N, NS, P, U, V, W, n_slots, eos_id;
+  int S, C, T, N, NS, V, W, n_slots, eos_id;
   int max_classes;            // largest class count of one lexer state
   int prog;                   // the classes are those of the reduced programs
   const uint16_t* pshift;      // shift targets per LR state
@@ -3089,7 +3087,12 @@ __global__ __launch_bounds__(64) void stack_hash_kernel(Tables tb, const grid_co
   }
 }
 
-bool bound(const grid_compiled* g, int which) { return g->dev[which] != nullptr || g->dev_bytes[which] == 0; }
+// An artifact that is empty needs no device copy.
+bool bound(const grid_compiled* g, int which) {
+  const void* p = nullptr;
+  size_t n = 0;
+  return g->dev[which] != nullptr || (grid_artifact(g, which, &p, &n) == GRID_OK && n == 0);
+}
 
 // Raises a kernel's dynamic-LDS limit (needed above 64 KB of LDS in total)
 // once per kernel, device and size.
@@ -3209,26 +3212,43 @@ extern "C" size_t grid_mask_workspace_bytes(const grid_compiled* g, int32_t B) {
   return workspace_size(g, B);
 }
 
-// The device tables of a compiled handle (every artifact bound, else
-// GRID_E_UNBOUND).
-static int bind_tables(const grid_compiled* g, Tables& tb) {
-  static const int needed[] = {GRID_ART_DFA_CLASS,   GRID_ART_BYTE_CLASS,  GRID_ART_DFA_ACCEPT_OFF,
-                               GRID_ART_DFA_ACCEPT_LIST, GRID_ART_DFA_LIVE, GRID_ART_ACTION,
-                               GRID_ART_PROD,        GRID_ART_TERM_INFO,   GRID_ART_SPELL_OFF,
-                               GRID_ART_SPELL_BYTES, GRID_ART_SPELL_REC,   GRID_ART_SPELL_TAIL,
-                               GRID_ART_ALIAS_OFF,   GRID_ART_ALIAS_IDS,   GRID_ART_LEX_FLAGS,
-                               GRID_ART_LEX_HASH,    GRID_ART_LEX_SLOTS,   GRID_ART_PARSE_STATE,
-                               GRID_ART_PARSE_REDX,  GRID_ART_GOTO_HASH,   GRID_ART_LEX_PREFIX,
-                               GRID_ART_SPELL_OF_ID, GRID_ART_LEX_STRIDE,  GRID_ART_LEX_TOKEN,
-                               GRID_ART_PARSE_SHIFT, GRID_ART_GOTO_SKIP,
-                               GRID_ART_STATE_SYMBOL, GRID_ART_LEX_CHILD, GRID_ART_ID_HEAD,
-                               GRID_ART_LEX_TOKSUM};
-  for (int w : needed)
-    if (!bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
+// What a call's kernels read.
+enum class Reads { kMask, kAdvance, kAdvanceHash, kStackHash };
+
+// GRID_E_UNBOUND if something is not bound that the call's kernels read.
+static int check_bound(const grid_compiled* g, Reads reads) {
+  static const int lexer[] = {GRID_ART_DFA_CLASS, GRID_ART_BYTE_CLASS,  GRID_ART_DFA_ACCEPT_OFF, GRID_ART_DFA_ACCEPT_LIST,
+                              GRID_ART_DFA_LIVE,  GRID_ART_TERM_INFO,   GRID_ART_SPELL_REC,      GRID_ART_SPELL_TAIL,
+                              GRID_ART_LEX_FLAGS, GRID_ART_LEX_HASH,    GRID_ART_LEX_SLOTS,      GRID_ART_SPELL_OF_ID,
+                              GRID_ART_GOTO_SKIP, GRID_ART_PARSE_SHIFT};
+  static const int mask[] = {GRID_ART_ACTION,     GRID_ART_PROD,    GRID_ART_LEX_PREFIX, GRID_ART_LEX_STRIDE,
+                             GRID_ART_LEX_TOKEN,  GRID_ART_LEX_CHILD, GRID_ART_ID_HEAD,  GRID_ART_LEX_TOKSUM};
+  static const int advance[] = {GRID_ART_PARSE_STATE, GRID_ART_PARSE_REDX, GRID_ART_GOTO_HASH};
+  auto missing = [&](int w) { return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound"); };
+  if (reads != Reads::kStackHash)
+    for (int w : lexer)
+      if (!bound(g, w)) return missing(w);
+  if (reads == Reads::kMask) {
+    for (int w : mask)
+      if (!bound(g, w)) return missing(w);
+    if (!g->uses_progs() && !g->uses_classes())  // the classes are never empty
+      for (int w : {GRID_ART_CLASS_MAP, GRID_ART_CLASS_OFF, GRID_ART_CLASS_REC})
+        if (!g->dev[w]) return missing(w);
+  } else if (reads != Reads::kStackHash) {
+    for (int w : advance)
+      if (!bound(g, w)) return missing(w);
+  }
+  if ((reads == Reads::kAdvanceHash || reads == Reads::kStackHash) && !bound(g, GRID_ART_STATE_SYMBOL))
+    return missing(GRID_ART_STATE_SYMBOL);
+  return GRID_OK;
+}
+
+// The device tables of a compiled handle for a call (GRID_E_UNBOUND as above).
+static int bind_tables(const grid_compiled* g, Tables& tb, Reads reads) {
+  const int rc = check_bound(g, reads);
+  if (rc != GRID_OK) return rc;
   // the classes: of the reduced programs, or of the full ones where those are not bound
   const bool prog = g->uses_progs();
-  for (int w : {GRID_ART_CLASS_MAP, GRID_ART_CLASS_OFF, GRID_ART_CLASS_REC})
-    if (!prog && !bound(g, w)) return fail(GRID_E_UNBOUND, "artifact " + std::to_string(w) + " is not bound");
   tb.dfa = (const uint16_t*)g->dev[GRID_ART_DFA_CLASS];
   tb.bclass = (const uint8_t*)g->dev[GRID_ART_BYTE_CLASS];
   tb.acc_off = (const uint32_t*)g->dev[GRID_ART_DFA_ACCEPT_OFF];
@@ -3241,8 +3261,6 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.pshift = (const uint16_t*)g->dev[GRID_ART_PARSE_SHIFT];
   tb.go = (const uint16_t*)g->dev[GRID_ART_GOTO_SKIP];
   tb.ghash = (const uint2*)g->dev[GRID_ART_GOTO_HASH];
-  tb.spell_off = (const uint32_t*)g->dev[GRID_ART_SPELL_OFF];
-  tb.spell_bytes = (const uint8_t*)g->dev[GRID_ART_SPELL_BYTES];
   tb.spell_rec = (const uint4*)g->dev[GRID_ART_SPELL_REC];
   tb.spell_tail = (const uint4*)g->dev[GRID_ART_SPELL_TAIL];
   tb.lex_flags = (const uint16_t*)g->dev[GRID_ART_LEX_FLAGS];
@@ -3267,8 +3285,6 @@ static int bind_tables(const grid_compiled* g, Tables& tb) {
   tb.T = g->parser.T;
   tb.N = g->parser.N;
   tb.NS = g->parser.n_states;
-  tb.P = (int)g->parser.prod.size();
-  tb.U = (int)g->vocab.spell_off.size() - 1;
   tb.V = g->vocab.V;
   tb.W = (g->vocab.V + 31) / 32;
   tb.n_slots = g->lex.n_slots;
@@ -3308,7 +3324,7 @@ static int mask_call(const grid_compiled* g, int32_t B, const grid_config* cfg_d
   if (workspace_bytes < workspace_size(g, B)) return fail(GRID_E_ARG, "grid_mask: workspace too small");
   if (((uintptr_t)workspace_dev & 255) != 0) return fail(GRID_E_ARG, "grid_mask: workspace not 256-byte aligned");
   Tables tb;
-  const int brc = bind_tables(g, tb);
+  const int brc = bind_tables(g, tb, Reads::kMask);
   if (brc != GRID_OK) return brc;
   tb.max_classes = (int)g->max_classes();  // (built above)
   tb.cache = nullptr;
@@ -3389,7 +3405,7 @@ extern "C" int grid_stack_hash(const grid_compiled* g, int32_t B, const grid_con
   if (!g || B <= 0 || !cfg_dev || !stack_pool_dev || !stack_hash_dev)
     return fail(GRID_E_ARG, "grid_stack_hash: null pointer or bad batch size");
   Tables tb;
-  const int rc = bind_tables(g, tb);
+  const int rc = bind_tables(g, tb, Reads::kStackHash);
   if (rc != GRID_OK) return rc;
   hipLaunchKernelGGL(stack_hash_kernel, dim3((unsigned)((B + 15) / 16)), dim3(64), 0, (hipStream_t)stream, tb, cfg_dev,
                      stack_pool_dev, stack_hash_dev, B);
@@ -3477,7 +3493,7 @@ static int accept_call(const grid_compiled* g, int32_t B, const grid_config* cfg
                        uint32_t stack_cap, int32_t* status_dev, int inplace, void* stream, int tok_stride = 1,
                        bool few_tokens = false) {
   Tables tb;
-  const int rc = bind_tables(g, tb);
+  const int rc = bind_tables(g, tb, hash_dev ? Reads::kAdvanceHash : Reads::kAdvance);
   if (rc != GRID_OK) return rc;
   if (tb.T > 255) return fail(GRID_E_CAPACITY, "grid_accept: more than 255 terminals");
   const ParseLds PL = prologue_parse_lds(tb);

@@ -249,3 +249,56 @@ def test_class_tables_in_any_order(G):
         size[k[0]] = g.workspace_bytes(4)
     free = fresh().workspace_bytes(4)
     assert free == max(size.values())
+
+
+READ = {  # what the kernels of each call read
+    "stack_hash": {"STATE_SYMBOL"},
+    "accept": {"DFA_CLASS", "BYTE_CLASS", "DFA_ACCEPT_OFF", "DFA_ACCEPT_LIST", "DFA_LIVE", "TERM_INFO", "SPELL_REC",
+               "SPELL_TAIL", "LEX_FLAGS", "LEX_HASH", "LEX_SLOTS", "SPELL_OF_ID", "GOTO_SKIP", "PARSE_SHIFT",
+               "PARSE_STATE", "PARSE_REDX", "GOTO_HASH"},
+}
+READ["mask"] = (READ["accept"] - {"PARSE_STATE", "PARSE_REDX", "GOTO_HASH"}) | {
+    "ACTION", "PROD", "LEX_PREFIX", "LEX_STRIDE", "LEX_TOKEN", "LEX_CHILD", "ID_HEAD", "LEX_TOKSUM"}
+
+
+@pytest.mark.parametrize("call", ["mask", "accept", "stack_hash"])
+def test_calls_on_unbound_artifacts_are_refused(G, call):
+    """Without a GPU a call that is not refused fails at its launch."""
+    import ctypes
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("binds addresses that are none; refusals only")
+    from workloads import make_workload
+    wl = make_workload(1, rows=1)
+    unbound = -9  # GRID_E_UNBOUND
+    fake = lambda: ctypes.c_void_p(1 << 20)
+
+    def run(g):
+        n = G.lib().grid_mask_workspace_bytes(g.h, 1) if call == "mask" else 0
+        if call == "mask":
+            return G.lib().grid_mask(g.h, 1, fake(), fake(), fake(), fake(), fake(), fake(), n, None)
+        if call == "accept":
+            return G.lib().grid_accept(g.h, 1, fake(), fake(), fake(), fake(), fake(), 64, fake(), None)
+        return G.lib().grid_stack_hash(g.h, 1, fake(), fake(), fake(), None)
+
+    def handle(names):
+        g = G.from_workload(wl)[0]
+        for n in names:
+            assert G.lib().grid_bind_device(g.h, G.grid.ART[n], fake()) == 0
+        return g
+
+    classes = [set(), {"PROG_MAP", "PROG_OFF", "PROG_REC"}, {"CLASS_MAP", "CLASS_OFF", "CLASS_REC"}]
+    empty = {n for n in READ[call] if not G.from_workload(wl)[0].artifact(n)}
+    assert run(handle(())) == unbound
+    if call == "mask":
+        for some in classes[1:]:
+            assert run(handle(READ[call] | some)) not in (0, unbound)
+            assert run(handle(READ[call] | set(sorted(some)[1:]))) == unbound
+        assert run(handle(READ[call])) == unbound
+    else:
+        assert run(handle(READ[call])) not in (0, unbound)
+    full = READ[call] | (classes[1] if call == "mask" else set())
+    for left_out in sorted(READ[call] - empty):
+        assert run(handle(full - {left_out})) == unbound, left_out
+    for n in empty:
+        assert run(handle(full - {n})) not in (0, unbound), n
