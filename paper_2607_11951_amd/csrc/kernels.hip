@@ -618,10 +618,10 @@ __device__ __forceinline__ bool lr_commit(const Tables& tb, uint32_t a, uint32_t
   if (a & kMactPushed) {  // the states the empty reductions push first (rare: the LALR tables in global memory)
     const uint32_t floor = m, T1 = (uint32_t)tb.T + 1u;
     uint32_t top = s;
-    for (int guard = 0;; ++guard) {
+    int guard = 0;
+    for (; guard < kGuard; ++guard) {
       const uint32_t la = tb.action[top * T1 + x];
       if ((la & 0xC000u) != kActReduce) break;
-      if (guard >= kGuard) return false;
       const uint32_t pr = tb.prod[la & 0x3FFFu], len = pr >> 16;
       if (len > m - floor) return false;
       m -= len;
@@ -630,6 +630,7 @@ __device__ __forceinline__ bool lr_commit(const Tables& tb, uint32_t a, uint32_t
       ov[m++] = (uint16_t)g;
       top = g;
     }
+    if (guard == kGuard) return false;
   }
   if (m >= cap) return false;
   ov[m++] = (uint16_t)(a & 0x3FFFu);
