@@ -89,7 +89,8 @@ struct Parser {
   int tw = 0;
   std::vector<uint32_t> pstate;
   std::vector<uint32_t> predx;     // extra reduce groups: [production][bits TW]
-  std::vector<uint16_t> pshift;    // shift targets per state, in terminal order (record word 2TW+2);
+  std::vector<uint16_t> pshift;    // shift targets per state, in terminal order (record word 2TW+2: LALR,
+                                   // 2TW+3: past unit states);
                                    // from entry mact_off: the mask kernels' action table (u16 [states][T+1])
   uint32_t mact_off = 0;           // a multiple of 8
   uint32_t n_shift_runs = 0;       // entries of pshift before it

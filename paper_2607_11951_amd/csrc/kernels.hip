@@ -83,11 +83,10 @@ constexpr int kQueue = kChunkMax + kStepIds;  // and at most (a whole last step)
 constexpr int kTableThreads = kResThreads - kChunkMax;  // those that take no listed id stage the tables
 constexpr int kCountRegs = 4;        // rows' counts a lane keeps
 constexpr int kLanesMax = 32;        // ids a wave takes at a time, at most
-constexpr int kFastLane = 16;        // per-lane stack area of a byte walk (overlay at the
-                                     // bottom, virtual pushes above it)
+constexpr int kFastLane = 16;        // per-lane stack area of a walk: its overlay
 constexpr int kSlowLane = 512;       // the same for a walk that outgrew it
 constexpr int kSlowWaves = kResWaves * kLanesMax * kFastLane / kSlowLane;  // walks that fit in its place
-static_assert(kStackWin == kBlock, "one stack-window entry per prologue thread");
+static_assert(kStackWin <= kProThreads, "a prologue thread per stack-window entry");
 constexpr uint32_t kLdsMax = 160 * 1024;
 constexpr uint32_t kLdsStatic = 4096;     // LDS the judge and mask kernels declare statically, at most
 constexpr uint32_t kTablesMax = 133328;   // lexer and LR tables, the largest that are supported
@@ -309,9 +308,9 @@ __device__ inline uint32_t dma_regions(const StageRegion (&rg)[N], int tid, int 
 __device__ inline void dma_wait() { __builtin_amdgcn_s_waitcnt(0); }
 
 // ------------------------------------------------------- compact LR tables
-// The tables and the lanes' stack areas sit in LDS in the prologue and the
-// walk (L = true), where LDS-typed pointers make every access an LDS load;
-// the rare slow path (L = false) reads them from global memory.
+// Those of the device advance.  The tables and the stack sit in LDS (L = true),
+// where LDS-typed pointers make every access an LDS load; a row whose stack
+// outgrows its area, or tables too large, are read from global memory (L = false).
 #define GRID_LDS __attribute__((address_space(3)))
 template <bool L, class T>
 struct MemSpace;
@@ -442,17 +441,15 @@ __device__ __forceinline__ uint32_t action_of(const ParseTabs<L>& pt, uint32_t s
   return a;
 }
 
-// Target of the shift of terminal x in state s (x's shift bit is set): entry
-// (shift bits below x) of the state's run of shift targets -- the mask run,
-// where a shift into a unit state goes straight to where its reduction leads,
-// or with lalr the LALR targets (stacks the device advance hands back).
+// LALR target of the shift of terminal x in state s (x's shift bit is set): entry
+// (shift bits below x) of the state's run of shift targets.
 template <bool L, int MW>
-__device__ __forceinline__ uint16_t shift_target(const ParseTabs<L>& pt, uint32_t s, int x, bool lalr = false) {
+__device__ __forceinline__ uint16_t shift_target(const ParseTabs<L>& pt, uint32_t s, int x) {
   constexpr int R = parse_record_words(MW);
-  static_assert(2 * MW + 3 < R, "the record holds both shift runs");
+  static_assert(2 * MW + 2 < R, "the record holds its shift run");
   const mptr<L, const uint32_t> rec = pt.st + s * (uint32_t)R;
   const uint32_t w = (uint32_t)x >> 5;
-  uint32_t rank = 0, base = rec[2 * MW + (lalr ? 2 : 3)];
+  uint32_t rank = 0, base = rec[2 * MW + 2];
 #pragma unroll
   for (int k = 0; k < MW; ++k) {
     const uint32_t bits = rec[k];
@@ -1247,11 +1244,8 @@ struct DfaView {  // lexer DFA by byte class (LDS copy or global)
 constexpr uint32_t kVerdictReject = 0, kVerdictAllow = 1, kVerdictWalk = 2, kVerdictLexicon = 3;
 constexpr uint32_t kCodeCi = 4;  // beside kVerdictAllow in a class's byte: its tokens are context-independent
 
-// Answers of a lexicon policy besides flags: the question is open (no
-// answer: the class is decided by the lexicon), or the lexeme is out of
-// reach of the lookup tables (the token takes the byte walk).  kLexOpen also
-// marks a lexeme whose flags were not asked for yet.
-constexpr uint32_t kLexOpen = 0xFFFFFFFFu, kLexOut = 0xFFFFFFFEu;
+// A lexeme whose lexicon flags were not asked for yet.
+constexpr uint32_t kLexOpen = 0xFFFFFFFFu;
 
 // Verdict of one lexeme-program class, or of one of its tokens, for a row.  The
 // lexemes the token ends are judged in order against the allowed set the parser
@@ -2187,7 +2181,7 @@ __device__ __forceinline__ int find_chunk(const uint32_t* counts, const uint32_t
 // An id whose lane's stack area was too small is judged again at the end with a
 // large one.  Allowed ids are OR-ed into the mask.  The last chunk of a row to
 // end writes the row's status (a row without open ids gets it from one thread).
-// (Per id the work is a chain of dependent reads and branches, some thousand
+// (Per id the work is a chain of dependent reads and branches, up to some 15,000
 // cycles long, so what counts is how few ids a lane takes one after the other
 // and that no wave waits for another in between.)
 template <int MW, bool Full>
@@ -2619,7 +2613,7 @@ __device__ int chain_shift(const ParseTabs<L>& pt, mptr<L, uint16_t> stk, uint32
         lo_mod = min(lo_mod, k);
         d = k + (uint32_t)t;
         if (d >= cap) return -1;
-        stk[d++] = shift_target<L, MW>(pt, s, x, true);  // the LALR stack
+        stk[d++] = shift_target<L, MW>(pt, s, x);
       }
       return 1;
     }
@@ -3095,10 +3089,9 @@ bool bound(const grid_compiled* g, int which) {
   return g->dev[which] != nullptr || (grid_artifact(g, which, &p, &n) == GRID_OK && n == 0);
 }
 
-// Raises a kernel's dynamic-LDS limit (needed above 64 KB of LDS in total)
-// once per kernel, device and size.
-// Raises a kernel's dynamic LDS limit once per (kernel, device, size); the
-// record of what was raised is shared by all host threads.
+// Raises a kernel's dynamic-LDS limit (needed above 64 KB of LDS in total) once
+// per (kernel, device, size); the record of what was raised is shared by all host
+// threads.
 bool raise_lds(const void* fn, uint32_t bytes) {
   struct Entry {
     const void* fn;
@@ -3142,8 +3135,8 @@ int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint1
     if (!raise_lds((const void*)prologue, pro) || !raise_lds((const void*)judge_kernel<MW>, jud))
       return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
     hipLaunchKernelGGL(prologue, dim3(B), dim3(kProThreads), pro, s, tb, cfg_dev, pool, mask, eos, status, ws, rb);
-    // a row's classes: as many parts as leave one workgroup per compute unit for
-    // the batch (each stages the tables anew), at most one block of classes each
+    // a row's classes: as many parts as make four workgroups per compute unit over
+    // the batch (each stages the tables anew), at least one block of classes each
     const int blocks = std::max(1, (tb.max_classes + kJudgeThreads - 1) / kJudgeThreads);
     const int parts = std::max(1, std::min(4 * compute_units() / B, blocks));
     hipLaunchKernelGGL(judge_kernel<MW>, dim3((uint32_t)B * (uint32_t)parts), dim3(kJudgeThreads), jud, s, tb, ws, rb, parts);
@@ -3151,7 +3144,7 @@ int launch_mask(const Tables& tb, int B, const grid_config* cfg_dev, const uint1
   if (phases & GRID_PHASE_WALK) {
     const uint32_t lds = stream_lds(tb).total;
     if (!raise_lds((const void*)stream_kernel, lds)) return fail(GRID_E_HIP, "grid_mask: cannot raise the LDS limit");
-    // a row's slices: four workgroups per compute unit over the batch (their
+    // a row's slices: three workgroups per compute unit over the batch (their
     // LDS lets them share one), at least one wave step each
     const int steps = stream_steps(tb.V);
     const int want = std::max(1, std::min(3 * compute_units() / B, steps));

@@ -481,8 +481,8 @@ void build_mask_actions(Parser& P, const std::vector<int>& unit) {
   }
 }
 
-// Compact tables for simulating a whole set of lookahead terminals at once:
-// per state the terminals that shift (or accept, end-of-input column), the
+// Compact tables of the device advance, which runs one terminal's chain at a time
+// on whole LALR stacks: per state the terminals that shift (or accept, end-of-input column), the
 // terminals reduced by the state's main production, and any further reduce
 // productions with their own terminal sets; productions appear as
 // lhs | length << 16 (empty runs folded in, see below), so a reduce needs no
@@ -534,8 +534,8 @@ void compact_tables(Parser& P) {
   for (int s = 0; s < P.n_states; ++s) {
     uint32_t* rec = &P.pstate[(size_t)s * stride];
     // an empty production's terminals take their run's reduction when they
-    // all share one (so the state keeps its number of reduce groups, which is
-    // what the set simulation pays for)
+    // all share one (so the state keeps its number of reduce groups, which a
+    // chain step scans)
     std::map<int, uint32_t> run_of;  // empty production -> the shared run (0 none)
     for (int t = 0; t < T1; ++t) {
       const uint16_t a = P.act(s, t);
@@ -588,7 +588,8 @@ void compact_tables(Parser& P) {
       if ((a & 0xC000) == kActShift) P.pshift.push_back((uint16_t)(a & 0x3FFF));
       else if ((a & 0xC000) == kActAccept) P.pshift.push_back(0);
     }
-    // the mask kernels' shift targets: a shift into a unit state (its one
+    // the mask path's shift targets (exported; the kernels have them in the dense
+    // actions): a shift into a unit state (its one
     // reduction pops the shifted entry) goes where that reduction leads, as a
     // GOTO into one does; the stack differs from the LALR one only by that
     // pending reduction, which any lookahead the unit state would accept
