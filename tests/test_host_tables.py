@@ -302,3 +302,95 @@ def test_calls_on_unbound_artifacts_are_refused(G, call):
         assert run(handle(full - {left_out})) == unbound, left_out
     for n in empty:
         assert run(handle(full - {n})) not in (0, unbound), n
+
+
+def reduced_program(term_info, dense, accepts, q, sp):
+    """The reduced program of spelling sp from lexer state q, in its own words: the
+    lexemes that are kept (state, first byte, end), whether dropped ones held the
+    pending bytes, whether byte 0 ends a kept one, the state after the last byte
+    and the trailing lexeme's first byte.  None if the lexer rejects it."""
+    cur, lexemes, first = q, [], 0
+    for i, b in enumerate(sp):
+        nxt = int(dense[cur, b])
+        if nxt == 0:
+            if not accepts[cur]:
+                return None
+            lexemes.append((cur, first, i))
+            first, nxt = i, int(dense[1, b])
+            if nxt == 0:
+                return None
+        cur = nxt
+    plain = lambda t: term_info[t] & 1 and term_info[t] >> 8 == 0xFF
+    kept = [x for x in lexemes if not plain(accepts[x[0]][0])]
+    fresh = bool(lexemes) and plain(accepts[lexemes[0][0]][0])
+    return kept, fresh, bool(kept) and kept[0][2] == 0, cur, first
+
+
+@pytest.mark.parametrize("name", ["expr", "sql_select", "sql_dml"])
+def test_reduced_class_tables(G, name):
+    rng = np.random.default_rng(12)
+    alphabet = np.frombuffer(b"selct frmwhe*,()'0123456789abcxyz_.=<>;\n\t-\"/+", np.uint8)
+    vocab = [bytes([b]) for b in range(256)]
+    vocab += [bytes(rng.choice(alphabet, int(n))) for n in rng.integers(2, 24, 400)]
+    vocab += [b"SELECT", b" FROM", b"'abc'", b"),", b"1;", b"x" * 200, b"", b"a b c d e", b" a  b\tc", b"a.b.c.d.e",
+              b" ( ( ( (", b"a , b , c", b"1 + 2 + 3 + 4", b"  ", b" a", b"a ", b"\n\t 1"]
+    specials = [3]
+    g = G.Grid(grammar_text(name), (), vocab, specials)
+    info = g.info()
+    S, V, T = info["n_dfa_states"], info["vocab_size"], info["n_terminals"]
+    dense = np.frombuffer(g.artifact("DFA_DENSE"), np.uint16).reshape(S, 256)
+    aoff = np.frombuffer(g.artifact("DFA_ACCEPT_OFF"), np.uint32).tolist()
+    alist = np.frombuffer(g.artifact("DFA_ACCEPT_LIST"), np.uint8).tolist()
+    accepts = [alist[aoff[q]:aoff[q + 1]] for q in range(S)]
+    term_info = np.frombuffer(g.artifact("TERM_INFO"), np.uint32).tolist()
+    words = np.frombuffer(g.artifact("DFA_LIVE"), np.uint32).reshape(S, 8)
+    live = [[t for t in range(T) if int(words[q, t >> 5]) >> (t & 31) & 1] for q in range(S)]
+    category = lambda t: term_info[t] >> 8 != 0xFF
+    any_trail = [any(term_info[t] & 1 and not category(t) for t in live[q]) for q in range(S)]
+    cmap = np.frombuffer(g.artifact("PROG_MAP"), np.uint16).reshape(S, V)
+    coff = np.frombuffer(g.artifact("PROG_OFF"), np.uint32)
+    rec = np.frombuffer(g.artifact("PROG_REC"), np.uint32).reshape(-1, 4)
+    assert coff[0] == 0 and coff[-1] == len(rec)
+    stands, kinds, fresh_seen = {}, set(), 0
+    blank = [q for q in range(S) if accepts[q] and term_info[accepts[q][0]] & 1]  # in an ignored lexeme
+    states = sorted({1, *blank, *rng.choice(S, min(S, 60), replace=False).tolist()})
+    for q in states:
+        recs = rec[coff[q]:coff[q + 1]].tolist()
+        assert recs[0] == [8, 0, 0, 0] and recs[1] == [32, 0, 0, 0]
+        assert len({tuple(r) for r in recs}) == len(recs)
+        for t, sp in enumerate(vocab):
+            want = None if (t in specials or not sp) else reduced_program(term_info, dense, accepts, q, sp)
+            c = int(cmap[q, t])
+            if want is None:
+                assert c == 0, (q, sp)
+                continue
+            assert c >= 2, (q, sp)
+            kept, fresh, p0, last, trail = want
+            w0, w1, w2, w3 = recs[c]
+            n = w0 & 7
+            assert n == min(len(kept), 4) and bool(w0 & 16) == p0 and bool(w0 & 64) == fresh, (q, sp)
+            kinds.add(n)
+            fresh_seen += fresh
+            starts = [w3 >> 24, w0 >> 8 & 0xFF, w0 >> 16 & 0xFF]
+            at = [w1 >> 16, w2 & 0xFFFF, w2 >> 16]
+            ends = [w3 & 0xFF, w3 >> 8 & 0xFF, w3 >> 16 & 0xFF]
+            for i in range(3):
+                if i >= len(kept):
+                    assert (at[i], starts[i], ends[i]) == (0, 0, 0), (q, sp)
+                    continue
+                state, first, end = kept[i]
+                assert at[i] == state, (q, sp)
+                asks = any(category(x) for x in accepts[state])
+                assert starts[i] == (first if asks else 0), (q, sp)
+                assert ends[i] == (end if asks or (n == 4 and i == 2) else 0), (q, sp)
+            if n == 4:
+                assert w1 & 0xFFFF == 0 and w0 >> 24 == 0, (q, sp)
+                continue
+            if any_trail[last]:  # one state stands for all of them
+                assert any_trail[w1 & 0xFFFF], (q, sp)
+                stands.setdefault("trail", set()).add(w1 & 0xFFFF)
+                assert w0 >> 24 == 0, (q, sp)
+            else:
+                assert w1 & 0xFFFF == last, (q, sp)
+                assert w0 >> 24 == (trail if any(category(x) for x in live[last]) else 0), (q, sp)
+    assert len(stands.get("trail", {0})) == 1 and {0, 1, 2, 3} <= kinds and fresh_seen > 0
