@@ -12,8 +12,8 @@ between them; the per-step latency from a second pass with an event pair
 around each step (p50/p99 per mask are that step latency divided by B, i.e.
 amortized over the batch); the phase split from a third pass with events
 between the launches, all on the launch stream.  The roofline is the whole
-mask call's: the algorithmic bytes of B masks over the summed mask-phase
-time, with each phase's own figure beside it.
+mask call's: the algorithmic bytes of B masks over the sum of the median
+mask-phase times, with each phase's own figure beside it.
 
 Beside the headline line: the 256-schema workload (B = 256, one lexicon per
 row) with its fused bf16 apply in GB/s, the small workloads' throughputs, the
@@ -496,7 +496,8 @@ def main():
         grid.mask(c, p, B, mask, eos, status, ws, stream)
         G.apply(mask, logits, stream)
 
-    phases = (G.grid.PHASE_PROLOGUE, G.grid.PHASE_WALK, G.grid.PHASE_RESIDUE, G.grid.PHASE_FINALIZE)
+    # (without a cache the last phase launches nothing beside the residue's)
+    phases = (G.grid.PHASE_PROLOGUE, G.grid.PHASE_WALK, G.grid.PHASE_RESIDUE | G.grid.PHASE_FINALIZE)
 
     def step_phases(i, ev):
         c, p = batches[i % len(batches)]
@@ -505,7 +506,7 @@ def main():
             grid.mask(c, p, B, mask, eos, status, ws, stream, phases=ph)
             ev[k + 1].record(stream)
         G.apply(mask, logits, stream)
-        ev[5].record(stream)
+        ev[4].record(stream)
 
     for i in range(args.warmup):
         step(i)
@@ -529,13 +530,14 @@ def main():
     step_us = np.array([e0.elapsed_time(e1) for e0, e1 in pairs]) * 1000.0
 
     # phase times on the launch stream, events between the launches
-    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(6)] for _ in range(args.steps)]
+    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(5)] for _ in range(args.steps)]
     for i in range(args.steps):
         step_phases(i, evs[i])
     torch.cuda.synchronize()
-    ph_ms = np.array([[e[k].elapsed_time(e[k + 1]) for k in range(5)] for e in evs])  # [steps, 5]
-    ph_mean_s = ph_ms.mean(axis=0) / 1000.0
-    mask_s = float(ph_mean_s[:4].sum())
+    ph_ms = np.array([[e[k].elapsed_time(e[k + 1]) for k in range(4)] for e in evs])  # [steps, 4]
+    # (medians: the first of a short run's launches are an order slower)
+    ph_s = np.median(ph_ms, axis=0) / 1000.0
+    mask_s = float(ph_s[:3].sum())
 
     # roofline of the whole mask call: the algorithmic bytes of the B masks
     # of a step (mean over the batches cycled) over the summed phase time;
@@ -544,15 +546,14 @@ def main():
     achieved = bytes_step / mask_s / 1e9
     stream_bytes = B * (2 * wl.V + 4 * grid.W)
     per_phase = {
-        "prologue+verdicts": {"us": ph_mean_s[0] * 1e6},
-        "stream": {"us": ph_mean_s[1] * 1e6, "bytes": stream_bytes,
-                   "achieved_gbs": stream_bytes / ph_mean_s[1] / 1e9,
-                   "frac": stream_bytes / ph_mean_s[1] / 1e9 / HBM_PEAK_GBS},
-        "residue": {"us": ph_mean_s[2] * 1e6},
-        "publish": {"us": ph_mean_s[3] * 1e6},
-        "apply": {"us": ph_mean_s[4] * 1e6},
+        "prologue+verdicts": {"us": ph_s[0] * 1e6},
+        "stream": {"us": ph_s[1] * 1e6, "bytes": stream_bytes,
+                   "achieved_gbs": stream_bytes / ph_s[1] / 1e9,
+                   "frac": stream_bytes / ph_s[1] / 1e9 / HBM_PEAK_GBS},
+        "residue": {"us": ph_s[2] * 1e6},
+        "apply": {"us": ph_s[3] * 1e6},
     }
-    dominant = max(("prologue+verdicts", "stream", "residue", "publish"), key=lambda k: per_phase[k]["us"])
+    dominant = max(("prologue+verdicts", "stream", "residue"), key=lambda k: per_phase[k]["us"])
 
     out = {
         "metric": "cold next-token masks/s at B=32, V=151,936; p50/p99 us per mask",
@@ -584,7 +585,7 @@ def main():
                      "mask_us_per_launch": mask_s * 1e6, "dominant_phase": dominant,
                      "per_phase": per_phase,
                      "note": "bytes = B x (2V class map + 4W mask words + 32 config) + 2 x stack entries; "
-                             "time = summed phase times of one grid_mask call on the launch stream"},
+                             "time = summed median phase times of one grid_mask call on the launch stream"},
     }
 
     extra = {}
