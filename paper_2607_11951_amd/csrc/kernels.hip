@@ -845,7 +845,7 @@ __host__ __device__ inline ProLds prologue_lds(const Tables& tb) {
 // lexicon continuation bits of the pending lexeme beside them; then the allowed
 // set of the stack after each allowed terminal's shift, a wave per 64 terminals,
 // the end of input one of them; then the pending lexeme's winner and the row
-// block.  Bound by the longest reduce chain and the staging of the tables: 12.6 us
+// block.  Bound by the longest reduce chain and the staging of the tables: 12.9 us
 // at 32 DML rows (V = 151,936), 17.7 with the compact tables and a set simulation.
 template <int MW, bool L>
 __global__ __launch_bounds__(kProThreads) void prologue_kernel(Tables tb, const grid_config* __restrict__ cfgs,
@@ -1498,7 +1498,8 @@ __host__ __device__ inline JudgeLds judge_lds(const Tables& tb) {
 // (The sets after two shifts can be had too: a row's classes ask for some 15 pairs
 // of terminals.  Finding them and judging those classes again took each workgroup
 // 5 us, in all 8 to 12 us of a step of 1 to 47 rows; walking their ids as well costs
-// the residue kernel 1 to 3 us.  At 256 rows, 20 us less residue paid for it.)
+// the residue kernel 1 to 3 us.  At 256 rows, 20 us less residue paid for it.
+// Measured when a step of 32 rows took 89 us and one of 256 rows 350.)
 template <int MW>
 __global__ __launch_bounds__(kJudgeThreads, 8) void judge_kernel(Tables tb, uint8_t* __restrict__ ws, size_t rbytes,
                                                               int parts) {
@@ -1583,8 +1584,8 @@ __device__ __forceinline__ int lane_rank(uint64_t bal) {
 // the row's continuation tables, or from its token-flag summary), or when that
 // question is a trailing one the token's prefix flags answer.  What stays
 // open is listed for the residue kernel, and marked in the row's open bitmap for
-// the row that has more than its list holds.  16 bytes of class map per lane: 13.2 us
-// at 32 rows of 151,936 ids and 58 us at 256 (64 ids per wave and one 2-byte load
+// the row that has more than its list holds.  16 bytes of class map per lane: 13.1 us
+// at 32 rows of 151,936 ids and 59 us at 256 (64 ids per wave and one 2-byte load
 // per lane: 20.8 and 123 us).  Bound by the open ids' chains of dependent lookups:
 // reading a batch's first lookups while the one before it is settled took it from 65
 // to 58 us at 256 rows; neither packing the queue with half the instructions nor
@@ -2168,10 +2169,10 @@ __device__ __forceinline__ int find_chunk(const uint32_t* counts, const uint32_t
   return -1;
 }
 
-// The largest part of a call: 42 us at 32 DML rows, 149 at 256 with a schema each
-// (55.9 and 261 when a workgroup took whole words of a row's bitmap and simulated
-// allowed sets), 20 to 26 us for the smallest calls, where a single id's chain
-// is all of it.
+// The largest part of a call: 37 to 40 us at 32 DML rows (V = 151,936) by what the
+// rows allow, 147 at 256 with a schema each (55.9 and 261 when a workgroup took
+// whole words of a row's bitmap and simulated allowed sets), 18 to 28 us for the
+// smallest calls, where a single id's chain is all of it.
 // The ids the stream left open, dealt evenly to the workgroups: a chunk is K
 // open ids of one row, K set by the batch's total, so a row with many costs no
 // workgroup more than a row with few.  The waves of the workgroup take a few ids
@@ -2849,7 +2850,7 @@ __host__ __device__ inline uint32_t accept_stack_cap(uint32_t cap) { return cap 
 // read).  While the other waves stage, wave 0 reads the token's bytes and follows
 // the lexicon trie from every byte it may start a lexeme at, a lane each, and
 // wave 1 copies the stack: read by the advancing thread in turn, a byte's trie
-// node was a global read each.  256 DML rows out of place take 13.2 us (15.7 with
+// node was a global read each.  256 DML rows out of place take 14.4 us (2.5 more with
 // one thread reading the token and the trie after the staging and trying the
 // trailing lexeme's terminals in turn).
 // Every row's output is self-contained, whatever its status: the input stack
